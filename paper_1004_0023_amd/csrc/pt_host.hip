@@ -737,6 +737,12 @@ struct pt_ctx {
     // graph of whole cycles for pt_run
     hipGraphExec_t graph = nullptr;
     int graph_cycles = 0;
+    // read-back: a pinned buffer for one instance's observables and the device error word,
+    // and up to two of kSpinChunk bytes for spins (allocated on first use)
+    char *obs_pin = nullptr;
+    char *spin_pin = nullptr;
+    size_t spin_pin_bytes = 0;
+    hipEvent_t spin_ev[2] = {nullptr, nullptr};
     // timing
     std::vector<hipEvent_t> ev_pool;
     std::vector<std::pair<int, int>> sweep_ev, exch_ev;  // indices into ev_pool
@@ -1054,6 +1060,8 @@ void journal_add(pt_ctx *c, int kind, int n)
     if (c->shadow && !c->replaying) c->journal.emplace_back(kind, n);
 }
 
+int check_err(pt_ctx *c, uint32_t err);
+
 // Wait for the stream, then check the device error word (a resident slice-block launch
 // that gave up a wait, an octet kernel that refused to run).  After a wait that gave up,
 // the state is restored from the copy of the last clean synchronisation and the calls
@@ -1063,9 +1071,16 @@ void journal_add(pt_ctx *c, int kind, int n)
 // synchronisation after new calls takes a new copy.
 int sync_and_check(pt_ctx *c)
 {
+    uint32_t *err = reinterpret_cast<uint32_t *>(c->obs_pin);
+    HIP_TRY(launch_gather_err(c->st, err, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    uint32_t err = 0;
-    HIP_TRY(hipMemcpy(&err, c->ws + c->plan.o_err, 4, hipMemcpyDeviceToHost));
+    return check_err(c, *err);
+}
+
+// The second half of sync_and_check, with the error word read by a launch that the stream
+// has been waited for.
+int check_err(pt_ctx *c, uint32_t err)
+{
     if (err != 0) {
         c->last_device_error = err;
         const uint32_t zero = 0;
@@ -1702,6 +1717,13 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     if (P.encoding == PT_BITPACK32) {
         c->block_threads = opt->block_threads > 0 ? opt->block_threads : 256;
     }
+    int32_t most_R = 2;
+    for (const auto &d : P.desc) most_R = std::max(most_R, d.R);
+    e = hipHostMalloc((void **)&c->obs_pin, (size_t)ObsLayout(most_R).bytes, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        c->obs_pin = nullptr;
+        return cleanup(fail(PT_ENOMEM, "hipHostMalloc of the read-back buffer failed"));
+    }
     const bool tune_int8 = P.encoding == PT_INT8 && opt->tile_replicas == 0 &&
                            opt->tile_bytes == 0 && opt->block_threads == 0;
     // packed: the workgroup size of the whole-octet launch
@@ -1868,36 +1890,42 @@ int pt_observables(pt_ctx *c, int32_t inst, pt_obs *o)
     if (rc) return rc;
     if (!o) return fail(PT_EINVAL, "null output");
     const InstDesc &d = c->plan.desc[inst];
-    const int R = d.R, b = d.rep_base, pb = d.pair_base;
-    char *w = c->ws;
-    const Plan &P = c->plan;
-    auto get = [&](void *dst, size_t off, size_t bytes) -> int {
-        if (!dst || !bytes) return PT_OK;
-        HIP_TRY(hipMemcpyAsync(dst, w + off, bytes, hipMemcpyDeviceToHost, c->stream));
-        return PT_OK;
+    const ObsLayout L(d.R);
+    const char *pin = c->obs_pin;
+    uint32_t err = 0;
+    for (int attempt = 0;; ++attempt) {
+        HIP_TRY(launch_gather_obs(c->st, L, inst, d.rep_base, d.pair_base, c->obs_pin, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        std::memcpy(&err, pin + L.err, 4);
+        if (err == 0 || attempt > 0) break;
+        // the recovery (or the failure) of a plain synchronisation, then what it left
+        if ((rc = check_err(c, err))) return rc;
+    }
+    if ((rc = check_err(c, err))) return rc;
+    auto get = [&](void *dst, int32_t at, int32_t bytes) {
+        if (dst) std::memcpy(dst, pin + at, (size_t)bytes);
     };
-    std::vector<int32_t> label(R);
-    Counters ctr{};
-    if ((rc = get(o->E_cl, P.o_E + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->C, P.o_C + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->rung_of, P.o_rung + (size_t)b * 4, (size_t)R * 4))) return rc;
-    if ((rc = get(o->replica_of, P.o_repof + (size_t)b * 4, (size_t)R * 4))) return rc;
-    if ((rc = get(o->acc, P.o_acc + (size_t)pb * 8, (size_t)(R - 1) * 8))) return rc;
-    if ((rc = get(o->att, P.o_att + (size_t)pb * 8, (size_t)(R - 1) * 8))) return rc;
-    if ((rc = get(o->roundtrips, P.o_rt + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(label.data(), P.o_label + (size_t)b * 4, (size_t)R * 4))) return rc;
-    if ((rc = get(o->sumE, P.o_sumE + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->sumC, P.o_sumC + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->sumE2, P.o_sumE2 + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->sumC2, P.o_sumC2 + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->nup, P.o_nup + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->ndown, P.o_ndown + (size_t)b * 8, (size_t)R * 8))) return rc;
-    if ((rc = get(o->sumCt, P.o_sumCt + (size_t)b * PT_TAU_LAGS * 8, (size_t)R * PT_TAU_LAGS * 8)))
-        return rc;
-    if ((rc = get(&ctr, P.o_ctr + (size_t)inst * sizeof(Counters), sizeof(Counters)))) return rc;
-    if ((rc = sync_and_check(c))) return rc;
-    if (o->label)
+    const int R = d.R;
+    get(o->E_cl, L.E, 8 * R);
+    get(o->C, L.C, 8 * R);
+    get(o->rung_of, L.rung, 4 * R);
+    get(o->replica_of, L.repof, 4 * R);
+    get(o->acc, L.acc, 8 * (R - 1));
+    get(o->att, L.att, 8 * (R - 1));
+    get(o->roundtrips, L.rt, 8 * R);
+    get(o->sumE, L.sumE, 8 * R);
+    get(o->sumC, L.sumC, 8 * R);
+    get(o->sumE2, L.sumE2, 8 * R);
+    get(o->sumC2, L.sumC2, 8 * R);
+    get(o->nup, L.nup, 8 * R);
+    get(o->ndown, L.ndown, 8 * R);
+    get(o->sumCt, L.sumCt, 8 * PT_TAU_LAGS * R);
+    if (o->label) {
+        const int32_t *label = reinterpret_cast<const int32_t *>(pin + L.label);
         for (int r = 0; r < R; ++r) o->label[r] = (int8_t)label[r];
+    }
+    Counters ctr{};
+    get(&ctr, L.ctr, (int32_t)sizeof ctr);
     o->t = ctr.t;
     o->e = ctr.e;
     o->n_acc = ctr.n_acc;
@@ -1924,34 +1952,55 @@ static inline size_t spin_pos(const InstDesc &d, int k, int i)
     return (size_t)p * d.N * d.Mh + (size_t)i * d.Mh + m;
 }
 
+// The device writes the spins in the caller's order into two pinned buffers by turns, and the
+// host copies one out while the other fills.
 int pt_get_spins(pt_ctx *c, int32_t inst, int8_t *out)
 {
     int rc = check_inst(c, inst);
     if (rc) return rc;
     if (!out) return fail(PT_EINVAL, "null output");
     const InstDesc &d = c->plan.desc[inst];
-    if (c->plan.encoding == PT_BITPACK32) {
-        std::vector<uint32_t> wb((size_t)bp_words(d));
-        HIP_TRY(hipMemcpyAsync(wb.data(), c->ws + c->plan.o_spins + d.spin_base, wb.size() * 4,
-                               hipMemcpyDeviceToHost, c->stream));
-        if ((rc = sync_and_check(c))) return rc;
-        for (int r = 0; r < d.R; ++r)
-            for (int k = 0; k < d.M; ++k)
-                for (int i = 0; i < d.N; ++i)
-                    out[((size_t)r * d.M + k) * d.N + i] =
-                        (int8_t)(2 * (int)((wb[bp_pos(d, r, k, i)] >> (r & 31)) & 1u) - 1);
-        return PT_OK;
+    // 2 MiB a buffer: a chunk's launch and wait (about 15 us) are a few percent of the time
+    // the host takes to copy it out
+    constexpr int64_t kSpinChunk = 2 << 20;
+    const int64_t total = (int64_t)d.R * d.M * d.N;
+    const int64_t chunk = std::min(total, kSpinChunk);
+    const int64_t n = (total + chunk - 1) / chunk;
+    const size_t stride = align_up((size_t)chunk, 256);
+    const size_t need = stride * (n > 1 ? 2 : 1);
+    if (c->spin_pin_bytes < need) {
+        if (c->spin_pin) (void)hipHostFree(c->spin_pin);
+        c->spin_pin = nullptr;
+        c->spin_pin_bytes = 0;
+        HIP_TRY(hipHostMalloc((void **)&c->spin_pin, need, hipHostMallocDefault));
+        c->spin_pin_bytes = need;
     }
-    std::vector<uint8_t> buf((size_t)d.R * d.rep_bytes);
-    HIP_TRY(hipMemcpyAsync(buf.data(), c->ws + c->plan.o_spins + d.spin_base, buf.size(),
-                           hipMemcpyDeviceToHost, c->stream));
-    if ((rc = sync_and_check(c))) return rc;
-    for (int r = 0; r < d.R; ++r)
-        for (int k = 0; k < d.M; ++k)
-            for (int i = 0; i < d.N; ++i)
-                out[((size_t)r * d.M + k) * d.N + i] =
-                    (int8_t)(2 * buf[(size_t)r * d.rep_bytes + spin_pos(d, k, i)] - 1);
-    return PT_OK;
+    for (auto &ev : c->spin_ev)
+        if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    uint32_t *err = reinterpret_cast<uint32_t *>(c->obs_pin);
+    auto issue = [&](int64_t j) -> int {
+        const int64_t first = j * chunk;
+        HIP_TRY(launch_gather_spins(c->st, c->plan.encoding == PT_BITPACK32, inst, first,
+                                    (int32_t)std::min(chunk, total - first), c->spin_pin + (j & 1) * stride,
+                                    err, c->stream));
+        HIP_TRY(hipEventRecord(c->spin_ev[j & 1], c->stream));
+        return PT_OK;
+    };
+    for (int attempt = 0;; ++attempt) {
+        for (int64_t j = 0; j < std::min<int64_t>(n, 2); ++j)
+            if ((rc = issue(j))) return rc;
+        HIP_TRY(hipEventSynchronize(c->spin_ev[0]));
+        if (*err == 0 || attempt > 0) break;
+        // the recovery (or the failure) of a plain synchronisation, then the state it left
+        if ((rc = sync_and_check(c))) return rc;
+    }
+    for (int64_t j = 0; j < n; ++j) {
+        if (j > 0) HIP_TRY(hipEventSynchronize(c->spin_ev[j & 1]));
+        const int64_t first = j * chunk;
+        std::memcpy(out + first, c->spin_pin + (j & 1) * stride, (size_t)std::min(chunk, total - first));
+        if (j + 2 < n && (rc = issue(j + 2))) return rc;
+    }
+    return check_err(c, *err);
 }
 
 int pt_set_spins(pt_ctx *c, int32_t inst, const int8_t *in)
@@ -2111,6 +2160,10 @@ void pt_free(pt_ctx *c)
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     drop_graph(c);
     if (c->shadow) (void)hipFree(c->shadow);
+    if (c->obs_pin) (void)hipHostFree(c->obs_pin);
+    if (c->spin_pin) (void)hipHostFree(c->spin_pin);
+    for (auto e : c->spin_ev)
+        if (e) (void)hipEventDestroy(e);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
     for (auto e : c->tune_ev)
         if (e) (void)hipEventDestroy(e);

@@ -136,6 +136,41 @@ hipError_t sweep_kernels_set_lds(int32_t fast_bytes, int32_t generic_bytes, int3
 // holds at once in the resident (persistent) block kernel.
 hipError_t block_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu);
 
+// Byte offsets of one instance's observables in the buffer gather_obs writes: arrays of R
+// (sumCt: R * kTauLags; acc, att: R - 1) in the types of the state region, then the counters
+// and the device error word.
+struct ObsLayout {
+    int32_t R;
+    int32_t E, C, rt, sumE, sumC, sumE2, sumC2, nup, ndown, sumCt, acc, att, ctr, rung, repof, label, err;
+    int32_t bytes;
+    explicit ObsLayout(int32_t R_) : R(R_)
+    {
+        int32_t at = 0;
+        auto take = [&](int32_t n) {
+            const int32_t here = at;
+            at += n;
+            return here;
+        };
+        for (int32_t *a : {&E, &C, &rt, &sumE, &sumC, &sumE2, &sumC2, &nup, &ndown}) *a = take(8 * R);
+        sumCt = take(8 * kTauLags * R);
+        acc = take(8 * (R - 1));
+        att = take(8 * (R - 1));
+        ctr = take((int32_t)sizeof(Counters));
+        for (int32_t *a : {&rung, &repof, &label}) *a = take(4 * R);
+        err = take(4);
+        bytes = at;
+    }
+};
+
+// Into pinned host memory: the observables of instance n; bytes [first, first + bytes) of its
+// spins as int8 in [R][M][N] order (out 16-byte aligned) and the device error word; the error
+// word alone.
+hipError_t launch_gather_obs(const DevState &st, const ObsLayout &o, int32_t n, int32_t rep_base,
+                             int32_t pair_base, void *out, hipStream_t s);
+hipError_t launch_gather_spins(const DevState &st, bool packed, int32_t n, int64_t first, int32_t bytes,
+                               void *out, uint32_t *err_out, hipStream_t s);
+hipError_t launch_gather_err(const DevState &st, uint32_t *out, hipStream_t s);
+
 // Record msg as the calling thread's last error (pt_last_error) and return code.
 int report_error(int code, const char *msg);
 

@@ -7,6 +7,7 @@ is no CPU fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Dict, Iterable, List, Optional, Sequence
 
@@ -221,6 +222,23 @@ def checkpoint_validate(instances: Sequence, seed: int, blob: bytes, **options):
                                         C.cast(buf, C.c_void_p), len(blob), None))
 
 
+@functools.lru_cache(maxsize=64)
+def _obs_layout(R: int):
+    """The arrays of an instance's observables in one buffer, in pt_obs order: (name, byte
+    offset, bytes, dtype, shape), 8-byte aligned, and the buffer's bytes."""
+    i64, u64, i32 = np.int64, np.uint64, np.int32
+    spec = [("E_cl", i64, (R,)), ("C", i64, (R,)), ("rung_of", i32, (R,)), ("replica_of", i32, (R,)),
+            ("acc", u64, (R - 1,)), ("att", u64, (R - 1,)), ("roundtrips", u64, (R,)),
+            ("label", np.int8, (R,)), ("sumE", i64, (R,)), ("sumC", i64, (R,)), ("sumE2", i64, (R,)),
+            ("sumC2", i64, (R,)), ("nup", u64, (R,)), ("ndown", u64, (R,)), ("sumCt", i64, (R, TAU_LAGS))]
+    fields, at = [], 0
+    for name, dtype, shape in spec:
+        size = int(np.prod(shape)) * np.dtype(dtype).itemsize
+        fields.append((name, at, size, dtype, shape))
+        at += (size + 7) // 8 * 8
+    return fields, at
+
+
 class Sampler:
     """A batch of instances sampled by the library (one pt_ctx).
 
@@ -292,26 +310,19 @@ class Sampler:
     # -- state
     def observables(self, n: int = 0) -> Dict[str, np.ndarray]:
         inst = self.instances[n]
-        R = inst.R
-        o = dict(E_cl=np.zeros(R, np.int64), C=np.zeros(R, np.int64),
-                 rung_of=np.zeros(R, np.int32), replica_of=np.zeros(R, np.int32),
-                 acc=np.zeros(R - 1, np.uint64), att=np.zeros(R - 1, np.uint64),
-                 roundtrips=np.zeros(R, np.uint64), label=np.zeros(R, np.int8),
-                 sumE=np.zeros(R, np.int64), sumC=np.zeros(R, np.int64),
-                 sumE2=np.zeros(R, np.int64), sumC2=np.zeros(R, np.int64),
-                 nup=np.zeros(R, np.uint64), ndown=np.zeros(R, np.uint64),
-                 sumCt=np.zeros((R, TAU_LAGS), np.int64))
-        rec = _Obs(*[o[k].ctypes.data for k in ("E_cl", "C", "rung_of", "replica_of", "acc",
-                                                 "att", "roundtrips", "label", "sumE", "sumC",
-                                                 "sumE2", "sumC2", "nup", "ndown")], 0, 0, 0,
-                   o["sumCt"].ctypes.data)
+        fields, nbytes = _obs_layout(int(inst.R))
+        buf = np.zeros(nbytes, np.uint8)  # one allocation; every array is a view of its part
+        base = buf.ctypes.data
+        rec = _Obs(*[base + at for _, at, _, _, _ in fields[:14]], 0, 0, 0, base + fields[14][1])
         _check(lib().pt_observables(self._ctx, int(n), C.byref(rec)))
+        o = {name: buf[at:at + size].view(dtype).reshape(shape)
+             for name, at, size, dtype, shape in fields}
         o["t"], o["e"], o["n_acc"] = int(rec.t), int(rec.e), int(rec.n_acc)
         return o
 
     def spins(self, n: int = 0) -> np.ndarray:
         inst = self.instances[n]
-        out = np.zeros((inst.R, inst.M, inst.N), dtype=np.int8)
+        out = np.empty((inst.R, inst.M, inst.N), dtype=np.int8)
         _check(lib().pt_get_spins(self._ctx, int(n), out.ctypes.data))
         return out
 
