@@ -143,6 +143,9 @@ struct InstDesc {
     // shape): 1 if they run this instance; its first 16-bit octet neighbour entry and its
     // first octet table word (kOctTableWords per rung)
     int32_t oct, oent_base, otbl_base, opad;
+    // WordsMode if the instance's replicas can be swept as word tiles; its neighbour entries
+    // are then N * D words j << 16 | w1 << 8 | w0 from ent_base
+    int32_t words;
 };
 
 // Octet tables: per rung, the acceptance threshold indexed n + 16 sigma + 64 hz, where n is
@@ -162,6 +165,11 @@ constexpr int kOctTableWords = 128;
 //              sums with three-input adds)
 enum EntMode { kEntPerm = 0, kEntXad16 = 2 };
 
+// Word tiles: whether an instance can run as them, and how the table index of a word's spins
+// is formed (by the field bound F): in bytes, partly in bytes, or in 16-bit halves (its
+// biases are then replicated in both halves of a word instead of in every byte).
+enum WordsMode { kWordsNone = 0, kWordsNarrow = 1, kWordsMiddle = 2, kWordsWide = 3 };
+
 // 32-bit words of the fast-path neighbour entries of an instance with N sites and row
 // length D (two 16-bit entries per word under kEntXad16).
 __host__ __device__ __forceinline__ int64_t ent_words(int64_t N, int32_t D, int32_t mode)
@@ -169,7 +177,7 @@ __host__ __device__ __forceinline__ int64_t ent_words(int64_t N, int32_t D, int3
     return mode == kEntXad16 ? (N * D + 1) / 2 : N * D;
 }
 
-enum TileKind { kTileGeneric = 0, kTileFast = 1, kTileBlock = 2 };
+enum TileKind { kTileGeneric = 0, kTileFast = 1, kTileBlock = 2, kTileWords = 3, kTileWordsR = 4 };
 
 struct Tile {
     int32_t inst;  // instance

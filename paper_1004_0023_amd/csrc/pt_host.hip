@@ -270,6 +270,23 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         std::vector<int32_t> cfill(in.n_colors, 0);
         std::vector<uint16_t> sites(in.N);
         for (int i = 0; i < in.N; ++i) sites[cls[in.color[i]] + cfill[in.color[i]]++] = (uint16_t)i;
+        // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and one degree
+        // D <= 8 on the fast shapes (M a power-of-two multiple of 8)
+        if (bp && d.fast && in.n_edges > 0 && in.N <= 32767) {
+            bool ok = D <= 8;
+            for (int e = 0; ok && e < in.n_edges; ++e) ok = std::abs((int)in.edge_J[e]) == 1;
+            for (int i = 0; ok && i < in.N; ++i)
+                ok = std::abs((int)in.h[i]) <= 1 && deg[i + 1] - deg[i] == D;
+            d.oct = ok ? 1 : 0;
+        }
+        // word tiles: byte instances off the fast shapes and bit-packed ones the octet kernels
+        // do not take, where padded neighbour rows and one replica fit a workgroup's LDS (and,
+        // bit-packed, a row's lanes fit the smallest workgroup)
+        if ((bp ? !d.oct && d.G4 <= 64 : !d.fast) &&
+            (int64_t)in.N * d.D * 4 <= kLdsPerWorkgroup) {
+            d.words = words_mode(F);
+            if (words_tile_lds_bytes(d, 1) > kLdsPerWorkgroup) d.words = 0;
+        }
         // fast-path rows: D entries per site, (j << ent_sh) << 16 | w1 << 8 | w0 with w0 / w1 the
         // contribution |J| [J < 0] / |J| [J > 0] of a neighbour whose spin byte is 0 / 1;
         // padding entries point at the site itself with weight 0.  When every |J| = 1, every
@@ -277,7 +294,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         // unit's LDS, the entries shrink to 16 bits (kEntXad16: j * Mh fits 15 bits), so
         // that two such tiles fit one unit.
         d.ent_mode = kEntPerm;
-        if (d.fast) {
+        if (d.fast && !d.words) {
             bool unit = true, regular = true;
             for (int e = 0; e < in.n_edges; ++e) unit = unit && std::abs((int)in.edge_J[e]) == 1;
             for (int i = 0; i < in.N; ++i) regular = regular && deg[i + 1] - deg[i] == d.D;
@@ -294,25 +311,27 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
                     d.ent_mode = kEntXad16;
             }
         }
-        if (d.fast) {
+        if (d.fast || d.words) {
+            const int sh = d.words ? 0 : d.ent_sh;  // word tiles: the entry holds j itself
             std::vector<uint32_t> row;
             for (int i = 0; i < in.N; ++i) {
                 int e = deg[i];
                 for (int k = 0; k < d.D; ++k, ++e) {
-                    uint32_t word = ((uint32_t)i << d.ent_sh) << 16;
+                    uint32_t word = ((uint32_t)i << sh) << 16;
                     if (e < deg[i + 1]) {
                         const int j = entries[e] & 0xFFFF;
                         const int J = entries[e] >> 16;
                         const uint32_t w0 = (J < 0) ? (uint32_t)(-J) : 0u;
                         const uint32_t w1 = (J > 0) ? (uint32_t)J : 0u;
                         word = (d.ent_mode == kEntXad16)
-                                   ? (((uint32_t)j << d.ent_sh) | (J < 0 ? 0x8000u : 0u))
-                                   : ((((uint32_t)j << d.ent_sh) << 16) | (w1 << 8) | w0);
+                                   ? (((uint32_t)j << sh) | (J < 0 ? 0x8000u : 0u))
+                                   : ((((uint32_t)j << sh) << 16) | (w1 << 8) | w0);
                     }
                     row.push_back(word);
                 }
-                const uint32_t b = (uint32_t)(in.h[i] - sumabs[i] + F) & 0xFFu;
-                P.bias.push_back(b * 0x01010101u);
+                // in every byte, or (wide table index of word tiles) in both halves
+                const uint32_t b = (uint32_t)(in.h[i] - sumabs[i] + F);
+                P.bias.push_back(d.words == kWordsWide ? b * 0x00010001u : (b & 0xFFu) * 0x01010101u);
             }
             if (d.ent_mode == kEntXad16) {
                 for (size_t k = 0; k < row.size(); k += 2)
@@ -322,16 +341,6 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
             }
         } else {
             for (int i = 0; i < in.N; ++i) P.bias.push_back(0);
-        }
-        // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and one degree
-        // D <= 8 on the fast shapes (M a power-of-two multiple of 8)
-        d.oct = 0;
-        if (bp && d.fast && in.n_edges > 0 && in.N <= 32767) {
-            bool ok = D <= 8;
-            for (int e = 0; ok && e < in.n_edges; ++e) ok = std::abs((int)in.edge_J[e]) == 1;
-            for (int i = 0; ok && i < in.N; ++i)
-                ok = std::abs((int)in.h[i]) <= 1 && deg[i + 1] - deg[i] == D;
-            d.oct = ok ? 1 : 0;
         }
         if (d.oct) {
             // entries and field codes padded to 16 bytes per instance (the kernels copy them
@@ -373,6 +382,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         P.n_adj.push_back(2 * in.n_edges);
         // byte-encoding tiles and slice-block records (the bit-packed kernels use neither)
         if (P.encoding == PT_INT8) P.max_tiles += (int64_t)in.R * std::max(1, d.G4);
+        else if (d.words) P.max_tiles += in.R;
         if (d.fast && P.encoding == PT_INT8) {
             // boundary records for slice blocks: three N-word rows per block, at most one
             // block per four-slice group, for every instance that may run as blocks
@@ -387,7 +397,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         adjb += 2 * (int64_t)in.n_edges;
         offb += in.N + 1;
         siteb += in.N;
-        entb += d.fast ? ent_words(in.N, d.D, d.ent_mode) : 0;
+        entb += d.fast || d.words ? ent_words(in.N, d.D, d.ent_mode) : 0;
         clsb += in.n_colors + 1;
         tblb += (int64_t)in.R * d.tbl_words;
         spinb += bp ? (int64_t)d.bp_W * d.parities * in.N * d.bp_row * 4
@@ -400,6 +410,13 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
     P.total_pairs = pair;
     P.spin_bytes = spinb;
     if (bp) {
+        // A batch that also holds octet slice blocks keeps its other instances on the
+        // per-class kernel: the blocks already take a clear and a resident launch per call.
+        bool blocks_too = false;
+        for (const auto &d : P.desc)
+            blocks_too = blocks_too || (d.oct && oct_lds_bytes(d, d.G4, kOctTile) > kLdsPerWorkgroup / 2);
+        for (auto &d : P.desc)
+            if (blocks_too) d.words = 0;
         // sweep blocks: colour g of every instance that has it, 256 items per block
         int max_colors = 0;
         for (const auto &d : P.desc) max_colors = std::max(max_colors, d.n_colors);
@@ -407,7 +424,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
             const int32_t first = (int32_t)(P.bp_sblk.size() / 2);
             for (int n = 0; n < n_inst; ++n) {
                 const InstDesc &d = P.desc[n];
-                if (g >= d.n_colors || d.oct) continue;
+                if (g >= d.n_colors || d.oct || d.words) continue;
                 const int64_t sg = P.cls_off[d.cls_base + g + 1] - P.cls_off[d.cls_base + g];
                 const int64_t items = (int64_t)d.bp_W * sg * d.G4 * kBpSweepLanes;
                 for (int64_t it = 0; it < items; it += kBpThreadsHost) {
@@ -442,7 +459,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         for (int n = 0; n < n_inst; ++n) {
             const InstDesc &d = P.desc[n];
             if (!d.oct) {
-                P.bp_generic = true;
+                P.bp_generic = P.bp_generic || !d.words;
                 continue;
             }
             const bool whole = oct_lds_bytes(d, d.G4, kOctTile) <= kLdsPerWorkgroup / 2;
@@ -694,8 +711,9 @@ struct pt_ctx {
     pt_options opt{};
     uint32_t key_flip0 = 0, key_flip1 = 0, key_swap0 = 0, key_swap1 = 0;
     // launch shape
-    std::vector<Tile> tiles;   // fast-kernel tiles, then generic ones, then slice blocks
-    int n_fast_tiles = 0, n_generic_tiles = 0, n_block_tiles = 0;
+    // fast-kernel tiles, then word tiles (slices, then replicas), generic ones, slice blocks
+    std::vector<Tile> tiles;
+    int n_fast_tiles = 0, n_words_tiles = 0, n_generic_tiles = 0, n_block_tiles = 0;
     int lds_block = 0;
     // resident slice blocks: compute-unit occupancy for (block threads, block LDS)
     std::pair<int, int> resident_key{-1, -1};
@@ -724,7 +742,7 @@ struct pt_ctx {
     std::vector<double> cand_ms;
     size_t cand_next = 0;
     hipEvent_t tune_ev[2] = {nullptr, nullptr};
-    int lds_fast = 0, lds_generic = 0;
+    int lds_fast = 0, lds_words = 0, lds_generic = 0;
     int max_P = 1;
     int lds_limit = 65536;     // LDS one workgroup may use
     int cu_lds = 65536;        // LDS of one compute unit
@@ -777,10 +795,46 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     if (tile_bytes > 0) target_bytes = tile_bytes;
     c->tile_bytes = (int)target_bytes;
     const bool force_blocks = (c->opt.flags & PT_FLAG_SLICE_BLOCKS) != 0;
-    std::vector<Tile> fast, generic, block;
-    int lds_f = 0, lds_g = 0, lds_b = 0, maxP = 1;
+    std::vector<Tile> fast, words, generic, block;
+    int lds_f = 0, lds_w = 0, lds_g = 0, lds_b = 0, maxP = 1;
+    int64_t words_reps = 0;
+    for (const auto &d : P.desc) words_reps += d.words ? d.R : 0;
     for (int n = 0; n < (int)P.desc.size(); ++n) {
         const InstDesc &d = P.desc[n];
+        if (d.words && words_lanes(d, 1) <= c->block_threads) {
+            // Replicas per word tile: the target bytes, but as few as leave every compute
+            // unit a tile (a tile's sweep is a chain of class steps, so a unit without one
+            // idles for the whole call: 512 replicas of 10^3 spins at M = 1 take 33 us a cycle
+            // in 256 tiles of 2 and 55 us in 64 tiles of 8; 768 packed replicas of 128 x 64
+            // spins 95 us in 768 tiles and 204 us in 96); a lane per word of a site, half a
+            // unit's LDS.
+            int p = force_P > 0 ? force_P
+                                : (int)std::min<int64_t>(target_bytes / ((int64_t)d.N * d.M),
+                                                         words_reps / c->cus);
+            p = std::max(1, std::min(p, d.R));
+            auto fits = [&](int q, int lds) {
+                return words_lanes(d, q) <= c->block_threads && words_tile_lds_bytes(d, q) <= lds;
+            };
+            while (p > 1 && !fits(p, force_P > 0 ? c->lds_limit : c->cu_lds / 2)) --p;
+            if (fits(p, c->lds_limit)) {
+                const int kind = d.M <= 2 ? kTileWordsR : kTileWords;
+                // bit-packed tiles stay within a word group
+                const int group = P.encoding == PT_BITPACK32 ? 32 : d.R;
+                for (int c0 = 0; c0 < d.R;) {
+                    const int q = std::min({p, d.R - c0, group - c0 % group});
+                    words.push_back(Tile{n, c0, q, kind, 0, d.G4});
+                    lds_w = std::max(lds_w, words_tile_lds_bytes(d, q));
+                    maxP = std::max(maxP, q);
+                    c0 += q;
+                }
+                continue;
+            }
+        }
+        if (P.encoding == PT_BITPACK32) {
+            if (!d.words) continue;  // octets and the per-class kernel
+            return fail(PT_EINVAL, "instance " + std::to_string(n) +
+                                       ": a word tile needs more LDS than the device has");
+        }
         int pmax = 0;
         for (int p = d.R; p >= 1; --p)
             if (sweep_tile_lds_bytes(d, P.n_adj[n], p) <= c->lds_limit &&
@@ -843,19 +897,26 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     // the list into occupancy classes (see launch_groups) and each class starts with its
     // largest tiles: the device dispatches workgroups roughly in order, so the longest work
     // starts earliest (the paper's "hardest chains first" work pool, Section 4).
-    auto lds_of = [&](const Tile &t) { return sweep_tile_lds_bytes(P.desc[t.inst], P.n_adj[t.inst], t.P); };
+    auto lds_of = [&](const Tile &t) {
+        return t.kind == kTileWords || t.kind == kTileWordsR
+                   ? words_tile_lds_bytes(P.desc[t.inst], t.P)
+                   : sweep_tile_lds_bytes(P.desc[t.inst], P.n_adj[t.inst], t.P);
+    };
     auto bigger = [&](const Tile &a, const Tile &b) {
+        if (a.kind != b.kind) return a.kind < b.kind;
         const int la = lds_of(a), lb = lds_of(b);
         if (la != lb) return la > lb;
         const InstDesc &da = P.desc[a.inst], &db = P.desc[b.inst];
         return (int64_t)a.P * da.M * da.N > (int64_t)b.P * db.M * db.N;
     };
     std::stable_sort(fast.begin(), fast.end(), bigger);
+    std::stable_sort(words.begin(), words.end(), bigger);
     std::stable_sort(generic.begin(), generic.end(), bigger);
-    if ((int64_t)(fast.size() + generic.size() + block.size()) > P.max_tiles)
+    const size_t n_whole = fast.size() + words.size() + generic.size();
+    if ((int64_t)(n_whole + block.size()) > P.max_tiles)
         return fail(PT_ESTATE, "internal: more tiles than reserved tile slots");
     // slice blocks: global neighbour indices and boundary-record offsets
-    const int block0 = (int)(fast.size() + generic.size());
+    const int block0 = (int)n_whole;
     int64_t hb = 0;
     for (Tile &t : block) {
         t.prev += block0;
@@ -882,14 +943,17 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
         c->block_xcd = rings_in_runs(rings, nb);
     }
     c->tiles = fast;
+    c->tiles.insert(c->tiles.end(), words.begin(), words.end());
     c->tiles.insert(c->tiles.end(), generic.begin(), generic.end());
     c->tiles.insert(c->tiles.end(), block.begin(), block.end());
     c->n_fast_tiles = (int)fast.size();
+    c->n_words_tiles = (int)words.size();
     c->n_generic_tiles = (int)generic.size();
     c->tile_lds.assign(c->tiles.size(), 0);
-    for (size_t k = 0; k < fast.size() + generic.size(); ++k) c->tile_lds[k] = lds_of(c->tiles[k]);
+    for (size_t k = 0; k < n_whole; ++k) c->tile_lds[k] = lds_of(c->tiles[k]);
     c->n_block_tiles = (int)block.size();
     c->lds_fast = lds_f;
+    c->lds_words = lds_w;
     c->lds_generic = lds_g;
     c->lds_block = lds_b;
     c->max_P = maxP;
@@ -898,9 +962,11 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     // tiles per instance: a PT cycle's exchange runs in the tile that completes the instance
     c->itiles.assign(P.desc.size(), 0);
     for (const Tile &t : c->tiles) c->itiles[t.inst] += 1;
+    for (int32_t k = 0; k < P.n_otile; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
     HIP_TRY(hipMemcpyAsync(c->ws + P.o_itiles, c->itiles.data(), c->itiles.size() * 4,
                            hipMemcpyHostToDevice, c->stream));
     HIP_TRY(sweep_kernels_set_lds(c->lds_fast, c->lds_generic, c->lds_block));
+    HIP_TRY(words_kernels_set_lds(c->lds_words));
     // Whole-replica tiles: two four-slice words per lane, unless the batch's lanes of one
     // colour class at that width would not give every SIMD of the device one wave; then
     // the sweep is a chain of short, barely parallel class steps, and one word per lane
@@ -1021,7 +1087,12 @@ std::vector<LaunchGroup> launch_groups(const pt_ctx *c)
         }
     };
     add_range(kTileFast, 0, c->n_fast_tiles);
-    add_range(kTileGeneric, c->n_fast_tiles, c->n_fast_tiles + c->n_generic_tiles);
+    const int w0 = c->n_fast_tiles, w1 = w0 + c->n_words_tiles;
+    int wr = w0;  // first word tile of replicas
+    while (wr < w1 && c->tiles[wr].kind == kTileWords) ++wr;
+    add_range(kTileWords, w0, wr);
+    add_range(kTileWordsR, wr, w1);
+    add_range(kTileGeneric, w1, w1 + c->n_generic_tiles);
     return out;
 }
 
@@ -1166,6 +1237,25 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
         if (e != hipSuccess) return hip_fail(e, "octet tile launch");
         O.queue = O.fuse = 0;
     }
+    if (c->n_words_tiles > 0) {
+        SweepLaunch W{};
+        W.st = c->st;
+        W.key0 = c->key_flip0;
+        W.key1 = c->key_flip1;
+        W.n_sweeps = n_sweeps;
+        W.block_threads = c->block_threads;
+        W.fuse_exchange = fuse_exchange ? 1 : 0;
+        W.swap_key0 = c->key_swap0;
+        W.swap_key1 = c->key_swap1;
+        W.t_add = (uint32_t)n_sweeps;
+        for (const LaunchGroup &g : launch_groups(c)) {
+            W.tile0 = g.tile0;
+            W.n_tiles = g.n_tiles;
+            W.lds_bytes = g.lds_bytes;
+            const hipError_t e = launch_sweep(W, g.kind, c->stream);
+            if (e != hipSuccess) return hip_fail(e, "word tile launch");
+        }
+    }
     if (P.n_oblock > 0) {
         O.tile0 = P.n_otile;
         O.n_tiles = P.n_oblock;
@@ -1231,7 +1321,7 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
 // launch of several PT cycles).
 bool whole_instance_tiles(const pt_ctx *c)
 {
-    if (c->n_generic_tiles != 0 || c->n_block_tiles != 0 || c->n_fast_tiles != n_inst_of(c))
+    if (c->n_words_tiles != 0 || c->n_generic_tiles != 0 || c->n_block_tiles != 0 || c->n_fast_tiles != n_inst_of(c))
         return false;
     for (int k = 0; k < c->n_fast_tiles; ++k) {
         const Tile &t = c->tiles[k];
@@ -1316,7 +1406,7 @@ int enqueue_sweep_once(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles =
             // slice blocks: boundary records of the current state (and E_cl, C cleared),
             // then all sweeps in one launch when every block can be resident at once,
             // else one launch per sweep
-            L.tile0 = c->n_fast_tiles + c->n_generic_tiles;
+            L.tile0 = c->n_fast_tiles + c->n_words_tiles + c->n_generic_tiles;
             L.n_tiles = c->n_block_tiles;
             L.lds_bytes = c->lds_block;
             if (e == hipSuccess && L.n_tiles > 0) {
@@ -1379,6 +1469,10 @@ int enqueue_sweep_once(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles =
             if (rc) return rc;
         } else if (c->block_threads > 64) {
             c->block_threads /= 2;
+            if (c->n_words_tiles > 0) {  // a word tile needs a thread per lane of a site
+                const int rc = build_tiles(c, 1, 0);
+                if (rc) return rc;
+            }
         } else {
             return fail(PT_ELAUNCH, std::string("sweep kernel cannot be launched: ") +
                                         hipGetErrorString(e));
@@ -1404,11 +1498,11 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
     const size_t k = c->cand_next % nc;
     const auto shape = c->cand[k];
     int rc = PT_OK;
-    if (!bp) {
-        rc = build_tiles(c, 0, shape.first);
+    c->block_threads = shape.second;
+    if (!bp || c->n_words_tiles > 0) {
+        rc = build_tiles(c, c->opt.tile_replicas, shape.first);
         if (rc) return rc;
     }
-    c->block_threads = shape.second;
     HIP_TRY(hipEventRecord(c->tune_ev[0], c->stream));
     const int fb = c->fallbacks;
     rc = bp ? enqueue_bp_sweep(c, n_sweeps, fuse_exchange)
@@ -1425,11 +1519,11 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
         for (size_t j = 1; j < nc; ++j)
             if (c->cand_ms[j] < c->cand_ms[best]) best = j;
         c->tuning = false;
-        if (!bp) {
-            rc = build_tiles(c, 0, c->cand[best].first);
+        c->block_threads = c->cand[best].second;
+        if (!bp || c->n_words_tiles > 0) {
+            rc = build_tiles(c, c->opt.tile_replicas, c->cand[best].first);
             if (rc) return rc;
         }
-        c->block_threads = c->cand[best].second;
     }
     return PT_OK;
 }
@@ -1482,7 +1576,9 @@ int enqueue_cycle(pt_ctx *c)
 {
     const int k = c->opt.sweeps_per_exchange;
     int rc;
-    if ((c->plan.encoding == PT_INT8 && c->tiles.size() <= kFuseMaxTiles) || c->oct_fuse) {
+    // word tiles count themselves without a release, whatever their number
+    const bool all_words = c->n_words_tiles == (int)c->tiles.size();
+    if ((c->plan.encoding == PT_INT8 && (c->tiles.size() <= kFuseMaxTiles || all_words)) || c->oct_fuse) {
         rc = enqueue_sweep(c, k, true);
     } else {
         rc = enqueue_sweep(c, k, false);
@@ -1697,14 +1793,10 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
         // whole octets in list order (or from the device work queues), and the exchange step
         // in the octet that completes an instance when every instance is in whole octets
         c->oct_queue = P.n_otile > 0 && (opt->flags & PT_FLAG_WORK_QUEUE);
-        c->oct_fuse = P.n_otile > 0 && P.n_oblock == 0 && !P.bp_generic;
-        if (c->oct_fuse) {
-            c->itiles.assign(P.desc.size(), 0);
-            for (int32_t k = 0; k < P.n_otile; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
-            e = hipMemcpyAsync(c->ws + P.o_itiles, c->itiles.data(), c->itiles.size() * 4,
-                               hipMemcpyHostToDevice, c->stream);
-            if (e != hipSuccess) return cleanup(hip_fail(e, "octet counts upload"));
-        }
+        c->oct_fuse = P.n_oblock == 0 && !P.bp_generic;
+        c->block_threads = opt->block_threads > 0 ? opt->block_threads : 256;
+        rc = build_tiles(c, opt->tile_replicas, opt->tile_bytes);
+        if (rc) return cleanup(rc);
         // octet slice blocks run resident (one launch per call) when every block fits the
         // compute units at once: blocks wait for their neighbours, which must all have started
         if (P.n_oblock > 0 && !(opt->flags & PT_FLAG_BLOCK_LAUNCH_PER_SWEEP)) {
@@ -1726,14 +1818,15 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     }
     const bool tune_int8 = P.encoding == PT_INT8 && opt->tile_replicas == 0 &&
                            opt->tile_bytes == 0 && opt->block_threads == 0;
-    // packed: the workgroup size of the whole-octet launch
-    const bool tune_bp = P.encoding == PT_BITPACK32 && P.n_otile > 0 && opt->block_threads == 0;
+    // packed: the workgroup size of the whole-octet and word-tile launches
+    const bool tune_bp = P.encoding == PT_BITPACK32 && (P.n_otile > 0 || c->n_words_tiles > 0) &&
+                         opt->block_threads == 0;
     if (tune_int8 || tune_bp) {
         if (tune_int8) {
             for (int tb : {8 * 1024, 16 * 1024, 32 * 1024, 64 * 1024, 128 * 1024})
                 for (int th : {256, 512, 1024}) c->cand.emplace_back(tb, th);
         } else {
-            for (int th : {256, 512, 1024}) c->cand.emplace_back(0, th);
+            for (int th : {256, 512, 1024}) c->cand.emplace_back(opt->tile_bytes, th);
         }
         c->cand_ms.assign(c->cand.size(), 0.0);
         c->tuning = true;
@@ -2112,7 +2205,7 @@ int pt_get_info(pt_ctx *c, pt_info *o)
     o->oct_tile_launches = c->plan.n_otile > 0 ? 1 : 0;
     o->oct_resident = c->oct_resident ? 1 : 0;
     o->oct_queue = c->oct_queue ? 1 : 0;
-    o->oct_fused = c->oct_fuse ? 1 : 0;
+    o->oct_fused = c->oct_fuse && c->plan.n_otile > 0 ? 1 : 0;
     o->oct_ring_xcd = oct_ring_xcd(c) ? 1 : 0;
     o->block_ring_xcd = block_ring_xcd(c) ? 1 : 0;
     o->recoveries = c->recoveries;

@@ -136,6 +136,14 @@ hipError_t sweep_kernels_set_lds(int32_t fast_bytes, int32_t generic_bytes, int3
 // holds at once in the resident (persistent) block kernel.
 hipError_t block_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu);
 
+// Word tiles (kTileWords; kTileWordsR: M <= 2, replicas in a word): the WordsMode of a field
+// bound F, LDS bytes and lanes per site of a tile of P replicas.
+int words_mode(int32_t F);
+int32_t words_tile_lds_bytes(const InstDesc &d, int32_t P);
+int32_t words_lanes(const InstDesc &d, int32_t P);
+hipError_t words_kernels_set_lds(int32_t bytes);
+hipError_t launch_sweep_words(const SweepLaunch &L, bool replicas, hipStream_t s);
+
 // Byte offsets of one instance's observables in the buffer gather_obs writes: arrays of R
 // (sumCt: R * kTauLags; acc, att: R - 1) in the types of the state region, then the counters
 // and the device error word.

@@ -9,8 +9,9 @@
 //   sweep_block    sweeps of slice blocks of replicas too large for one workgroup's LDS
 //                  (or whose rows need offsets beyond 16 bits): all sweeps of a call in
 //                  one launch with every block resident, or one launch per sweep
-//   sweep_generic  the same chain for any other shape (slice groups that are not a power
-//                  of two, M = 1, large fields), one byte at a time
+//   sweep_generic  the same chain for the shapes neither these nor the word tiles of
+//                  pt_words.hip hold (more lanes per site than the workgroup has threads,
+//                  or padded words and rows that do not fit LDS), one byte at a time
 //   exchange       one even/odd replica-exchange step per instance (one workgroup each)
 //   tau_corr       imaginary-time spin correlations of every replica, added per rung
 //   advance        t += n
@@ -2072,6 +2073,8 @@ hipError_t launch_sweep(const SweepLaunch &L, int kind, hipStream_t s)
             else
                 hipLaunchKernelGGL((sweep_block_kernel<false, false>), grid, block, L.lds_bytes, s, L);
         }
+    } else if (kind == kTileWords || kind == kTileWordsR) {
+        return launch_sweep_words(L, kind == kTileWordsR, s);
     } else {
         if (fuse)
             hipLaunchKernelGGL(sweep_generic_kernel<true>, grid, block, L.lds_bytes, s, L);

@@ -1,0 +1,708 @@
+// pt_words.hip -- sweeps of tiles of replicas whose shape the power-of-two kernels do not
+// take, for both encodings: any slice count, any couplings (fields up to the library's
+// bound), M = 1 and M = 2, and bit-packed instances the octet kernels do not take.
+//
+// A tile's replicas are held in LDS as words of four spins (one byte each) that one lane
+// updates together:
+//   slices (M >= 4)  word (q, p, i, g): slices 4g .. 4g + 3 of one parity of site i of
+//                    replica q, which one Philox call serves; rows are padded to whole
+//                    words, the padding stays 0 and is never flipped
+//   replicas (M <= 2) word (Q, p, i): replicas 4Q .. 4Q + 3 at one slice of site i, four
+//                    Philox calls (each attempt's draw is word 0 of its own call)
+// The spins are expanded from either encoding when a tile is staged and packed again when it
+// is written back, so the sweep itself is the same for both.
+//
+// Measured on MI355X, us per cycle of 10 sweeps and an exchange, the one-byte-at-a-time kernel
+// or a launch per colour class -> word tiles: 16 lattices of 10^3 spins at M = 1, 32 replicas,
+// 149 -> 33; 8 instances of 201 spins at M = 100, 27 replicas, 262 -> 70; 16 packed instances
+// of 128 spins at M = 64 with couplings up to 3, 48 replicas, 760 -> 95.
+//
+// What bounds it is VALU issue: per word about 37 operations of Philox, 2 to 3 per neighbour,
+// 5 for the table index and 4.5 per attempt for lookup, compare and merge.  The time
+// neighbours of every word come from one v_perm whose selector, fixed per thread, also does
+// the wrap at the ends of a row, so slice counts that are not a multiple of eight cost
+// nothing more.
+//
+// Table index (x (2F + 1) + f + F) 3 + tau, formed for the word's four spins at once:
+//   narrow  F <= 20: in bytes (at most 245)
+//   middle  F <= 63: x (2F + 1) + f + F in bytes (at most 253), the rest per attempt
+//   wide    else:    in two pairs of 16-bit halves (at most 12,281)
+#include "pt_exchange.h"
+#include "pt_internal.h"
+
+#pragma clang fp contract(off)
+
+namespace ptq {
+namespace {
+
+constexpr int kWave = 64;
+constexpr int kWaitVmcnt0 = 0x0F70;                 // s_waitcnt: vector-memory count 0 only
+
+template <int V>
+struct IntC {
+    static constexpr int value = V;
+};
+
+// Replicas per word, and words between the tile's units (replicas, or quads of replicas).
+// The stride is padded so that it is congruent to a row's words modulo 64: the lanes of a
+// wave run over (unit, group) with groups fastest, and the units then start on different
+// banks.
+__host__ __device__ __forceinline__ int words_rpw(const InstDesc &d) { return d.M <= 2 ? 4 : 1; }
+__host__ __device__ __forceinline__ int words_row(const InstDesc &d) { return d.M <= 2 ? 1 : d.G4; }
+__host__ __device__ __forceinline__ int words_units(const InstDesc &d, int P)
+{
+    return d.M <= 2 ? (P + 3) / 4 : P;
+}
+__host__ __device__ __forceinline__ int64_t words_stride(const InstDesc &d)
+{
+    const int64_t row = words_row(d);
+    int64_t w = (int64_t)d.parities * d.N * row;
+    if (row < 64) w += ((row - w) % 64 + 64) % 64;
+    return w;
+}
+
+struct WordsOffsets {
+    int64_t sp, ent, bias, csite, coff, tbl, red, end;
+};
+
+__host__ __device__ __forceinline__ WordsOffsets words_offsets(const InstDesc &d, int P)
+{
+    auto up = [](int64_t x) { return (x + 15) & ~(int64_t)15; };
+    const int64_t units = words_units(d, P), reps = units * words_rpw(d);
+    WordsOffsets o;
+    o.sp = 0;
+    o.ent = up(units * words_stride(d) * 4);
+    o.bias = up(o.ent + (int64_t)d.N * d.D * 4);
+    o.csite = up(o.bias + (int64_t)d.N * 4);
+    o.coff = up(o.csite + (int64_t)d.N * 2);
+    o.tbl = up(o.coff + (int64_t)(d.n_colors + 1) * 4);
+    o.red = up(o.tbl + reps * d.tbl_words * 4);
+    o.end = up(o.red + reps * 2 * 8 + 8);
+    return o;
+}
+
+struct WordsLds {
+    uint8_t *sp;
+    const uint32_t *ent, *bias;
+    const uint16_t *csite;
+    const int32_t *coff;
+    const uint32_t *tbl;
+};
+
+__device__ __forceinline__ uint32_t lds32(const uint8_t *base, uint32_t off)
+{
+    return *reinterpret_cast<const uint32_t *>(base + off);
+}
+
+// ------------------------------------------------------------------ Philox
+
+// The part of a Philox call that a replica's draws of one sweep share: with counter
+// (c0, t, c, n), the second product of round 1 and the first of round 2 do not see c0.
+struct Draws {
+    uint32_t c1;      // word 1 after round 1
+    uint32_t h2, l2;  // the halves of round 2's first product, the high one with its key
+};
+
+__device__ __forceinline__ Draws draws_of(uint32_t t, uint32_t c, uint32_t k0, uint32_t k1)
+{
+    Draws r;
+    const uint64_t pb = (uint64_t)kPhiloxM1 * c;
+    r.c1 = (uint32_t)pb;
+    const uint64_t pa = (uint64_t)kPhiloxM0 * xor3((uint32_t)(pb >> 32), t, k0);
+    r.h2 = (uint32_t)(pa >> 32) ^ (k1 + kPhiloxW1);
+    r.l2 = (uint32_t)pa;
+    return r;
+}
+
+// The part that a site's draws share: round 1's first product and what round 2 makes of it
+// (k0, k1: the call's keys; n: counter word 3).
+struct SiteDraws {
+    uint32_t lo1, h2, l2;
+};
+
+__device__ __forceinline__ SiteDraws site_draws(uint32_t ctr0, uint32_t n, uint32_t k0, uint32_t k1)
+{
+    SiteDraws s;
+    const uint64_t pa = (uint64_t)kPhiloxM0 * ctr0;
+    s.lo1 = (uint32_t)pa;
+    const uint64_t pb = (uint64_t)kPhiloxM1 * xor3((uint32_t)(pa >> 32), n, k1);
+    s.h2 = (uint32_t)(pb >> 32) ^ (k0 + kPhiloxW0);
+    s.l2 = (uint32_t)pb;
+    return s;
+}
+
+// The call's four words: philox10(ctr0, t, c, n, k0, k1).
+__device__ __forceinline__ Words4 draw(const Draws &r, const SiteDraws &s, uint32_t k0, uint32_t k1)
+{
+    uint32_t c0 = s.h2 ^ r.c1, c1 = s.l2, c2 = r.h2 ^ s.lo1, c3 = r.l2;
+    k0 += 2 * kPhiloxW0;
+    k1 += 2 * kPhiloxW1;
+#pragma unroll
+    for (int i = 2; i < 10; ++i) {
+        const uint64_t pa = (uint64_t)kPhiloxM0 * c0;
+        const uint64_t pb = (uint64_t)kPhiloxM1 * c2;
+        const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(pa >> 32), c3, k1);
+        c1 = (uint32_t)pb;
+        c3 = (uint32_t)pa;
+        c0 = n0;
+        c2 = n2;
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
+    }
+    Words4 o;
+    o.w[0] = c0;
+    o.w[1] = c1;
+    o.w[2] = c2;
+    o.w[3] = c3;
+    return o;
+}
+
+// ------------------------------------------------------------------ one word
+
+// Per launch, and per thread (its unit and group are fixed).
+struct Args {
+    uint32_t key0, key1, n;
+    uint32_t plane, row;  // bytes of one parity of a unit, of a row
+    uint32_t sel_x;       // v_perm selector: x -> x (2F + 1) (narrow, middle)
+    uint32_t xstep;       // 2F + 1
+    uint32_t ctr_site;    // Philox counter words per site (2 G4)
+    int D, G4, tbl_words;
+};
+
+struct Lane {
+    uint32_t base;        // byte of the lane's word in row 0, parity 0
+    int32_t prev, next;   // bytes to the words before and after it in its row (cyclic)
+    uint32_t sel0, sel1;  // selectors of the time neighbours of parity 0 and 1
+    uint32_t valid;       // 1 in every byte that holds a spin
+    uint32_t g;           // its group
+    const uint32_t *tb;   // its (first) replica's table
+};
+
+// Weighted neighbour counts of a word's four spins: bytes (a0), or the even bytes' counts in
+// the halves of a0 and the odd bytes' in those of a1 (wide).
+template <int DT, int MODE>
+__device__ __forceinline__ void field(const Args &a, const WordsLds &t, uint32_t at, int i, uint32_t &a0,
+                                      uint32_t &a1)
+{
+    a0 = a1 = 0;
+    auto add = [&](uint32_t e, uint32_t y) {
+        const uint32_t w = __builtin_amdgcn_perm(0u, e, y);
+        if constexpr (MODE == kWordsWide) {
+            a0 += w & 0x00FF00FFu;
+            a1 += (w >> 8) & 0x00FF00FFu;
+        } else {
+            a0 += w;
+        }
+    };
+    if constexpr (DT > 0) {
+        uint32_t e[DT], y[DT];
+#pragma unroll
+        for (int k = 0; k < DT; ++k) e[k] = t.ent[i * DT + k];
+#pragma unroll
+        for (int k = 0; k < DT; ++k) y[k] = lds32(t.sp, at + __umul24(e[k] >> 16, a.row));
+#pragma unroll
+        for (int k = 0; k < DT; ++k) add(e[k], y[k]);
+    } else {
+#pragma unroll 4
+        for (int k = 0; k < a.D; ++k) {
+            const uint32_t e = t.ent[i * a.D + k];
+            add(e, lds32(t.sp, at + __umul24(e >> 16, a.row)));
+        }
+    }
+}
+
+// Table index of spin b of a word from its counts, spins X and time fields T.
+template <int MODE>
+struct Index {
+    uint32_t i0, i1, T;
+    __device__ __forceinline__ Index(const Args &a, uint32_t X, uint32_t a0, uint32_t a1, uint32_t T_,
+                                     uint32_t bias)
+        : i0(0), i1(0), T(T_)
+    {
+        if constexpr (MODE == kWordsWide) {
+            const uint32_t v0 = __umul24(X & 0x00010001u, a.xstep) + (a0 << 1) + bias;
+            const uint32_t v1 = __umul24((X >> 8) & 0x00010001u, a.xstep) + (a1 << 1) + bias;
+            i0 = v0 + (v0 << 1) + (T & 0x00FF00FFu);
+            i1 = v1 + (v1 << 1) + ((T >> 8) & 0x00FF00FFu);
+        } else {
+            i0 = __builtin_amdgcn_perm(0u, a.sel_x, X) + (a0 << 1) + bias;
+            if constexpr (MODE == kWordsNarrow) i0 = i0 + (i0 << 1) + T;
+        }
+    }
+    __device__ __forceinline__ uint32_t at(int b) const
+    {
+        if constexpr (MODE == kWordsWide)
+            return ((b & 1 ? i1 : i0) >> (b & 2 ? 16 : 0)) & 0xFFFFu;
+        else if constexpr (MODE == kWordsMiddle)
+            return ((i0 >> (8 * b)) & 0xFFu) * 3u + ((T >> (8 * b)) & 0xFFu);
+        else
+            return (i0 >> (8 * b)) & 0xFFu;
+    }
+};
+
+// The four attempts of the lane's word at site i, parity PAR.  RM: the word holds replicas;
+// nr of them are in use (uniform), r[k] are their shared draws.
+template <int DT, int PAR, int MODE, bool RM>
+__device__ __forceinline__ void item(const Args &a, const WordsLds &t, const Lane &ln, const Draws *r,
+                                     int nr, bool timed, int i)
+{
+    const uint32_t irow = __umul24((uint32_t)i, a.row);
+    const uint32_t plane = ln.base + (uint32_t)PAR * a.plane;
+    const uint32_t own = plane + irow, oth = ln.base + (uint32_t)(PAR ^ 1) * a.plane + irow;
+    const uint32_t X = lds32(t.sp, own);
+    uint32_t T;
+    if constexpr (RM) {
+        T = timed ? 2u * lds32(t.sp, oth) : 0x01010101u;  // M = 2: both neighbours are the other slice
+    } else {
+        const uint32_t W = lds32(t.sp, oth);
+        const uint32_t Wx = lds32(t.sp, oth + (uint32_t)(PAR == 0 ? ln.prev : ln.next));
+        T = __builtin_amdgcn_perm(W, Wx, PAR == 0 ? ln.sel0 : ln.sel1) + W;
+    }
+    uint32_t a0, a1;
+    field<DT, MODE>(a, t, plane, i, a0, a1);
+    const Index<MODE> idx(a, X, a0, a1, T, t.bias[i]);
+    const SiteDraws s = site_draws(__umul24((uint32_t)i, a.ctr_site) + (uint32_t)(PAR * a.G4) + ln.g, a.n, a.key0, a.key1);
+    uint32_t flip = 0;
+    if constexpr (RM) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b < nr) {
+                const uint32_t thr = ln.tb[b * a.tbl_words + idx.at(b)];
+                flip |= (draw(r[b], s, a.key0, a.key1).w[0] <= thr ? 1u : 0u) << (8 * b);
+            }
+        }
+    } else {
+        const Words4 u = draw(r[0], s, a.key0, a.key1);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) flip |= (u.w[b] <= ln.tb[idx.at(b)] ? 1u : 0u) << (8 * b);
+    }
+    *reinterpret_cast<uint32_t *>(t.sp + own) = X ^ (flip & ln.valid);
+}
+
+// ------------------------------------------------------------------ a tile
+
+struct Tid {
+    int s, rows;  // the thread's first site of a class, and the sites a pass covers
+};
+
+template <int DT, int MODE, bool RM>
+__device__ __forceinline__ void sweeps(const SweepLaunch &L, const InstDesc &d, const Tile &tile,
+                                       const WordsLds &t, const Args &a, const Lane &ln, const Tid &id,
+                                       uint32_t c, uint64_t t0)
+{
+    constexpr int NR = RM ? 4 : 1;
+    const int nr = min(tile.P, NR);
+    const bool timed = d.M >= 2;
+    const int nc = d.n_colors;
+    auto draws = [&](Draws (&r)[NR], uint64_t tt) {
+#pragma unroll
+        for (int k = 0; k < NR; ++k) r[k] = draws_of((uint32_t)tt, c + (uint32_t)k, a.key0, a.key1);
+    };
+    auto cls = [&](auto par, const Draws (&r)[NR], int g) {
+        const int s1 = t.coff[g + 1];
+        for (int si = t.coff[g] + id.s; si < s1; si += id.rows)
+            item<DT, decltype(par)::value, MODE, RM>(a, t, ln, r, nr, timed, t.csite[si]);
+    };
+    Draws ra[NR], rb[NR];
+    if (!timed || nc < 2) {
+        for (int sw = 0; sw < L.n_sweeps; ++sw) {
+            draws(ra, t0 + (uint64_t)sw);
+            for (int g = 0; g < nc; ++g) {
+                cls(IntC<0>{}, ra, g);
+                __syncthreads();
+            }
+            for (int g = 0; g < nc && timed; ++g) {
+                cls(IntC<1>{}, ra, g);
+                __syncthreads();
+            }
+        }
+        return;
+    }
+    // class k of parity 0 with class k - 1 of parity 1 (from the previous sweep when k = 0):
+    // they share no site, and each reads the other parity only at its own sites, so one
+    // barrier closes both and every update reads what it reads in the plain order
+    for (int sw = 0; sw <= L.n_sweeps; ++sw) {
+        const bool tail = sw == L.n_sweeps;
+        if (!tail) draws(ra, t0 + (uint64_t)sw);
+        for (int k = 0; k < (tail ? 1 : nc); ++k) {
+            if (k == 1)
+                for (int j = 0; j < NR; ++j) rb[j] = ra[j];
+            if (!tail) cls(IntC<0>{}, ra, k);
+            if (k > 0 || sw > 0) cls(IntC<1>{}, rb, k > 0 ? k - 1 : nc - 1);
+            __syncthreads();
+        }
+    }
+}
+
+// 2 E_cl and C of the tile's replicas, summed per replica in red[2 q], red[2 q + 1] (zeroed).
+// 2E = sum_i s_i (f_i + h_i) with f + F from the weighted counts as in the sweep; sumJ comes
+// from the entries (their two weight bytes sum to |J|).
+template <int MODE, bool RM>
+__device__ __forceinline__ void energy(const InstDesc &d, const Tile &tile, const WordsLds &t, const Args &a,
+                                       unsigned long long *red)
+{
+    const int row = words_row(d), units = words_units(d, tile.P), stride = (int)words_stride(d);
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int wpu = nw > units ? nw / units : 1, ngroups = nw / wpu;
+    const int grp = wid / wpu, sub = wid - grp * wpu;
+    constexpr int NR = RM ? 4 : 1;
+    for (int q = grp; q < units && grp < ngroups; q += ngroups) {
+        long long e2[NR], cc[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) e2[k] = cc[k] = 0;
+        const int items = d.N * row;
+        for (int it = sub * kWave + lane; it < items; it += wpu * kWave) {
+            const int i = it / row, g = it - i * row;
+            const uint32_t base = 4u * (uint32_t)(q * stride + g), irow = (uint32_t)i * a.row;
+            int sumJ = 0;
+            for (int k = 0; k < a.D; ++k) {
+                const uint32_t e = t.ent[i * a.D + k];
+                sumJ += (int)(e & 0xFFu) + (int)((e >> 8) & 0xFFu);
+            }
+            const int b0 = (int)(t.bias[i] & (MODE == kWordsWide ? 0xFFFFu : 0xFFu));
+            const int hF = b0 + sumJ - 2 * d.F;  // h - F
+            const int left = RM ? 4 : d.Mh - 4 * g, nv = left < 4 ? left : 4;
+            uint32_t X[2] = {0u, 0u};
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if (p >= d.parities) break;
+                const uint32_t plane = base + (uint32_t)p * a.plane;
+                X[p] = lds32(t.sp, plane + irow);
+                uint32_t a0, a1;
+                field<0, MODE>(a, t, plane, i, a0, a1);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    if (b >= nv) break;
+                    const int cnt = MODE == kWordsWide ? (int)(((b & 1 ? a1 : a0) >> (b & 2 ? 16 : 0)) & 0xFFFFu)
+                                                  : (int)((a0 >> (8 * b)) & 0xFFu);
+                    const int s = 2 * (int)((X[p] >> (8 * b)) & 1u) - 1;
+                    e2[RM ? b : 0] += s * (2 * cnt + b0 + hF);
+                }
+            }
+            if (d.M >= 2) {
+                // bonds (2m, 2m + 1) and (2m + 1, 2m + 2): parity 0 at the next slice
+                uint32_t nx;
+                if constexpr (RM) {
+                    nx = X[0];
+                } else {
+                    const int gn = g + 1 == row ? 0 : g + 1;
+                    nx = __builtin_amdgcn_perm(X[0], lds32(t.sp, 4u * (uint32_t)(q * stride + gn) + irow),
+                                               nv == 4 ? 0x00070605u : nv == 3 ? 0x0C000605u
+                                                                   : nv == 2   ? 0x0C0C0005u
+                                                                               : 0x0C0C0C00u);
+                }
+                const uint32_t diff = (X[0] ^ X[1]) + (X[1] ^ nx);
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (b < nv) cc[RM ? b : 0] += 2 - 2 * (int)((diff >> (8 * b)) & 3u);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            long long e = e2[k], c = cc[k];
+#pragma unroll
+            for (int o = kWave / 2; o > 0; o >>= 1) {
+                e += __shfl_xor(e, o, kWave);
+                c += __shfl_xor(c, o, kWave);
+            }
+            if (lane == 0) {
+                atomicAdd(&red[2 * (NR * q + k)], (unsigned long long)e);
+                atomicAdd(&red[2 * (NR * q + k) + 1], (unsigned long long)c);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ staging
+
+__device__ __forceinline__ uint32_t spread4(uint32_t v) { return (v * 0x00204081u) & 0x01010101u; }
+
+// Byte-encoded replicas of the tile into LDS words (IN) or back.
+template <bool IN>
+__device__ __forceinline__ void move_bytes(const DevState &st, const InstDesc &d, const Tile &tile, uint8_t *sp)
+{
+    uint8_t *dev = st.spins + d.spin_base + (int64_t)tile.c0 * d.rep_bytes;
+    const int stride = (int)words_stride(d);
+    if (d.M <= 2) {
+        // a word's four bytes are one position of four replicas
+        const int pos = d.parities * d.N, units = words_units(d, tile.P);
+        for (int it = threadIdx.x; it < pos * units; it += blockDim.x) {
+            const int Q = it / pos, x = it - Q * pos;
+            uint32_t *w = reinterpret_cast<uint32_t *>(sp) + Q * stride + x;
+            if (IN) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (4 * Q + b < tile.P) v |= (uint32_t)dev[(int64_t)(4 * Q + b) * d.rep_bytes + x] << (8 * b);
+                *w = v;
+            } else {
+                const uint32_t v = *w;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (4 * Q + b < tile.P) dev[(int64_t)(4 * Q + b) * d.rep_bytes + x] = (uint8_t)(v >> (8 * b));
+            }
+        }
+        return;
+    }
+    const int words = (d.N * d.M + 3) >> 2;  // of a replica in device memory
+    if ((d.Mh & 3) == 0) {
+        for (int q = 0; q < tile.P; ++q) {
+            uint32_t *l = reinterpret_cast<uint32_t *>(sp) + q * stride;
+            uint32_t *g = reinterpret_cast<uint32_t *>(dev + (int64_t)q * d.rep_bytes);
+            for (int w = threadIdx.x; w < words; w += blockDim.x) {
+                if (IN)
+                    l[w] = g[w];
+                else
+                    g[w] = l[w];
+            }
+        }
+        return;
+    }
+    // rows are not whole words: four consecutive bytes of device memory at a time
+    const int rows = 2 * d.N;
+    for (int q = 0; q < tile.P; ++q) {
+        uint8_t *l = sp + 4 * (int64_t)q * stride;
+        uint32_t *g = reinterpret_cast<uint32_t *>(dev + (int64_t)q * d.rep_bytes);
+        for (int w = threadIdx.x; w < words; w += blockDim.x) {
+            int rw = 4 * w / d.Mh, m = 4 * w - rw * d.Mh;
+            uint32_t v = IN ? g[w] : 0u;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (rw < rows) {
+                    if (IN)
+                        l[rw * 4 * d.G4 + m] = (uint8_t)(v >> (8 * b));
+                    else
+                        v |= (uint32_t)l[rw * 4 * d.G4 + m] << (8 * b);
+                }
+                if (++m == d.Mh) {
+                    m = 0;
+                    ++rw;
+                }
+            }
+            if (!IN) g[w] = v;
+        }
+    }
+}
+
+// Bit-packed replicas (all within one word group) into LDS words, or back: the words of a
+// four-slice group are one 16-byte load for all the tile's replicas.  Other tiles hold
+// other bits of the same words, so the bits that changed are flipped with atomic xors.
+template <bool IN>
+__device__ __forceinline__ void move_bits(const DevState &st, const InstDesc &d, const Tile &tile, uint8_t *sp)
+{
+    const int row = d.G4, pos = d.parities * d.N * row, stride = (int)words_stride(d);
+    const int c = tile.c0 & 31, units = words_units(d, tile.P);
+    uint32_t *dev = reinterpret_cast<uint32_t *>(st.spins + d.spin_base) +
+                    (int64_t)(tile.c0 >> 5) * d.parities * d.N * d.bp_row;
+    uint32_t *l = reinterpret_cast<uint32_t *>(sp);
+    for (int x = threadIdx.x; x < pos; x += blockDim.x) {
+        uint4 v = reinterpret_cast<const uint4 *>(dev)[x];
+        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        if (d.M <= 2) {
+            uint32_t now = 0, mask = 0;
+            for (int Q = 0; Q < units; ++Q) {
+                const int sh = c + 4 * Q, nv = min(4, tile.P - 4 * Q);
+                if (IN) {
+                    l[Q * stride + x] = spread4((w[0] >> sh) & ((1u << nv) - 1u));
+                } else {
+                    const uint32_t y = l[Q * stride + x];
+                    now |= ((y | (y >> 7) | (y >> 14) | (y >> 21)) & 0xFu) << sh;
+                    mask |= ((1u << nv) - 1u) << sh;
+                }
+            }
+            if (!IN) {
+                const uint32_t diff = (w[0] ^ now) & mask;
+                if (diff) atomicXor(dev + 4 * (int64_t)x, diff);
+            }
+            continue;
+        }
+        if (IN) {
+            for (int q = 0; q < tile.P; ++q) {
+                uint32_t y = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) y |= ((w[b] >> (c + q)) & 1u) << (8 * b);
+                l[q * stride + x] = y;
+            }
+        } else {
+            uint32_t diff[4] = {0u, 0u, 0u, 0u};
+            for (int q = 0; q < tile.P; ++q) {
+                const uint32_t y = l[q * stride + x];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) diff[b] |= (((y >> (8 * b)) ^ (w[b] >> (c + q))) & 1u) << (c + q);
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if (diff[b]) atomicXor(dev + 4 * (int64_t)x + b, diff[b]);
+        }
+    }
+}
+
+// RM: replicas in a word (M <= 2).
+template <bool RM>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) sweep_words_kernel(SweepLaunch L)
+{
+    extern __shared__ __align__(16) char lds[];
+    const DevState &st = L.st;
+    const Tile tile = st.tiles[L.tile0 + blockIdx.x];
+    const int n = tile.inst;
+    const InstDesc d = st.inst[n];
+    const WordsOffsets o = words_offsets(d, tile.P);
+    uint8_t *sp = reinterpret_cast<uint8_t *>(lds);
+    uint32_t *ent = reinterpret_cast<uint32_t *>(lds + o.ent), *bias = reinterpret_cast<uint32_t *>(lds + o.bias);
+    uint16_t *csite = reinterpret_cast<uint16_t *>(lds + o.csite);
+    int32_t *coff = reinterpret_cast<int32_t *>(lds + o.coff);
+    uint32_t *tbl = reinterpret_cast<uint32_t *>(lds + o.tbl);
+    unsigned long long *red = reinterpret_cast<unsigned long long *>(lds + o.red);
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const bool packed = d.bp_row != 0;
+
+    for (int e = tid; e < d.N * d.D; e += nt) ent[e] = st.ent[d.ent_base + e];
+    for (int i = tid; i < d.N; i += nt) {
+        bias[i] = st.bias[d.site_base + i];
+        csite[i] = st.csite[d.site_base + i];
+    }
+    for (int g = tid; g <= d.n_colors; g += nt) coff[g] = st.cls_off[d.cls_base + g];
+    for (int k = tid; k < tile.P * d.tbl_words; k += nt) {
+        const int q = k / d.tbl_words, e = k - q * d.tbl_words;
+        tbl[k] = st.tbl[d.tbl_base + (int64_t)st.rung_of[d.rep_base + tile.c0 + q] * d.tbl_words + e];
+    }
+    for (int k = tid; k < 2 * words_units(d, tile.P) * words_rpw(d); k += nt) red[k] = 0;
+    const uint64_t t0 = st.ctr[n].t;
+    if (packed) {
+        move_bits<true>(st, d, tile, sp);
+    } else {
+        if (!RM && (d.Mh & 3) != 0) {
+            const int words = tile.P * (int)words_stride(d);
+            for (int w = tid; w < words; w += nt) reinterpret_cast<uint32_t *>(sp)[w] = 0u;
+            __syncthreads();
+        }
+        move_bytes<true>(st, d, tile, sp);
+    }
+    __syncthreads();
+
+    const WordsLds t = {sp, ent, bias, csite, coff, tbl};
+    Args a;
+    a.key0 = L.key0;
+    a.key1 = L.key1;
+    a.n = (uint32_t)n;
+    const int row = words_row(d);
+    a.row = 4u * (uint32_t)row;
+    a.plane = a.row * (uint32_t)d.N;
+    a.xstep = (uint32_t)(2 * d.F + 1);
+    a.sel_x = a.xstep << 8;
+    a.ctr_site = 2u * (uint32_t)d.G4;
+    a.D = d.D;
+    a.G4 = d.G4;
+    a.tbl_words = d.tbl_words;
+    // lanes run over (unit, group), groups fastest; each keeps its own and strides over the
+    // sites of a class, threads past the last whole row of lanes stay idle
+    const int lanes = words_units(d, tile.P) * row;  // at most nt (the host's choice of P)
+    Tid id;
+    id.rows = nt / lanes;
+    id.s = tid / lanes;
+    const int r = tid - id.s * lanes;
+    if (id.s >= id.rows) id.s = 1 << 30;
+    const int unit = r / row, g = r - unit * row;
+    Lane ln;
+    ln.base = 4u * (uint32_t)(unit * (int)words_stride(d) + g);
+    ln.g = (uint32_t)g;
+    ln.prev = 4 * ((g == 0 ? row - 1 : g - 1) - g);
+    ln.next = 4 * ((g + 1 == row ? 0 : g + 1) - g);
+    ln.sel0 = 0x06050400u | (uint32_t)(g == 0 ? (d.Mh - 1) & 3 : 3);
+    const int left = RM ? tile.P - 4 * unit : d.Mh - 4 * g, nv = left < 4 ? left : 4;
+    // parity 1 in a row's last word: the wrapped spin follows the row's last one
+    ln.sel1 = nv == 4 ? 0x00070605u : nv == 3 ? 0x0C000605u : nv == 2 ? 0x0C0C0005u : 0x0C0C0C00u;
+    ln.valid = nv == 4 ? 0x01010101u : 0x01010101u >> (8 * (4 - nv));
+    ln.tb = tbl + (RM ? 4 * unit : unit) * d.tbl_words;
+    const uint32_t c = (uint32_t)(tile.c0 + (RM ? 4 * unit : unit));
+
+    auto run = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        auto with = [&](auto dt) {
+            constexpr int DT = MODE == kWordsWide ? 0 : decltype(dt)::value;
+            sweeps<DT, MODE, RM>(L, d, tile, t, a, ln, id, c, t0);
+        };
+        switch (d.D) {
+        case 3: with(IntC<3>{}); break;
+        case 4: with(IntC<4>{}); break;
+        case 5: with(IntC<5>{}); break;
+        case 6: with(IntC<6>{}); break;
+        case 7: with(IntC<7>{}); break;
+        case 8: with(IntC<8>{}); break;
+        default: with(IntC<0>{}); break;
+        }
+        energy<MODE, RM>(d, tile, t, a, red);
+    };
+    switch (d.words) {
+    case kWordsNarrow: run(IntC<kWordsNarrow>{}); break;
+    case kWordsMiddle: run(IntC<kWordsMiddle>{}); break;
+    default: run(IntC<kWordsWide>{}); break;
+    }
+    if (packed)
+        move_bits<false>(st, d, tile, sp);
+    else
+        move_bytes<false>(st, d, tile, sp);
+    __syncthreads();
+    for (int q = tid; q < tile.P; q += nt) {
+        const int64_t e = (int64_t)red[2 * q] / 2, cc = (int64_t)red[2 * q + 1];
+        int64_t *Eo = st.E + d.rep_base + tile.c0 + q, *Co = st.C + d.rep_base + tile.c0 + q;
+        if (L.fuse_exchange) {
+            __hip_atomic_store(Eo, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(Co, cc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            *Eo = e;
+            *Co = cc;
+        }
+    }
+    if (L.fuse_exchange) {
+        // The tile that completes its instance runs the exchange step.  The step reads no
+        // other tile's stores but E_cl and C, which are written and read coherently, so a
+        // tile waits for those and counts itself; nothing waits on another workgroup.
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        uint32_t *flag = reinterpret_cast<uint32_t *>(red + 2 * words_units(d, tile.P) * words_rpw(d));
+        if (tid == 0) {
+            const uint32_t before = __hip_atomic_fetch_add(&st.icount[n], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t done = before + 1u == (uint32_t)st.itiles[n] ? 1u : 0u;
+            if (done) __hip_atomic_store(&st.icount[n], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *flag = done;
+        }
+        __syncthreads();
+        if (*flag) exchange_instance<true>(st, n, L.swap_key0, L.swap_key1, L.t_add);
+    }
+}
+
+}  // namespace
+
+int words_mode(int32_t F) { return F <= 20 ? kWordsNarrow : F <= 63 ? kWordsMiddle : kWordsWide; }
+
+int32_t words_tile_lds_bytes(const InstDesc &d, int32_t P)
+{
+    const int64_t x = words_offsets(d, P).end;
+    return (int32_t)(x > 0x7fffffff ? 0x7fffffff : x);
+}
+
+int32_t words_lanes(const InstDesc &d, int32_t P) { return words_units(d, P) * words_row(d); }
+
+hipError_t words_kernels_set_lds(int32_t bytes)
+{
+    if (bytes <= 0) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_words_kernel<false>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_words_kernel<true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+hipError_t launch_sweep_words(const SweepLaunch &L, bool replicas, hipStream_t s)
+{
+    if (L.n_tiles <= 0) return hipSuccess;
+    if (replicas)
+        hipLaunchKernelGGL(sweep_words_kernel<true>, dim3(L.n_tiles), dim3(L.block_threads), L.lds_bytes, s, L);
+    else
+        hipLaunchKernelGGL(sweep_words_kernel<false>, dim3(L.n_tiles), dim3(L.block_threads), L.lds_bytes, s, L);
+    return hipGetLastError();
+}
+
+}  // namespace ptq
