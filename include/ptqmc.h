@@ -76,11 +76,13 @@ extern "C" {
 #define PT_INT8 0       /* one byte per spin                                                */
 #define PT_BITPACK32 1  /* 32 replica slots per uint32 word: bit (c mod 32) of word group
                            c/32 holds slot c's spin at (k, i); device memory 8x smaller.
-                           Instances with +-1 couplings, |h| <= 1, one degree D <= 8 and
+                           Instances with +-1 couplings, |h| <= 1, degrees up to 8 and
                            M a power-of-two multiple of 8 are swept by octets (8 slots, one
                            byte of each word) staged in LDS with bit-sliced local fields;
-                           others one colour class per launch in device memory.  The chain
-                           is the same as under PT_INT8                                  */
+                           others, and batches of fewer octets than compute units where the
+                           tuner finds it faster, replica by replica with their spins spread
+                           to bytes in LDS; what fits neither one colour class per launch in
+                           device memory.  The chain is the same as under PT_INT8        */
 
 /* Imaginary-time correlation lags: with PT_FLAG_TAU_CORR every exchange step adds, for
  * each rung r and l < PT_TAU_LAGS, Ct_l = sum_k sum_i s_i^k s_i^{(k + lag_l) mod M} of

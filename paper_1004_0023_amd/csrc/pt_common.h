@@ -139,7 +139,7 @@ struct InstDesc {
     // (4 * G4), and the instance's first word group in the batch
     int32_t bp_W, bp_row, bp_wg_base;
     int32_t ent_mode;  // EntMode of the fast-path neighbour entries
-    // bit-packed encoding, octet kernels (every |J| = 1, |h| <= 1, one degree D, fast
+    // bit-packed encoding, octet kernels (every |J| = 1, |h| <= 1, degrees up to 8, fast
     // shape): 1 if they run this instance; its first 16-bit octet neighbour entry and its
     // first octet table word (kOctTableWords per rung)
     int32_t oct, oent_base, otbl_base, opad;
@@ -149,9 +149,9 @@ struct InstDesc {
 };
 
 // Octet tables: per rung, the acceptance threshold indexed n + 16 sigma + 64 hz, where n is
-// the number of a site's inputs (its D couplings and, when h != 0, its field) that agree with
-// its spin, sigma the number of agreeing time neighbours and hz = [h != 0]; then
-// a = s f = 2 n - D - hz.
+// the number of a site's inputs (its row of D entries, padded, and when h != 0 its field) that
+// agree with its spin, sigma the number of agreeing time neighbours and hz the table half
+// with the parity of the site's unpadded inputs; then a = s f = 2 n - D - hz.
 constexpr int kOctTableWords = 128;
 
 // How the byte-SWAR kernels form a site's local field from its neighbour entries.
@@ -235,7 +235,7 @@ struct DevState {
     const int32_t *bp_wg;
     int64_t *bp_part;
     // bit-packed encoding, octet kernels: 16-bit neighbour entries (j | [J < 0] << 15, D per
-    // site), per-site field codes (bit 0: h < 0, bit 1: h != 0), per-rung tables, the work
+    // site), per-site field codes (bit 0: h < 0, bit 1: h != 0, bit 2: table half), per-rung tables, the work
     // list of the octet launches (kOctRec ints per item), and for resident slice blocks
     // their boundary records (an R0 region, then an R1 region) and progress counts (two per
     // work item: parity 0, parity 1)

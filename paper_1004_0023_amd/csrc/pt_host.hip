@@ -86,6 +86,7 @@ struct Plan {
     int32_t oblock_res_lds = 0;                // slice blocks, resident layout
     int64_t orec_words = 0;                    // words of each boundary-record region
     bool bp_generic = false;                   // some packed instance runs the per-class kernel
+    bool words_alt = false;                    // every whole octet could run as word tiles
     int64_t halo_words = 0; // one buffer of slice-block boundary records, at most
     uint64_t flips_per_sweep = 0;
     // byte offsets in the workspace
@@ -157,7 +158,7 @@ void build_table(uint32_t *out, int F, int M, double b, double K)
 }
 
 // Octet table of one rung (kOctTableWords words): entry n + 16 sigma + 64 hz holds thr(dS) for
-// a = s f = 2 n - D - hz agreeing-minus-disagreeing inputs and sigma agreeing time
+// a = s f = 2 n - D - hz agreeing-minus-disagreeing inputs (hz: the table's half) and sigma agreeing time
 // neighbours, i.e. dE = -2 a and dC = -4 (sigma - 1): the entry build_table holds for x = 1,
 // f = a, tau = sigma, from the same operations.  Unused entries stay 0.
 void build_oct_table(uint32_t *out, int D, double b, double K)
@@ -178,6 +179,9 @@ bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 // LDS of one gfx950 workgroup; instances whose whole replicas exceed it run as slice blocks
 constexpr int32_t kLdsPerWorkgroup = 163840;
+
+// Compute units of a gfx950 device.
+constexpr int64_t kMostCus = 256;
 
 // Bit-packed encoding: position blocks per word group (at most this many; each block
 // passes over 64 positions at a time).
@@ -203,6 +207,9 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
     P = Plan();
     P.encoding = encoding;
     const bool bp = encoding == PT_BITPACK32;
+    // octets of the batch, whichever kernel runs them
+    int64_t octets = 0;
+    for (int n = 0; bp && n < n_inst; ++n) octets += (inst[n].R + 7) / 8;
     int64_t rep = 0, pair = 0, adjb = 0, offb = 0, siteb = 0, entb = 0, clsb = 0, tblb = 0,
             spinb = 0, wgb = 0;
     for (int n = 0; n < n_inst; ++n) {
@@ -270,19 +277,23 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         std::vector<int32_t> cfill(in.n_colors, 0);
         std::vector<uint16_t> sites(in.N);
         for (int i = 0; i < in.N; ++i) sites[cls[in.color[i]] + cfill[in.color[i]]++] = (uint16_t)i;
-        // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and one degree
-        // D <= 8 on the fast shapes (M a power-of-two multiple of 8)
+        // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and degrees
+        // up to D <= 8 on the fast shapes (M a power-of-two multiple of 8).  Instances of
+        // several degrees that do not fit them even as blocks of one group run elsewhere.
         if (bp && d.fast && in.n_edges > 0 && in.N <= 32767) {
-            bool ok = D <= 8;
+            bool ok = D <= 8, regular = true;
             for (int e = 0; ok && e < in.n_edges; ++e) ok = std::abs((int)in.edge_J[e]) == 1;
-            for (int i = 0; ok && i < in.N; ++i)
-                ok = std::abs((int)in.h[i]) <= 1 && deg[i + 1] - deg[i] == D;
-            d.oct = ok ? 1 : 0;
+            for (int i = 0; ok && i < in.N; ++i) {
+                ok = std::abs((int)in.h[i]) <= 1;
+                regular = regular && deg[i + 1] - deg[i] == D;
+            }
+            d.oct = ok && (regular || oct_lds_bytes(d, 1, kOctResident) <= kLdsPerWorkgroup) ? 1 : 0;
         }
         // word tiles: byte instances off the fast shapes and bit-packed ones the octet kernels
-        // do not take, where padded neighbour rows and one replica fit a workgroup's LDS (and,
-        // bit-packed, a row's lanes fit the smallest workgroup)
-        if ((bp ? !d.oct && d.G4 <= 64 : !d.fast) &&
+        // do not take (and, in batches with fewer octets than compute units, those they do:
+        // the tuner decides), where padded neighbour rows and one replica fit a workgroup's
+        // LDS (and, bit-packed, a row's lanes fit the smallest workgroup)
+        if ((bp ? (!d.oct || octets < kMostCus) && d.G4 <= 64 : !d.fast) &&
             (int64_t)in.N * d.D * 4 <= kLdsPerWorkgroup) {
             d.words = words_mode(F);
             if (words_tile_lds_bytes(d, 1) > kLdsPerWorkgroup) d.words = 0;
@@ -346,16 +357,27 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
             // entries and field codes padded to 16 bytes per instance (the kernels copy them
             // in 16-byte pieces)
             d.oent_base = (int32_t)P.oent.size();
-            for (int i = 0; i < in.N; ++i)
+            // rows padded to D with the site itself, J > 0 (agrees with it) or J < 0 (does
+            // not): with I inputs (couplings and a nonzero field) and T = D, or D + 1 where
+            // that has I's parity, (T - I) / 2 agreeing ones make a = 2 n - T
+            for (int i = 0; i < in.N; ++i) {
                 for (int e = deg[i]; e < deg[i + 1]; ++e) {
                     const int j = entries[e] & 0xFFFF;
                     const int J = entries[e] >> 16;
                     P.oent.push_back((uint16_t)(j | (J < 0 ? 0x8000 : 0)));
                 }
+                const int di = deg[i + 1] - deg[i], inputs = di + (in.h[i] != 0 ? 1 : 0);
+                const int agree = (D + ((D - inputs) & 1) - inputs) / 2;
+                for (int k = 0; k < D - di; ++k) P.oent.push_back((uint16_t)(i | (k < agree ? 0 : 0x8000)));
+            }
             P.oent.resize(align_up(P.oent.size(), 8), 0);
+            // field codes: h < 0, h != 0, and whether T is D + 1 (the table's second half)
             d.opad = (int32_t)P.ohinfo.size();
-            for (int i = 0; i < in.N; ++i)
-                P.ohinfo.push_back((uint8_t)((in.h[i] < 0 ? 1 : 0) | (in.h[i] != 0 ? 2 : 0)));
+            for (int i = 0; i < in.N; ++i) {
+                const int inputs = deg[i + 1] - deg[i] + (in.h[i] != 0 ? 1 : 0);
+                P.ohinfo.push_back((uint8_t)((in.h[i] < 0 ? 1 : 0) | (in.h[i] != 0 ? 2 : 0) |
+                                             (((D - inputs) & 1) ? 4 : 0)));
+            }
             P.ohinfo.resize(align_up(P.ohinfo.size(), 16), 0);
             d.otbl_base = (int32_t)P.otbl.size();
             P.otbl.resize(P.otbl.size() + (size_t)in.R * kOctTableWords);
@@ -566,6 +588,8 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         for (const auto &t : blocks) P.otiles.insert(P.otiles.end(), t.begin(), t.end());
         P.n_otile = (int32_t)tiles.size();
         P.n_oblock = (int32_t)blocks.size();
+        P.words_alt = P.n_otile > 0 && P.n_oblock == 0 && !P.bp_generic && !(flags & PT_FLAG_WORK_QUEUE);
+        for (const auto &d : P.desc) P.words_alt = P.words_alt && d.words;
         // slice blocks: one pass over a colour class of the largest block, with two lanes per
         // (site, group) when a class has at most 512 of them
         int most = 1;
@@ -734,11 +758,14 @@ struct pt_ctx {
     // whole octets from the device work queue; the exchange fused into the octet that
     // completes an instance (every instance of the batch in whole octets)
     bool oct_queue = false, oct_fuse = false;
+    // whole octets run as word tiles instead (the tuner's choice, Plan::words_alt)
+    bool oct_as_words = false;
     int block_threads = 256;
     int tile_bytes = 0;        // target spin bytes per tile in use
     // self-tuning: candidate (tile bytes, threads) shapes timed on the first sweep launches
     bool tuning = false;
     std::vector<std::pair<int, int>> cand;
+    std::vector<char> cand_words;  // oct_as_words of each candidate
     std::vector<double> cand_ms;
     size_t cand_next = 0;
     hipEvent_t tune_ev[2] = {nullptr, nullptr};
@@ -797,11 +824,12 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     const bool force_blocks = (c->opt.flags & PT_FLAG_SLICE_BLOCKS) != 0;
     std::vector<Tile> fast, words, generic, block;
     int lds_f = 0, lds_w = 0, lds_g = 0, lds_b = 0, maxP = 1;
+    auto as_words = [&](const InstDesc &d) { return d.words && (!d.oct || c->oct_as_words); };
     int64_t words_reps = 0;
-    for (const auto &d : P.desc) words_reps += d.words ? d.R : 0;
+    for (const auto &d : P.desc) words_reps += as_words(d) ? d.R : 0;
     for (int n = 0; n < (int)P.desc.size(); ++n) {
         const InstDesc &d = P.desc[n];
-        if (d.words && words_lanes(d, 1) <= c->block_threads) {
+        if (as_words(d) && words_lanes(d, 1) <= c->block_threads) {
             // Replicas per word tile: the target bytes, but as few as leave every compute
             // unit a tile (a tile's sweep is a chain of class steps, so a unit without one
             // idles for the whole call: 512 replicas of 10^3 spins at M = 1 take 33 us a cycle
@@ -831,7 +859,7 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
             }
         }
         if (P.encoding == PT_BITPACK32) {
-            if (!d.words) continue;  // octets and the per-class kernel
+            if (!as_words(d)) continue;  // octets and the per-class kernel
             return fail(PT_EINVAL, "instance " + std::to_string(n) +
                                        ": a word tile needs more LDS than the device has");
         }
@@ -962,7 +990,7 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     // tiles per instance: a PT cycle's exchange runs in the tile that completes the instance
     c->itiles.assign(P.desc.size(), 0);
     for (const Tile &t : c->tiles) c->itiles[t.inst] += 1;
-    for (int32_t k = 0; k < P.n_otile; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
+    for (int32_t k = 0; k < P.n_otile && !c->oct_as_words; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
     HIP_TRY(hipMemcpyAsync(c->ws + P.o_itiles, c->itiles.data(), c->itiles.size() * 4,
                            hipMemcpyHostToDevice, c->stream));
     HIP_TRY(sweep_kernels_set_lds(c->lds_fast, c->lds_generic, c->lds_block));
@@ -1221,7 +1249,7 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
     O.key0 = c->key_flip0;
     O.key1 = c->key_flip1;
     O.n_sweeps = n_sweeps;
-    if (P.n_otile > 0) {
+    if (P.n_otile > 0 && !c->oct_as_words) {
         O.tile0 = 0;
         O.n_tiles = P.n_otile;
         O.threads = c->block_threads;
@@ -1499,7 +1527,8 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
     const auto shape = c->cand[k];
     int rc = PT_OK;
     c->block_threads = shape.second;
-    if (!bp || c->n_words_tiles > 0) {
+    c->oct_as_words = c->cand_words[k] != 0;
+    if (!bp || c->n_words_tiles > 0 || c->plan.words_alt) {
         rc = build_tiles(c, c->opt.tile_replicas, shape.first);
         if (rc) return rc;
     }
@@ -1520,7 +1549,8 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
             if (c->cand_ms[j] < c->cand_ms[best]) best = j;
         c->tuning = false;
         c->block_threads = c->cand[best].second;
-        if (!bp || c->n_words_tiles > 0) {
+        c->oct_as_words = c->cand_words[best] != 0;
+        if (!bp || c->n_words_tiles > 0 || c->plan.words_alt) {
             rc = build_tiles(c, c->opt.tile_replicas, c->cand[best].first);
             if (rc) return rc;
         }
@@ -1828,6 +1858,16 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
         } else {
             for (int th : {256, 512, 1024}) c->cand.emplace_back(opt->tile_bytes, th);
         }
+        c->cand_words.assign(c->cand.size(), 0);
+        // Few octets leave most compute units idle, and a word tile can be as small as one
+        // replica: try both.  40 octets of 336 x 64 spins take 255 us a cycle as octets and
+        // 109 us as 320 word tiles; with an octet for every unit the octets' shared adder
+        // tree wins (7.3e9 attempts/s a unit against about 3e9).
+        if (tune_bp && P.words_alt)
+            for (int th : {512, 1024}) {
+                c->cand.emplace_back(opt->tile_bytes, th);
+                c->cand_words.push_back(1);
+            }
         c->cand_ms.assign(c->cand.size(), 0.0);
         c->tuning = true;
         for (auto &ev : c->tune_ev) {
@@ -2200,12 +2240,12 @@ int pt_get_info(pt_ctx *c, pt_info *o)
     o->block_tiles = c->n_block_tiles;
     o->block_resident = c->block_persistent;
     o->class_launches = 0;
-    o->oct_tiles = c->plan.n_otile;
+    o->oct_tiles = c->oct_as_words ? 0 : c->plan.n_otile;
     o->oct_blocks = c->plan.n_oblock;
-    o->oct_tile_launches = c->plan.n_otile > 0 ? 1 : 0;
+    o->oct_tile_launches = o->oct_tiles > 0 ? 1 : 0;
     o->oct_resident = c->oct_resident ? 1 : 0;
     o->oct_queue = c->oct_queue ? 1 : 0;
-    o->oct_fused = c->oct_fuse && c->plan.n_otile > 0 ? 1 : 0;
+    o->oct_fused = c->oct_fuse && o->oct_tiles > 0 ? 1 : 0;
     o->oct_ring_xcd = oct_ring_xcd(c) ? 1 : 0;
     o->block_ring_xcd = block_ring_xcd(c) ? 1 : 0;
     o->recoveries = c->recoveries;

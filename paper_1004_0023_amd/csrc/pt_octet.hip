@@ -9,10 +9,12 @@
 // and thresholds.
 //
 // The local field is bit-sliced.  For instances whose couplings are all +-1 and fields
-// in {-1, 0, 1}, with every site of one degree D <= 8, a site's Metropolis move depends on
-// n, the number of its inputs (D couplings and, when h != 0, the field) that agree with its
-// spin (a = s f = 2 n - D - [h != 0]), and on sigma, the number of agreeing time
-// neighbours.  For one LDS word each input gives a word of agreement bits (one three-input
+// in {-1, 0, 1}, with degrees up to D <= 8, a site's Metropolis move depends on
+// n, the number of its inputs (its couplings and, when h != 0, its field) that agree with its
+// spin (a = s f = 2 n - inputs), and on sigma, the number of agreeing time
+// neighbours.  Rows are padded to D entries that name the site itself, J > 0 (always agrees)
+// or J < 0 (never does), so many of each that a = 2 n - D or, from the second half of the
+// table, 2 n - D - 1, whichever has the parity of the site's inputs.  For one LDS word each input gives a word of agreement bits (one three-input
 // operation), a carry-save adder tree turns D + 1 of them into the four bit planes of n
 // for all 32 (slot, slice) pairs at once, and two operations give sigma's planes.  Per slot
 // the planes' bits are gathered into a word of four table byte offsets, one per slice;
@@ -170,7 +172,7 @@ __device__ __forceinline__ void slot_offsets(uint32_t n0, uint32_t n1, uint32_t 
 struct OctSite {
     uint32_t hneg;   // ~0 when h < 0
     uint32_t hzm;    // ~0 when h != 0
-    uint32_t hzbase; // LDS byte address of the slot-0 table half for [h != 0] (low byte 0)
+    uint32_t hzbase; // LDS byte address of the site's half of the slot-0 table (low byte 0)
 };
 
 // New octet word of one site at four same-parity slices: X its word, Tlo / Thi the words of
@@ -331,8 +333,15 @@ __device__ __forceinline__ OctSite oct_site(const OctLds &o, int i)
     OctSite s;
     s.hneg = (hb & 1u) ? 0xFFFFFFFFu : 0u;
     s.hzm = (hb & 2u) ? 0xFFFFFFFFu : 0u;
-    s.hzbase = o.tbl + ((hb & 2u) ? 256u : 0u);
+    s.hzbase = o.tbl + ((hb & 4u) ? 256u : 0u);
     return s;
+}
+
+// Agreeing minus disagreeing padding entries of site i's row: [table half 1] - [h != 0].
+__device__ __forceinline__ int oct_pad(const OctLds &o, int i)
+{
+    const uint32_t hb = ld8(o.hinfo + (uint32_t)i);
+    return (int)((hb >> 2) & 1u) - (int)((hb >> 1) & 1u);
 }
 
 // Neighbour e of site i: its site index and sign mask (~0 when J < 0).
@@ -346,12 +355,13 @@ __device__ __forceinline__ void oct_entry(const OctLds &o, int idx, uint32_t &j,
 
 // Per-slot sums of 2 E_cl and C over one (site, four-slice group) position: X0, X1 the
 // site's words of parities 0 and 1, X0n its parity-0 word of the next group, Y0 / Y1 its
-// neighbours' words, h its field.
+// neighbours' words, h its field, pad the agreeing minus the disagreeing padding entries of
+// its row.
 template <int DT>
 __device__ __forceinline__ void oct_energy_item(uint32_t X0, uint32_t X1, uint32_t X0n,
                                                 const uint32_t (&Y0)[DT], const uint32_t (&Y1)[DT],
-                                                const uint32_t (&nm)[DT], int h, int (&e2)[8],
-                                                int (&cc)[8])
+                                                const uint32_t (&nm)[DT], int h, int pad,
+                                                int (&e2)[8], int (&cc)[8])
 {
     uint32_t A0[DT], A1[DT];
 #pragma unroll
@@ -368,7 +378,7 @@ __device__ __forceinline__ void oct_energy_item(uint32_t X0, uint32_t X1, uint32
 #pragma unroll
         for (int e = 0; e < DT; ++e) agree += __popc(A0[e] & m) + __popc(A1[e] & m);
         const int up = __popc(X0 & m) + __popc(X1 & m);
-        e2[r] += 2 * agree - 8 * DT + 2 * h * (2 * up - 8);
+        e2[r] += 2 * agree - 8 * (DT + pad) + 2 * h * (2 * up - 8);
         cc[r] += 8 - 2 * (__popc(d1 & m) + __popc(d2 & m));
     }
 }
@@ -574,7 +584,7 @@ __device__ __forceinline__ void oct_tile_energy(const OctLaunch &L, const InstDe
             Y1[e] = ld32(plane + a);
         }
         const int h = L.st.hfield[d.site_base + i];
-        oct_energy_item<DT>(X0, X1, X0n, Y0, Y1, nm, h, e2, cc);
+        oct_energy_item<DT>(X0, X1, X0n, Y0, Y1, nm, h, oct_pad(o, i), e2, cc);
     }
     oct_reduce(lds, o, e2, cc);
 }
@@ -776,7 +786,7 @@ __device__ __forceinline__ void oct_block_energy(const OctLaunch &L, const InstD
             Y1[e] = ld32(p1.own + j * p1.own_stride + gl4);
         }
         const int h = L.st.hfield[d.site_base + i];
-        oct_energy_item<DT>(X0, X1, X0n, Y0, Y1, nm, h, e2, cc);
+        oct_energy_item<DT>(X0, X1, X0n, Y0, Y1, nm, h, oct_pad(o, i), e2, cc);
     }
     oct_reduce(lds, o, e2, cc);
 }
