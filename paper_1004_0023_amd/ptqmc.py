@@ -394,7 +394,7 @@ class LadderNet:
         x = torch.as_tensor(x, dtype=torch.float32).cuda().contiguous()
         q = torch.as_tensor(q, dtype=torch.float32).cuda().contiguous()
         B = x.shape[0]
-        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        loss = torch.empty(1, dtype=torch.float32, device="cuda")
         rc = lib().pt_mlp_loss_grad(self.params.data_ptr(), x.data_ptr(), q.data_ptr(), B,
                                     int(kind), self.grads.data_ptr(), loss.data_ptr(),
                                     self._workspace(B).data_ptr(),
