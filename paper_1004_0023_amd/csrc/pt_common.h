@@ -60,6 +60,71 @@ __host__ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, ui
     return o;
 }
 
+// The same call in parts, for kernels that make many with common counter words.  With counter
+// (c0, t, c, n) the second product of round 1 and the first of round 2 do not see c0, and the
+// others of these rounds see nothing but c0 and n: a call that has both parts ready takes two
+// operations for its first two rounds instead of eight.
+struct Draws {       // of (t, c): a replica's draws of one sweep
+    uint32_t c1;     // word 1 after round 1
+    uint32_t h2, l2; // the halves of round 2's first product, the high one with its key
+};
+struct SiteDraws {   // of (c0, n): a site's draws, whichever replica's
+    uint32_t h2, l2; // the halves of round 2's second product, the high one with its key
+    uint32_t lo1;    // word 3 after round 1
+};
+
+__device__ __forceinline__ Draws draws_of(uint32_t t, uint32_t c, uint32_t k0, uint32_t k1)
+{
+    Draws r;
+    const uint64_t pb = (uint64_t)kPhiloxM1 * c;
+    r.c1 = (uint32_t)pb;
+    const uint64_t pa = (uint64_t)kPhiloxM0 * xor3((uint32_t)(pb >> 32), t, k0);
+    r.h2 = (uint32_t)(pa >> 32) ^ (k1 + kPhiloxW1);
+    r.l2 = (uint32_t)pa;
+    return r;
+}
+
+__device__ __forceinline__ SiteDraws site_draws(uint32_t c0, uint32_t n, uint32_t k0, uint32_t k1)
+{
+    SiteDraws s;
+    const uint64_t pa = (uint64_t)kPhiloxM0 * c0;
+    s.lo1 = (uint32_t)pa;
+    const uint64_t pb = (uint64_t)kPhiloxM1 * xor3((uint32_t)(pa >> 32), n, k1);
+    s.h2 = (uint32_t)(pb >> 32) ^ (k0 + kPhiloxW0);
+    s.l2 = (uint32_t)pb;
+    return s;
+}
+
+// philox10(c0, t, c, n, k0, k1).  KEYS: each round key is formed in its round; left to itself
+// the compiler keeps all of them live in scalar registers across the sweep loops.
+template <bool KEYS>
+__device__ __forceinline__ Words4 philox_draw(const Draws &r, const SiteDraws &s, uint32_t k0, uint32_t k1)
+{
+    uint32_t c0 = s.h2 ^ r.c1, c1 = s.l2, c2 = r.h2 ^ s.lo1, c3 = r.l2;
+    k0 += kPhiloxW0;
+    k1 += kPhiloxW1;
+#pragma unroll
+    for (int i = 2; i < 10; ++i) {
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
+        if constexpr (KEYS) __asm__ volatile("" : "+s"(k0), "+s"(k1));
+        const uint64_t pa = (uint64_t)kPhiloxM0 * c0;
+        const uint64_t pb = (uint64_t)kPhiloxM1 * c2;
+        const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(pa >> 32), c3, k1);
+        c1 = (uint32_t)pb;
+        c3 = (uint32_t)pa;
+        c0 = n0;
+        c2 = n2;
+    }
+    Words4 o;
+    o.w[0] = c0;
+    o.w[1] = c1;
+    o.w[2] = c2;
+    o.w[3] = c3;
+    return o;
+}
+
 // ------------------------------------------------------------------ exp and thresholds
 // exp(x), x <= 0, from IEEE multiply/add/floor/ldexp only (every operation separately
 // rounded; contraction is off for this file), so host and device agree bitwise:

@@ -52,39 +52,15 @@ typedef __attribute__((address_space(3))) uint16_t LdsU16;
 typedef __attribute__((address_space(3))) uint8_t LdsU8;
 __device__ __forceinline__ uint32_t ld32(uint32_t a) { return *(const LdsU32 *)(uintptr_t)a; }
 __device__ __forceinline__ void st32(uint32_t a, uint32_t v) { *(LdsU32 *)(uintptr_t)a = v; }
+typedef __attribute__((address_space(3))) uint64_t LdsU64;
+__device__ __forceinline__ uint64_t ld64(uint32_t a) { return *(const LdsU64 *)(uintptr_t)a; }
+__device__ __forceinline__ void st64(uint32_t a, uint64_t v) { *(LdsU64 *)(uintptr_t)a = v; }
 __device__ __forceinline__ uint32_t ld16(uint32_t a) { return *(const LdsU16 *)(uintptr_t)a; }
 __device__ __forceinline__ uint32_t ld8(uint32_t a) { return *(const LdsU8 *)(uintptr_t)a; }
 
 // s_waitcnt immediate with the vector-memory count 0 and the export and LDS counts at
 // their maxima (no wait on them): vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8.
 constexpr int kOctWaitVmcnt0 = 0x0F70;
-
-// Philox4x32-10 (the sampler's generator) with each round key formed in its round: left to
-// itself the compiler keeps all twenty live in scalar registers across the sweep loops.
-__device__ __forceinline__ Words4 philox10_rk(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1)
-{
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        __asm__ volatile("" : "+s"(k0), "+s"(k1));
-        const uint64_t pa = (uint64_t)kPhiloxM0 * c0;
-        const uint64_t pb = (uint64_t)kPhiloxM1 * c2;
-        const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(pa >> 32), c3, k1);
-        c1 = (uint32_t)pb;
-        c3 = (uint32_t)pa;
-        c0 = n0;
-        c2 = n2;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    Words4 o;
-    o.w[0] = c0;
-    o.w[1] = c1;
-    o.w[2] = c2;
-    o.w[3] = c3;
-    return o;
-}
 
 // Byte o of each of the four words of v as one word (byte b from word b); sel = (4 + o) << 8
 // | o with zero upper bytes.
@@ -177,8 +153,7 @@ struct OctSite {
 
 // New octet word of one site at four same-parity slices: X its word, Tlo / Thi the words of
 // its time neighbours below and above (byte b = slice 4 g + b), Y / nm the words and sign
-// masks of its D neighbours.  ctr0: Philox counter word 0 of (site, parity, global group);
-// slot 8 o + r of word group w is replica cbase + r.  A lane takes SPL of the eight slots,
+// masks of its D neighbours.  draws(r) gives the Philox words of the lane's slot r.  A lane takes SPL of the eight slots,
 // those from SPL * half on; with SPL = 4 the two lanes of an item are neighbours and join
 // their flips with one lane exchange (both must call).  MASK = false: slots is the number of
 // the lane's slots in use, nslots - SPL * half (at most SPL counts), and each slot is
@@ -186,13 +161,11 @@ struct OctSite {
 // looked up (the tables of all eight slots lie in LDS) and slots is the lane's flip mask
 // (oct_slot_mask), which clears the flips of slots beyond the count: no per-slot test, more
 // registers live.
-template <int DT, int SPL, bool MASK>
+template <int DT, int SPL, bool MASK, class DrawOf>
 __device__ __forceinline__ uint32_t oct_update(uint32_t X, uint32_t Tlo,
                                                uint32_t Thi, const uint32_t (&Y)[DT],
                                                const uint32_t (&nm)[DT], const OctSite &site,
-                                               uint32_t ctr0, uint32_t tt, uint32_t cbase,
-                                               uint32_t n, uint32_t key0, uint32_t key1,
-                                               uint32_t slots, int half)
+                                               DrawOf &&draws, uint32_t slots, int half)
 {
     uint32_t v[9];
 #pragma unroll
@@ -220,7 +193,7 @@ __device__ __forceinline__ uint32_t oct_update(uint32_t X, uint32_t Tlo,
     for (int r = 0; r < SPL; ++r) {
         if (MASK || r < (int)slots) {
             const uint32_t idx = offs[r];  // table byte offsets of slot sh + r's four slices
-            const Words4 u = philox10_rk(ctr0, tt, cbase + (uint32_t)(sh + r), n, key0, key1);
+            const Words4 u = draws(r);
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
                 const uint32_t addr = __builtin_amdgcn_perm(tbase, idx, 0x0C060500u | (uint32_t)b);
@@ -234,6 +207,34 @@ __device__ __forceinline__ uint32_t oct_update(uint32_t X, uint32_t Tlo,
     if constexpr (SPL < 8) flip |= (uint32_t)__shfl_xor((int)flip, 1, kWave);
     return X ^ flip;
 }
+
+// The draws of a workgroup's slots in two sweeps (even and odd), in LDS: 8 bytes per slot, the
+// halves of Draws (a replica's part of a Philox call).  A lane reads a slot's pair where it
+// would otherwise form two products and two xors per call: whole octets are bound by VALU
+// issue, and this takes the 512-instance batch from 2.32 to 2.18 ms a cycle (1.87e12 to
+// 1.99e12 attempts/s).
+__device__ __forceinline__ void oct_put_draws(uint32_t at, int sw, uint32_t tt, uint32_t c0, uint32_t key0,
+                                              uint32_t key1)
+{
+    const uint32_t r = threadIdx.x;
+    if (r < 8) {
+        const Draws d = draws_of(tt, c0 + r, key0, key1);
+        st64(at + 64u * (uint32_t)(sw & 1) + 8u * r, ((uint64_t)d.l2 << 32) | d.h2);
+    }
+}
+
+// A lane's source of draws: at = its first slot's pair, c1 = word 1 after round 1 of its first
+// slot's calls (the next slot's is kPhiloxM1 more).
+struct OctDraws {
+    const OctLaunch &L;
+    uint32_t at, c1;
+    __device__ __forceinline__ Words4 get(const SiteDraws &s, int r) const
+    {
+        const uint64_t v = ld64(at + 8u * (uint32_t)r);
+        const Draws d = {c1 + kPhiloxM1 * (uint32_t)r, (uint32_t)v, (uint32_t)(v >> 32)};
+        return philox_draw<true>(d, s, L.key0, L.key1);
+    }
+};
 
 // The flip mask of oct_update for a lane of the given half: in every byte, the bits of the
 // lane's SPL slots that are among the octet's nslots in use.
@@ -429,7 +430,7 @@ __device__ __forceinline__ void oct_store(uint32_t *row, int g, int o, uint32_t 
 template <class Body>
 __device__ __forceinline__ void oct_dispatch(int D, bool split, Body &&body)
 {
-    auto go = [&](auto spl) {
+    auto go = [&](auto spl) __attribute__((always_inline)) {
         switch (D) {
         case 1: body(IC<1>{}, spl); break;
         case 2: body(IC<2>{}, spl); break;
@@ -463,6 +464,9 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
     const uint32_t nv = (uint32_t)(nslots - SPL * half);  // this lane's slots in use (signed)
     const uint32_t plane = (uint32_t)N * (uint32_t)G4 * 4u;
     const int nc = d.n_colors;
+    const uint32_t c1 = kPhiloxM1 * (uint32_t)(c0 + SPL * half), dat = o.red + 8u * (uint32_t)(SPL * half);
+    oct_put_draws(o.red, 0, (uint32_t)t0, (uint32_t)c0, L.key0, L.key1);
+    __syncthreads();
     if (nc >= 2) {
         // Class k of parity 0 and class k - 1 of parity 1 (mod nc; of the previous sweep
         // when k = 0) touch disjoint words: each writes its own sites' words of its parity
@@ -483,7 +487,6 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
                 const bool inA = it < itemsA;
                 const int p = inA ? 0 : 1;
                 const int jt = inA ? it : it - itemsA;
-                const uint32_t tt = (uint32_t)(t0 + (uint64_t)(inA ? sw : swB));
                 const uint32_t pb = inA ? 0u : plane, ob = inA ? plane : 0u;
                 const int gg = (jt >> lgL) & (G4 - 1);
                 const int i = (int)ld16(o.csite + 2u * (uint32_t)((inA ? a0 : b0) + (jt >> (lgG4 + lgL))));
@@ -502,12 +505,17 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
                     Y[e] = ld32(pb + ((j << lgG4) + (uint32_t)gg) * 4u);
                 }
                 const OctSite site = oct_site(o, i);
-                const uint32_t ctr0 = (uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)gg;
-                const uint32_t nx = oct_update<DT, SPL, false>(X, Tlo, Thi, Y, nm, site, ctr0, tt,
-                                                               (uint32_t)c0, (uint32_t)n, L.key0,
-                                                               L.key1, nv, half);
+                const SiteDraws sd = site_draws((uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)gg,
+                                                (uint32_t)n, L.key0, L.key1);
+                const OctDraws dr = {L, dat + 64u * (uint32_t)((inA ? sw : swB) & 1), c1};
+                const uint32_t nx = oct_update<DT, SPL, false>(X, Tlo, Thi, Y, nm, site,
+                                                               [&](int r) { return dr.get(sd, r); }, nv, half);
                 if (half == 0) st32(pb + rowi + 4u * (uint32_t)gg, nx);
             }
+            // the next sweep's draws, in the place of the previous one's (last read in the
+            // step with k = 0)
+            if (k == nc - 1)
+                oct_put_draws(o.red, sw + 1, (uint32_t)(t0 + (uint64_t)(sw + 1)), (uint32_t)c0, L.key0, L.key1);
             __syncthreads();
             if (++k == nc) {
                 k = 0;
@@ -517,7 +525,8 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
         return;
     }
     for (int sw = 0; sw < L.n_sweeps; ++sw) {
-        const uint32_t tt = (uint32_t)(t0 + (uint64_t)sw);
+        const OctDraws dr = {L, dat + 64u * (uint32_t)(sw & 1), c1};
+        oct_put_draws(o.red, sw + 1, (uint32_t)(t0 + (uint64_t)(sw + 1)), (uint32_t)c0, L.key0, L.key1);
         for (int p = 0; p < 2; ++p) {
             const uint32_t pb = (uint32_t)p * plane, ob = (uint32_t)(p ^ 1) * plane;
             for (int g = 0; g < d.n_colors; ++g) {
@@ -545,10 +554,10 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
                         Y[e] = ld32(pb + ((j << lgG4) + (uint32_t)gg) * 4u);
                     }
                     const OctSite site = oct_site(o, i);
-                    const uint32_t ctr0 = (uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)gg;
-                    const uint32_t nx = oct_update<DT, SPL, false>(X, Tlo, Thi, Y, nm, site, ctr0, tt,
-                                                                   (uint32_t)c0, (uint32_t)n, L.key0,
-                                                                   L.key1, nv, half);
+                    const SiteDraws sd = site_draws((uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)gg,
+                                                    (uint32_t)n, L.key0, L.key1);
+                    const uint32_t nx = oct_update<DT, SPL, false>(X, Tlo, Thi, Y, nm, site,
+                                                                   [&](int r) { return dr.get(sd, r); }, nv, half);
                     if (half == 0) st32(pb + rowi + 4u * (uint32_t)gg, nx);
                 }
                 __syncthreads();
@@ -626,6 +635,8 @@ __device__ __forceinline__ void oct_tile_item(const OctLaunch &L, char *lds, int
         constexpr int DT = decltype(dt)::value, SPL = decltype(spl)::value;
         oct_tile_sweeps<DT, SPL>(L, d, o, n, c0, nslots, t0);
     });
+    if (tid < 32) st32(o.red + 4u * (uint32_t)tid, 0u);  // held draws until here
+    __syncthreads();
     switch (d.D) {
     case 1: oct_tile_energy<1>(L, d, lds, o); break;
     case 2: oct_tile_energy<2>(L, d, lds, o); break;
@@ -714,51 +725,88 @@ struct OctPlanes {
 // Every colour class of parity p over the block's ng groups.  SPL: slots per lane (8, or 4
 // with two lanes per item, for blocks with few items per colour class).
 template <int DT, int SPL>
-__device__ __forceinline__ void oct_block_sweep(const OctLaunch &L, const InstDesc &d, const OctLds &o,
-                                                const OctPlanes &pl, int p, int n, int c0,
-                                                int nslots, int g0, int ng, uint32_t tt)
-{
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int G4 = d.G4, lgng = 31 - __clz(ng);
-    constexpr int lgL = SPL == 8 ? 0 : 1;  // lanes per item
-    // items come in lane pairs and the block size is even, so a thread keeps its half
-    const int half = tid & ((1 << lgL) - 1);
-    const uint32_t vmask = oct_slot_mask<SPL>(nslots, half);
-    for (int g = 0; g < d.n_colors; ++g) {
-        const int s0 = (int)ld32(o.coff + 4u * (uint32_t)g);
-        const int items = ((int)ld32(o.coff + 4u * (uint32_t)(g + 1)) - s0) << (lgng + lgL);
-        for (int it = tid; it < items; it += nt) {
-            const uint32_t gl4 = 4u * (uint32_t)((it >> lgL) & (ng - 1));
-            const int i = (int)ld16(o.csite + 2u * (uint32_t)(s0 + (it >> (lgng + lgL))));
-            const uint32_t own = pl.own + (uint32_t)i * pl.own_stride + gl4;
-            const uint32_t oth = pl.oth + (uint32_t)i * pl.oth_stride + gl4;
-            const uint32_t X = ld32(own);
-            const uint32_t W0 = ld32(oth), W1 = ld32(oth + 4u);
-            uint32_t Tlo, Thi;
-            if (p == 0) {
-                Tlo = __builtin_amdgcn_alignbyte(W1, W0, 3);
-                Thi = W1;
-            } else {
-                Tlo = W0;
-                Thi = __builtin_amdgcn_alignbyte(W1, W0, 1);
-            }
-            uint32_t Y[DT], nm[DT];
+struct OctBlock {
+    const OctLaunch &L;
+    const InstDesc &d;
+    const OctLds &o;
+    int n, g0, ng, lgng, half;
+    uint32_t vmask, c1, dat;
+    static constexpr int lgL = SPL == 8 ? 0 : 1;  // lanes per item
+
+    __device__ __forceinline__ OctBlock(const OctLaunch &L_, const InstDesc &d_, const OctLds &o_, int n_, int c0,
+                                        int nslots, int g0_, int ng_)
+        : L(L_), d(d_), o(o_), n(n_), g0(g0_), ng(ng_), lgng(31 - __clz(ng_)),
+          // items come in lane pairs and the block size is even, so a thread keeps its half
+          half((int)threadIdx.x & ((1 << lgL) - 1)), vmask(oct_slot_mask<SPL>(nslots, half)),
+          c1(kPhiloxM1 * (uint32_t)(c0 + SPL * half)), dat(o_.red + 8u * (uint32_t)(SPL * half))
+    {
+    }
+    __device__ __forceinline__ int first(int g) const { return (int)ld32(o.coff + 4u * (uint32_t)g); }
+    __device__ __forceinline__ int items(int g) const { return (first(g + 1) - first(g)) << (lgng + lgL); }
+    __device__ __forceinline__ int site(int g, int it) const
+    {
+        return (int)ld16(o.csite + 2u * (uint32_t)(first(g) + (it >> (lgng + lgL))));
+    }
+    __device__ __forceinline__ uint32_t group4(int it) const { return 4u * (uint32_t)((it >> lgL) & (ng - 1)); }
+    __device__ __forceinline__ SiteDraws site_part(int i, uint32_t gl4, int p) const
+    {
+        return site_draws((uint32_t)(2 * i + p) * (uint32_t)d.G4 + (uint32_t)g0 + (gl4 >> 2), (uint32_t)n, L.key0, L.key1);
+    }
+    // one item (both lanes of a pair call it)
+    template <class DrawOf>
+    __device__ __forceinline__ void update(const OctPlanes &pl, int p, int i, uint32_t gl4, DrawOf &&draws) const
+    {
+        const uint32_t own = pl.own + (uint32_t)i * pl.own_stride + gl4;
+        const uint32_t oth = pl.oth + (uint32_t)i * pl.oth_stride + gl4;
+        const uint32_t X = ld32(own);
+        const uint32_t W0 = ld32(oth), W1 = ld32(oth + 4u);
+        uint32_t Tlo, Thi;
+        if (p == 0) {
+            Tlo = __builtin_amdgcn_alignbyte(W1, W0, 3);
+            Thi = W1;
+        } else {
+            Tlo = W0;
+            Thi = __builtin_amdgcn_alignbyte(W1, W0, 1);
+        }
+        uint32_t Y[DT], nm[DT];
 #pragma unroll
-            for (int e = 0; e < DT; ++e) {
-                uint32_t j;
-                oct_entry(o, i * DT + e, j, nm[e]);
-                Y[e] = ld32(pl.own + j * pl.own_stride + gl4);
+        for (int e = 0; e < DT; ++e) {
+            uint32_t j;
+            oct_entry(o, i * DT + e, j, nm[e]);
+            Y[e] = ld32(pl.own + j * pl.own_stride + gl4);
+        }
+        const uint32_t nx = oct_update<DT, SPL, true>(X, Tlo, Thi, Y, nm, oct_site(o, i), draws, vmask, half);
+        if (half == 0) st32(own, nx);
+    }
+    // Parity p of sweep sw (its draws are in LDS), closed by a barrier.  Every item draws
+    // before it reads a spin, and a class's first items draw before the barrier that ends the
+    // class before it: ready(g) is that barrier for class g, or what else has to happen (a
+    // neighbour's record arrives) before class 0 may read.  With the shared draws 11.70 ->
+    // 11.46 us a sweep of 64 replicas of 1024 sites and 256 slices.
+    template <class Ready>
+    __device__ __forceinline__ void sweep(const OctPlanes &pl, int p, int sw, Ready &&ready) const
+    {
+        const OctDraws dr = {L, dat + 64u * (uint32_t)(sw & 1), c1};
+        for (int g = 0; g < d.n_colors; ++g) {
+            const int m = items(g);
+            bool first = true;
+            for (int it = (int)threadIdx.x; first || it < m; it += (int)blockDim.x) {
+                Words4 u[SPL];
+                const int i = it < m ? site(g, it) : 0;
+                const uint32_t gl4 = group4(it);
+                if (it < m) {
+                    const SiteDraws sd = site_part(i, gl4, p);
+#pragma unroll
+                    for (int r = 0; r < SPL; ++r) u[r] = dr.get(sd, r);
+                }
+                if (first) ready(g);  // by every thread: each takes this pass
+                first = false;
+                if (it < m) update(pl, p, i, gl4, [&](int r) { return u[r]; });
             }
-            const OctSite site = oct_site(o, i);
-            const uint32_t ctr0 = (uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)g0 + (gl4 >> 2);
-            const uint32_t nx = oct_update<DT, SPL, true>(X, Tlo, Thi, Y, nm, site, ctr0, tt,
-                                                          (uint32_t)c0, (uint32_t)n, L.key0, L.key1,
-                                                          vmask, half);
-            if (half == 0) st32(own, nx);
         }
         __syncthreads();
     }
-}
+};
 
 // The block's part of E_cl and C into its LDS reduction area, from the final spins: p1
 // holds parity 1 of the block's groups (as own), p0 parity 0 of groups g0 .. g0 + ng (as
@@ -856,9 +904,16 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     __syncthreads();
     const OctPlanes pl = {o.sp, 4u * (uint32_t)ng, o.oth, 4u * (uint32_t)(ng + 1)};
     const bool energy = L.last && p == 1;
-    oct_dispatch(d.D, L.split != 0, [&](auto dt, auto spl) {
+    oct_dispatch(d.D, L.split != 0, [&](auto dt, auto spl) __attribute__((always_inline)) {
         constexpr int DT = decltype(dt)::value, SPL = decltype(spl)::value;
-        oct_block_sweep<DT, SPL>(L, d, o, pl, p, n, c0, nslots, g0, ng, tt);
+        const OctBlock<DT, SPL> blk(L, d, o, n, c0, nslots, g0, ng);
+        oct_put_draws(o.red, 0, tt, (uint32_t)c0, L.key0, L.key1);
+        __syncthreads();
+        blk.sweep(pl, p, 0, [](int g) {
+            if (g > 0) __syncthreads();
+        });
+        if (tid < 32) st32(o.red + 4u * (uint32_t)tid, 0u);  // held draws until here
+        __syncthreads();
         if (energy) oct_block_energy<DT>(L, d, lds, o, pl, ng);
     });
     __syncthreads();
@@ -880,7 +935,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
 // an agent-scope release and acquire instead, which write the whole XCD's L2 back and
 // invalidate it, made config 4's sweeps 1.4x slower.)
 //
-// When every ring of blocks sits on one XCD (LOCAL), a block's reader and writer share that
+// When every ring of blocks sits on one XCD (local), a block's reader and writer share that
 // XCD's L2, and the stores need not go through to the coherence point: records and counts
 // are written with plain stores, which land in the L2, and read with the same
 // device-scope loads, which bypass the L1 and find the L2's line (measured between two
@@ -890,10 +945,9 @@ __device__ __forceinline__ uint32_t rec_ld(const uint32_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <bool LOCAL>
-__device__ __forceinline__ void rec_st(uint32_t *p, uint32_t v)
+__device__ __forceinline__ void rec_st(uint32_t *p, uint32_t v, bool local)
 {
-    if constexpr (LOCAL)
+    if (local)
         *p = v;
     else
         __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -922,12 +976,11 @@ __device__ __forceinline__ void oct_wait(const DevState &st, const int32_t *flag
 
 // After the workgroup's record stores: every wave waits for its own stores to complete
 // (a workgroup barrier does not wait for them), then thread 0 stores v.
-template <bool LOCAL>
-__device__ __forceinline__ void oct_publish(int32_t *flag, int v)
+__device__ __forceinline__ void oct_publish(int32_t *flag, int v, bool local)
 {
     __builtin_amdgcn_s_waitcnt(kOctWaitVmcnt0);
     __syncthreads();
-    if (threadIdx.x == 0) rec_st<LOCAL>(reinterpret_cast<uint32_t *>(flag), (uint32_t)v);
+    if (threadIdx.x == 0) rec_st(reinterpret_cast<uint32_t *>(flag), (uint32_t)v, local);
 }
 
 // All sweeps of a call over one octet slice block, with every block of the launch resident.
@@ -988,39 +1041,40 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
     const int polls = L.wait_polls > 0 ? L.wait_polls : kOctWaitPolls;
     const OctPlanes pl0 = {P0, RS, P1, RS}, pl1 = {P1 + 4u, RS, P0, RS};
     const uint32_t halo1 = P1, halo0 = P0 + 4u * (uint32_t)ng;  // x = 0 of P1, x = ng of P0
-    auto sweeps = [&](auto local) __attribute__((always_inline)) {
-        constexpr bool LOCAL = decltype(local)::value != 0;
-        oct_dispatch(d.D, L.split != 0, [&](auto dt, auto spl) {
-            constexpr int DT = decltype(dt)::value, SPL = decltype(spl)::value;
-            for (int sw = 0; sw < L.n_sweeps; ++sw) {
-                const uint32_t tt = (uint32_t)(t0 + (uint64_t)sw);
-                if (sw > 0) {
-                    oct_wait(st, prog + 2 * prev + 1, sw + L.wait_extra, polls);
-                    for (int i = tid; i < N; i += nt)
-                        st32(halo1 + (uint32_t)i * RS, rec_ld(R1prev + i));
+    const bool local = L.xcd_local != 0;
+    oct_dispatch(d.D, L.split != 0, [&](auto dt, auto spl) __attribute__((always_inline)) {
+        constexpr int DT = decltype(dt)::value, SPL = decltype(spl)::value;
+        const OctBlock<DT, SPL> blk(L, d, o, n, c0, nslots, g0, ng);
+        oct_put_draws(o.red, 0, (uint32_t)t0, (uint32_t)c0, L.key0, L.key1);
+        __syncthreads();
+        for (int ph = 0; ph < 2 * L.n_sweeps; ++ph) {
+            const int p = ph & 1, sw = ph >> 1;
+            if (p == 0)
+                oct_put_draws(o.red, sw + 1, (uint32_t)(t0 + (uint64_t)(sw + 1)), (uint32_t)c0, L.key0, L.key1);
+            const int32_t *flag = p == 0 ? prog + 2 * prev + 1 : prog + 2 * next;
+            const uint32_t *rin = p == 0 ? R1prev : R0next;
+            const uint32_t hin = p == 0 ? halo1 : halo0;
+            blk.sweep(p == 0 ? pl0 : pl1, p, sw, [&](int g) {
+                if (g > 0) {
+                    __syncthreads();
+                } else if (ph > 0) {
+                    // the neighbour's record, on its way while this block drew
+                    oct_wait(st, flag, sw + p + L.wait_extra, polls);
+                    for (int i = tid; i < N; i += nt) st32(hin + (uint32_t)i * RS, rec_ld(rin + i));
                     __syncthreads();
                 }
-                oct_block_sweep<DT, SPL>(L, d, o, pl0, 0, n, c0, nslots, g0, ng, tt);
-                for (int i = tid; i < N; i += nt) rec_st<LOCAL>(R0 + i, ld32(P0 + (uint32_t)i * RS));
-                oct_publish<LOCAL>(prog + 2 * b, sw + 1);
-                oct_wait(st, prog + 2 * next, sw + 1 + L.wait_extra, polls);
-                for (int i = tid; i < N; i += nt)
-                    st32(halo0 + (uint32_t)i * RS, rec_ld(R0next + i));
-                __syncthreads();
-                oct_block_sweep<DT, SPL>(L, d, o, pl1, 1, n, c0, nslots, g0, ng, tt);
-                if (sw + 1 < L.n_sweeps) {
-                    for (int i = tid; i < N; i += nt)
-                        rec_st<LOCAL>(R1 + i, ld32(P1 + (uint32_t)i * RS + 4u * (uint32_t)ng));
-                    oct_publish<LOCAL>(prog + 2 * b + 1, sw + 1);
-                }
+            });
+            if (ph + 1 < 2 * L.n_sweeps) {
+                uint32_t *rout = p == 0 ? R0 : R1;
+                const uint32_t from = p == 0 ? P0 : P1 + 4u * (uint32_t)ng;
+                for (int i = tid; i < N; i += nt) rec_st(rout + i, ld32(from + (uint32_t)i * RS), local);
+                oct_publish(prog + 2 * b + p, sw + 1, local);
             }
-            oct_block_energy<DT>(L, d, lds, o, pl1, ng);
-        });
-    };
-    if (L.xcd_local)
-        sweeps(IC<1>{});
-    else
-        sweeps(IC<0>{});
+        }
+        if (tid < 32) st32(o.red + 4u * (uint32_t)tid, 0u);  // held draws until here
+        __syncthreads();
+        oct_block_energy<DT>(L, d, lds, o, pl1, ng);
+    });
     __syncthreads();
     oct_block_energy_out(st, d, lds, o, c0, nslots);
     for (int k = tid; k < (N << lgng); k += nt) {

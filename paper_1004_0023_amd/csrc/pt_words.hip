@@ -94,70 +94,6 @@ __device__ __forceinline__ uint32_t lds32(const uint8_t *base, uint32_t off)
     return *reinterpret_cast<const uint32_t *>(base + off);
 }
 
-// ------------------------------------------------------------------ Philox
-
-// The part of a Philox call that a replica's draws of one sweep share: with counter
-// (c0, t, c, n), the second product of round 1 and the first of round 2 do not see c0.
-struct Draws {
-    uint32_t c1;      // word 1 after round 1
-    uint32_t h2, l2;  // the halves of round 2's first product, the high one with its key
-};
-
-__device__ __forceinline__ Draws draws_of(uint32_t t, uint32_t c, uint32_t k0, uint32_t k1)
-{
-    Draws r;
-    const uint64_t pb = (uint64_t)kPhiloxM1 * c;
-    r.c1 = (uint32_t)pb;
-    const uint64_t pa = (uint64_t)kPhiloxM0 * xor3((uint32_t)(pb >> 32), t, k0);
-    r.h2 = (uint32_t)(pa >> 32) ^ (k1 + kPhiloxW1);
-    r.l2 = (uint32_t)pa;
-    return r;
-}
-
-// The part that a site's draws share: round 1's first product and what round 2 makes of it
-// (k0, k1: the call's keys; n: counter word 3).
-struct SiteDraws {
-    uint32_t lo1, h2, l2;
-};
-
-__device__ __forceinline__ SiteDraws site_draws(uint32_t ctr0, uint32_t n, uint32_t k0, uint32_t k1)
-{
-    SiteDraws s;
-    const uint64_t pa = (uint64_t)kPhiloxM0 * ctr0;
-    s.lo1 = (uint32_t)pa;
-    const uint64_t pb = (uint64_t)kPhiloxM1 * xor3((uint32_t)(pa >> 32), n, k1);
-    s.h2 = (uint32_t)(pb >> 32) ^ (k0 + kPhiloxW0);
-    s.l2 = (uint32_t)pb;
-    return s;
-}
-
-// The call's four words: philox10(ctr0, t, c, n, k0, k1).
-__device__ __forceinline__ Words4 draw(const Draws &r, const SiteDraws &s, uint32_t k0, uint32_t k1)
-{
-    uint32_t c0 = s.h2 ^ r.c1, c1 = s.l2, c2 = r.h2 ^ s.lo1, c3 = r.l2;
-    k0 += 2 * kPhiloxW0;
-    k1 += 2 * kPhiloxW1;
-#pragma unroll
-    for (int i = 2; i < 10; ++i) {
-        const uint64_t pa = (uint64_t)kPhiloxM0 * c0;
-        const uint64_t pb = (uint64_t)kPhiloxM1 * c2;
-        const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(pa >> 32), c3, k1);
-        c1 = (uint32_t)pb;
-        c3 = (uint32_t)pa;
-        c0 = n0;
-        c2 = n2;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    Words4 o;
-    o.w[0] = c0;
-    o.w[1] = c1;
-    o.w[2] = c2;
-    o.w[3] = c3;
-    return o;
-}
-
 // ------------------------------------------------------------------ one word
 
 // Per launch, and per thread (its unit and group are fixed).
@@ -269,11 +205,11 @@ __device__ __forceinline__ void item(const Args &a, const WordsLds &t, const Lan
         for (int b = 0; b < 4; ++b) {
             if (b < nr) {
                 const uint32_t thr = ln.tb[b * a.tbl_words + idx.at(b)];
-                flip |= (draw(r[b], s, a.key0, a.key1).w[0] <= thr ? 1u : 0u) << (8 * b);
+                flip |= (philox_draw<false>(r[b], s, a.key0, a.key1).w[0] <= thr ? 1u : 0u) << (8 * b);
             }
         }
     } else {
-        const Words4 u = draw(r[0], s, a.key0, a.key1);
+        const Words4 u = philox_draw<false>(r[0], s, a.key0, a.key1);
 #pragma unroll
         for (int b = 0; b < 4; ++b) flip |= (u.w[b] <= ln.tb[idx.at(b)] ? 1u : 0u) << (8 * b);
     }
