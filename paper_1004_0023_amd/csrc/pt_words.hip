@@ -27,6 +27,8 @@
 //   narrow  F <= 20: in bytes (at most 245)
 //   middle  F <= 63: x (2F + 1) + f + F in bytes (at most 253), the rest per attempt
 //   wide    else:    in two pairs of 16-bit halves (at most 12,281)
+#include <utility>
+
 #include "pt_exchange.h"
 #include "pt_internal.h"
 
@@ -93,6 +95,15 @@ __device__ __forceinline__ uint32_t lds32(const uint8_t *base, uint32_t off)
 {
     return *reinterpret_cast<const uint32_t *>(base + off);
 }
+
+// Division by a number fixed per launch, of dividends below 2^32 / d (here both are below
+// the 2^16 words of LDS): one product instead of some twenty-five operations.
+struct Div {
+    uint32_t m;
+    int d;
+    __device__ __forceinline__ explicit Div(int d_) : m(0xFFFFFFFFu / (uint32_t)d_ + 1u), d(d_) {}
+    __device__ __forceinline__ int operator()(int x) const { return d == 1 ? x : (int)__umulhi((uint32_t)x, m); }
+};
 
 // ------------------------------------------------------------------ one word
 
@@ -273,7 +284,8 @@ __device__ __forceinline__ void sweeps(const SweepLaunch &L, const InstDesc &d, 
 
 // 2 E_cl and C of the tile's replicas, summed per replica in red[2 q], red[2 q + 1] (zeroed).
 // 2E = sum_i s_i (f_i + h_i) with f + F from the weighted counts as in the sweep; sumJ comes
-// from the entries (their two weight bytes sum to |J|).
+// from the entries (their two weight bytes sum to |J|).  A lane takes both parities of a
+// word, so that a neighbour's entry is read once.
 template <int MODE, bool RM>
 __device__ __forceinline__ void energy(const InstDesc &d, const Tile &tile, const WordsLds &t, const Args &a,
                                        unsigned long long *red)
@@ -282,69 +294,86 @@ __device__ __forceinline__ void energy(const InstDesc &d, const Tile &tile, cons
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, nw = blockDim.x / kWave;
     const int wpu = nw > units ? nw / units : 1, ngroups = nw / wpu;
     const int grp = wid / wpu, sub = wid - grp * wpu;
+    const bool timed = d.M >= 2;
+    const Div by_row(row);
     constexpr int NR = RM ? 4 : 1;
     for (int q = grp; q < units && grp < ngroups; q += ngroups) {
-        long long e2[NR], cc[NR];
+        // 32 bits hold a wave's sums: |2E| and |C| of a replica in LDS are below 2^30
+        int e2[NR], cc[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k) e2[k] = cc[k] = 0;
         const int items = d.N * row;
         for (int it = sub * kWave + lane; it < items; it += wpu * kWave) {
-            const int i = it / row, g = it - i * row;
-            const uint32_t base = 4u * (uint32_t)(q * stride + g), irow = (uint32_t)i * a.row;
-            int sumJ = 0;
+            const int i = RM ? it : by_row(it), g = RM ? 0 : it - i * row;
+            const uint32_t base = 4u * (uint32_t)(q * stride + g), irow = __umul24((uint32_t)i, a.row);
+            uint32_t X[2], a0[2] = {0u, 0u}, a1[2] = {0u, 0u}, sumJ = 0;
+            X[0] = lds32(t.sp, base + irow);
+            X[1] = timed ? lds32(t.sp, base + a.plane + irow) : 0u;
+#pragma unroll 4
             for (int k = 0; k < a.D; ++k) {
-                const uint32_t e = t.ent[i * a.D + k];
-                sumJ += (int)(e & 0xFFu) + (int)((e >> 8) & 0xFFu);
+                const uint32_t e = t.ent[i * a.D + k], at = base + __umul24(e >> 16, a.row);
+                const uint32_t y[2] = {lds32(t.sp, at), lds32(t.sp, timed ? at + a.plane : at)};
+                sumJ = __builtin_amdgcn_udot4(e, 0x00000101u, sumJ, false);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const uint32_t w = __builtin_amdgcn_perm(0u, e, y[p]);
+                    if constexpr (MODE == kWordsWide) {
+                        a0[p] += w & 0x00FF00FFu;
+                        a1[p] += (w >> 8) & 0x00FF00FFu;
+                    } else {
+                        a0[p] += w;
+                    }
+                }
             }
-            const int b0 = (int)(t.bias[i] & (MODE == kWordsWide ? 0xFFFFu : 0xFFu));
-            const int hF = b0 + sumJ - 2 * d.F;  // h - F
+            const uint32_t bias = t.bias[i];
+            const int b0 = (int)(bias & (MODE == kWordsWide ? 0xFFFFu : 0xFFu));
+            const int hF = b0 + (int)sumJ - 2 * d.F;  // h - F
             const int left = RM ? 4 : d.Mh - 4 * g, nv = left < 4 ? left : 4;
-            uint32_t X[2] = {0u, 0u};
+            const uint32_t vm = 0x01010101u >> (8 * (4 - nv));
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                if (p >= d.parities) break;
-                const uint32_t plane = base + (uint32_t)p * a.plane;
-                X[p] = lds32(t.sp, plane + irow);
-                uint32_t a0, a1;
-                field<0, MODE>(a, t, plane, i, a0, a1);
+                if (p > 0 && !timed) break;
+                if constexpr (!RM && MODE != kWordsWide) {
+                    const uint32_t G = (a0[p] << 1) + bias;  // f + F of every spin
+                    e2[0] += 2 * (int)__builtin_amdgcn_udot4(X[p], G, 0u, false) + 2 * hF * __popc(X[p]) -
+                             (int)__builtin_amdgcn_udot4(vm, G, 0u, false) - nv * hF;
+                } else {
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    if (b >= nv) break;
-                    const int cnt = MODE == kWordsWide ? (int)(((b & 1 ? a1 : a0) >> (b & 2 ? 16 : 0)) & 0xFFFFu)
-                                                  : (int)((a0 >> (8 * b)) & 0xFFu);
-                    const int s = 2 * (int)((X[p] >> (8 * b)) & 1u) - 1;
-                    e2[RM ? b : 0] += s * (2 * cnt + b0 + hF);
+                    for (int b = 0; b < 4; ++b) {
+                        if (b >= nv) break;
+                        const int cnt = MODE == kWordsWide ? (int)(((b & 1 ? a1[p] : a0[p]) >> (b & 2 ? 16 : 0)) & 0xFFFFu)
+                                                           : (int)((a0[p] >> (8 * b)) & 0xFFu);
+                        const int sgn = 2 * (int)((X[p] >> (8 * b)) & 1u) - 1;
+                        e2[RM ? b : 0] += sgn * (2 * cnt + b0 + hF);
+                    }
                 }
             }
-            if (d.M >= 2) {
+            if (timed) {
                 // bonds (2m, 2m + 1) and (2m + 1, 2m + 2): parity 0 at the next slice
-                uint32_t nx;
                 if constexpr (RM) {
-                    nx = X[0];
+                    const uint32_t diff = X[0] ^ X[1];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) cc[b] += 2 - 4 * (int)((diff >> (8 * b)) & 1u);
                 } else {
                     const int gn = g + 1 == row ? 0 : g + 1;
-                    nx = __builtin_amdgcn_perm(X[0], lds32(t.sp, 4u * (uint32_t)(q * stride + gn) + irow),
-                                               nv == 4 ? 0x00070605u : nv == 3 ? 0x0C000605u
-                                                                   : nv == 2   ? 0x0C0C0005u
-                                                                               : 0x0C0C0C00u);
+                    const uint32_t nx = __builtin_amdgcn_perm(
+                        X[0], lds32(t.sp, 4u * (uint32_t)(q * stride + gn) + irow),
+                        nv == 4 ? 0x00070605u : nv == 3 ? 0x0C000605u : nv == 2 ? 0x0C0C0005u : 0x0C0C0C00u);
+                    cc[0] += 2 * nv - 2 * (__popc(X[0] ^ X[1]) + __popc(X[1] ^ nx));
                 }
-                const uint32_t diff = (X[0] ^ X[1]) + (X[1] ^ nx);
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (b < nv) cc[RM ? b : 0] += 2 - 2 * (int)((diff >> (8 * b)) & 3u);
             }
         }
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            long long e = e2[k], c = cc[k];
+            int e = e2[k], c = cc[k];
 #pragma unroll
             for (int o = kWave / 2; o > 0; o >>= 1) {
                 e += __shfl_xor(e, o, kWave);
                 c += __shfl_xor(c, o, kWave);
             }
             if (lane == 0) {
-                atomicAdd(&red[2 * (NR * q + k)], (unsigned long long)e);
-                atomicAdd(&red[2 * (NR * q + k) + 1], (unsigned long long)c);
+                atomicAdd(&red[2 * (NR * q + k)], (unsigned long long)(long long)e);
+                atomicAdd(&red[2 * (NR * q + k) + 1], (unsigned long long)(long long)c);
             }
         }
     }
@@ -354,123 +383,162 @@ __device__ __forceinline__ void energy(const InstDesc &d, const Tile &tile, cons
 
 __device__ __forceinline__ uint32_t spread4(uint32_t v) { return (v * 0x00204081u) & 0x01010101u; }
 
-// Byte-encoded replicas of the tile into LDS words (IN) or back.
-template <bool IN>
-__device__ __forceinline__ void move_bytes(const DevState &st, const InstDesc &d, const Tile &tile, uint8_t *sp)
+// A tile starts with half a dozen arrays to stage, each a trip to memory that no cache of
+// this launch holds yet.  Every array's first K elements per thread are therefore loaded
+// before any is stored (indexes past the end are clamped, so that no load is under a branch
+// and waited for there); the rest follow K at a time.
+template <int K, class Load>
+struct Staged {
+    decltype(std::declval<Load>()(0)) v[K];
+    Load load;
+    int count;
+    __device__ __forceinline__ Staged(int n, Load f) : load(f), count(n)
+    {
+#pragma unroll
+        for (int u = 0; u < K; ++u) v[u] = load(min((int)threadIdx.x + u * (int)blockDim.x, count - 1));
+    }
+    template <class Store>
+    __device__ __forceinline__ void put(Store &&store)
+    {
+        const int nt = blockDim.x;
+        for (int at = threadIdx.x;;) {
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+                if (at + u * nt < count) store(at + u * nt, v[u]);
+            at += K * nt;
+            if (at >= count) break;
+#pragma unroll
+            for (int u = 0; u < K; ++u) v[u] = load(min(at + u * nt, count - 1));
+        }
+    }
+};
+
+// The tile's replicas in the byte encoding, as LDS words: word x of all of them.
+template <bool RM>
+struct LoadBytes {
+    const uint8_t *dev;
+    int rep_bytes, G4, Mh, P;
+    Div by_unit, by_row;  // words of a unit, of a row
+    __device__ __forceinline__ uint32_t operator()(int x) const
+    {
+        const int q = by_unit(x), w = x - q * by_unit.d;
+        if constexpr (RM) {
+            // the four bytes are one position of four replicas (past the last one: its own)
+            uint32_t v = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t y = dev[(int64_t)min(4 * q + b, P - 1) * rep_bytes + w];
+                v |= (4 * q + b < P ? y : 0u) << (8 * b);
+            }
+            return v;
+        } else {
+            const uint32_t *rep = reinterpret_cast<const uint32_t *>(dev + (int64_t)q * rep_bytes);
+            if ((Mh & 3) == 0) return rep[w];
+            // a row of Mh bytes need not start at a word: two words joined, the padding cleared
+            const int r = by_row(w), m = 4 * (w - r * G4), at = r * Mh + m, nv = min(Mh - m, 4);
+            const uint32_t lo = rep[at >> 2], hi = rep[min((at >> 2) + 1, (rep_bytes >> 2) - 1)];
+            return __builtin_amdgcn_alignbyte(hi, lo, (uint32_t)(at & 3)) & (0xFFFFFFFFu >> (8 * (4 - nv)));
+        }
+    }
+};
+
+// LDS words of byte-encoded replicas back to device memory.
+template <bool RM>
+__device__ __forceinline__ void store_bytes(const DevState &st, const InstDesc &d, const Tile &tile, const uint8_t *sp)
 {
     uint8_t *dev = st.spins + d.spin_base + (int64_t)tile.c0 * d.rep_bytes;
     const int stride = (int)words_stride(d);
-    if (d.M <= 2) {
-        // a word's four bytes are one position of four replicas
+    if constexpr (RM) {
         const int pos = d.parities * d.N, units = words_units(d, tile.P);
+        const Div by_unit(pos);
         for (int it = threadIdx.x; it < pos * units; it += blockDim.x) {
-            const int Q = it / pos, x = it - Q * pos;
-            uint32_t *w = reinterpret_cast<uint32_t *>(sp) + Q * stride + x;
-            if (IN) {
-                uint32_t v = 0;
+            const int Q = by_unit(it), x = it - Q * pos;
+            const uint32_t v = reinterpret_cast<const uint32_t *>(sp)[Q * stride + x];
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (4 * Q + b < tile.P) v |= (uint32_t)dev[(int64_t)(4 * Q + b) * d.rep_bytes + x] << (8 * b);
-                *w = v;
-            } else {
-                const uint32_t v = *w;
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (4 * Q + b < tile.P) dev[(int64_t)(4 * Q + b) * d.rep_bytes + x] = (uint8_t)(v >> (8 * b));
-            }
+            for (int b = 0; b < 4; ++b)
+                if (4 * Q + b < tile.P) dev[(int64_t)(4 * Q + b) * d.rep_bytes + x] = (uint8_t)(v >> (8 * b));
         }
         return;
     }
     const int words = (d.N * d.M + 3) >> 2;  // of a replica in device memory
-    if ((d.Mh & 3) == 0) {
-        for (int q = 0; q < tile.P; ++q) {
-            uint32_t *l = reinterpret_cast<uint32_t *>(sp) + q * stride;
-            uint32_t *g = reinterpret_cast<uint32_t *>(dev + (int64_t)q * d.rep_bytes);
-            for (int w = threadIdx.x; w < words; w += blockDim.x) {
-                if (IN)
-                    l[w] = g[w];
-                else
-                    g[w] = l[w];
-            }
-        }
-        return;
-    }
-    // rows are not whole words: four consecutive bytes of device memory at a time
     const int rows = 2 * d.N;
+    const Div by_half(d.Mh);
     for (int q = 0; q < tile.P; ++q) {
-        uint8_t *l = sp + 4 * (int64_t)q * stride;
+        const uint8_t *l = sp + 4 * (int64_t)q * stride;
         uint32_t *g = reinterpret_cast<uint32_t *>(dev + (int64_t)q * d.rep_bytes);
         for (int w = threadIdx.x; w < words; w += blockDim.x) {
-            int rw = 4 * w / d.Mh, m = 4 * w - rw * d.Mh;
-            uint32_t v = IN ? g[w] : 0u;
+            if ((d.Mh & 3) == 0) {
+                g[w] = reinterpret_cast<const uint32_t *>(l)[w];
+                continue;
+            }
+            int rw = by_half(4 * w), m = 4 * w - rw * d.Mh;
+            uint32_t v = 0;
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                if (rw < rows) {
-                    if (IN)
-                        l[rw * 4 * d.G4 + m] = (uint8_t)(v >> (8 * b));
-                    else
-                        v |= (uint32_t)l[rw * 4 * d.G4 + m] << (8 * b);
-                }
+                if (rw < rows) v |= (uint32_t)l[rw * 4 * d.G4 + m] << (8 * b);
                 if (++m == d.Mh) {
                     m = 0;
                     ++rw;
                 }
             }
-            if (!IN) g[w] = v;
+            g[w] = v;
         }
     }
 }
 
-// Bit-packed replicas (all within one word group) into LDS words, or back: the words of a
-// four-slice group are one 16-byte load for all the tile's replicas.  Other tiles hold
-// other bits of the same words, so the bits that changed are flipped with atomic xors.
-template <bool IN>
-__device__ __forceinline__ void move_bits(const DevState &st, const InstDesc &d, const Tile &tile, uint8_t *sp)
+// Bit-packed replicas (all within one word group): the words of a four-slice group are one
+// 16-byte load for all the tile's replicas.
+struct LoadBits {
+    const uint4 *dev;
+    __device__ __forceinline__ uint4 operator()(int x) const { return dev[x]; }
+};
+
+template <bool RM>
+__device__ __forceinline__ void put_bits(const InstDesc &d, const Tile &tile, uint32_t *l, int x, const uint4 &v)
 {
-    const int row = d.G4, pos = d.parities * d.N * row, stride = (int)words_stride(d);
-    const int c = tile.c0 & 31, units = words_units(d, tile.P);
-    uint32_t *dev = reinterpret_cast<uint32_t *>(st.spins + d.spin_base) +
-                    (int64_t)(tile.c0 >> 5) * d.parities * d.N * d.bp_row;
-    uint32_t *l = reinterpret_cast<uint32_t *>(sp);
-    for (int x = threadIdx.x; x < pos; x += blockDim.x) {
-        uint4 v = reinterpret_cast<const uint4 *>(dev)[x];
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        if (d.M <= 2) {
-            uint32_t now = 0, mask = 0;
-            for (int Q = 0; Q < units; ++Q) {
-                const int sh = c + 4 * Q, nv = min(4, tile.P - 4 * Q);
-                if (IN) {
-                    l[Q * stride + x] = spread4((w[0] >> sh) & ((1u << nv) - 1u));
-                } else {
-                    const uint32_t y = l[Q * stride + x];
-                    now |= ((y | (y >> 7) | (y >> 14) | (y >> 21)) & 0xFu) << sh;
-                    mask |= ((1u << nv) - 1u) << sh;
-                }
-            }
-            if (!IN) {
-                const uint32_t diff = (w[0] ^ now) & mask;
-                if (diff) atomicXor(dev + 4 * (int64_t)x, diff);
-            }
-            continue;
+    const int stride = (int)words_stride(d), c = tile.c0 & 31;
+    if constexpr (RM) {
+        for (int Q = 0; 4 * Q < tile.P; ++Q) {
+            const int nv = min(4, tile.P - 4 * Q);
+            l[Q * stride + x] = spread4((v.x >> (c + 4 * Q)) & ((1u << nv) - 1u));
         }
-        if (IN) {
-            for (int q = 0; q < tile.P; ++q) {
-                uint32_t y = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) y |= ((w[b] >> (c + q)) & 1u) << (8 * b);
-                l[q * stride + x] = y;
-            }
-        } else {
-            uint32_t diff[4] = {0u, 0u, 0u, 0u};
-            for (int q = 0; q < tile.P; ++q) {
-                const uint32_t y = l[q * stride + x];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) diff[b] |= (((y >> (8 * b)) ^ (w[b] >> (c + q))) & 1u) << (c + q);
-            }
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if (diff[b]) atomicXor(dev + 4 * (int64_t)x + b, diff[b]);
+    } else {
+        for (int q = 0; q < tile.P; ++q) {
+            const int sh = c + q;
+            l[q * stride + x] = ((v.x >> sh) & 1u) | ((v.y >> sh) & 1u) << 8 | ((v.z >> sh) & 1u) << 16 |
+                                ((v.w >> sh) & 1u) << 24;
         }
+    }
+}
+
+// And back.  Other tiles hold other bits of the same words, so the bits that changed are
+// flipped with atomic xors.
+template <bool RM>
+__device__ __forceinline__ void store_bits(const InstDesc &d, const Tile &tile, const uint32_t *l, uint32_t *dev,
+                                           int x, const uint4 &v)
+{
+    const int stride = (int)words_stride(d), c = tile.c0 & 31;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    if constexpr (RM) {
+        uint32_t now = 0, mask = 0;
+        for (int Q = 0; 4 * Q < tile.P; ++Q) {
+            const int sh = c + 4 * Q, nv = min(4, tile.P - 4 * Q);
+            const uint32_t y = l[Q * stride + x];
+            now |= ((y | (y >> 7) | (y >> 14) | (y >> 21)) & 0xFu) << sh;
+            mask |= ((1u << nv) - 1u) << sh;
+        }
+        const uint32_t diff = (w[0] ^ now) & mask;
+        if (diff) atomicXor(dev + 4 * (int64_t)x, diff);
+    } else {
+        uint32_t diff[4] = {0u, 0u, 0u, 0u};
+        for (int q = 0; q < tile.P; ++q) {
+            const uint32_t y = l[q * stride + x];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) diff[b] |= (((y >> (8 * b)) ^ (w[b] >> (c + q))) & 1u) << (c + q);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (diff[b]) atomicXor(dev + 4 * (int64_t)x + b, diff[b]);
     }
 }
 
@@ -493,28 +561,54 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     const int tid = threadIdx.x, nt = blockDim.x;
     const bool packed = d.bp_row != 0;
 
-    for (int e = tid; e < d.N * d.D; e += nt) ent[e] = st.ent[d.ent_base + e];
-    for (int i = tid; i < d.N; i += nt) {
-        bias[i] = st.bias[d.site_base + i];
-        csite[i] = st.csite[d.site_base + i];
-    }
-    for (int g = tid; g <= d.n_colors; g += nt) coff[g] = st.cls_off[d.cls_base + g];
-    for (int k = tid; k < tile.P * d.tbl_words; k += nt) {
-        const int q = k / d.tbl_words, e = k - q * d.tbl_words;
-        tbl[k] = st.tbl[d.tbl_base + (int64_t)st.rung_of[d.rep_base + tile.c0 + q] * d.tbl_words + e];
-    }
-    for (int k = tid; k < 2 * words_units(d, tile.P) * words_rpw(d); k += nt) red[k] = 0;
-    const uint64_t t0 = st.ctr[n].t;
-    if (packed) {
-        move_bits<true>(st, d, tile, sp);
-    } else {
-        if (!RM && (d.Mh & 3) != 0) {
-            const int words = tile.P * (int)words_stride(d);
-            for (int w = tid; w < words; w += nt) reinterpret_cast<uint32_t *>(sp)[w] = 0u;
-            __syncthreads();
+    const int units = words_units(d, tile.P), pos = d.parities * d.N * words_row(d), stride = (int)words_stride(d);
+    uint32_t *packed_dev = reinterpret_cast<uint32_t *>(st.spins + d.spin_base) +
+                           (int64_t)(tile.c0 >> 5) * d.parities * d.N * d.bp_row;
+    const LoadBits load_bits = {reinterpret_cast<const uint4 *>(packed_dev)};
+    {
+        auto table_at = [&](int k) {
+            const int q = k / d.tbl_words;
+            return d.tbl_base + (int64_t)st.rung_of[d.rep_base + tile.c0 + q] * d.tbl_words + (k - q * d.tbl_words);
+        };
+        const int n_tbl = tile.P * d.tbl_words;
+        auto load_tbl = [&](int k) { return st.tbl[table_at(k)]; };
+        // the first table addresses (which wait for the rungs) ahead of everything else
+        Staged<2, decltype(load_tbl)> s_tbl(n_tbl, load_tbl);
+        auto load_ent = [&](int e) { return st.ent[d.ent_base + e]; };
+        Staged<2, decltype(load_ent)> s_ent(d.N * d.D, load_ent);
+        auto load_bias = [&](int i) { return st.bias[d.site_base + i]; };
+        Staged<1, decltype(load_bias)> s_bias(d.N, load_bias);
+        auto load_site = [&](int i) { return st.csite[d.site_base + i]; };
+        Staged<1, decltype(load_site)> s_site(d.N, load_site);
+        auto load_cls = [&](int g) { return st.cls_off[d.cls_base + g]; };
+        Staged<1, decltype(load_cls)> s_cls(d.n_colors + 1, load_cls);
+        auto put_rest = [&]() __attribute__((always_inline)) {
+            s_ent.put([&](int e, uint32_t v) { ent[e] = v; });
+            s_bias.put([&](int i, uint32_t v) { bias[i] = v; });
+            s_site.put([&](int i, uint16_t v) { csite[i] = v; });
+            s_cls.put([&](int g, int32_t v) { coff[g] = v; });
+            s_tbl.put([&](int k, uint32_t v) { tbl[k] = v; });
+        };
+        if (packed) {
+            Staged<4, LoadBits> s_sp(pos, load_bits);
+            put_rest();
+            s_sp.put([&](int x, const uint4 &v) {
+                put_bits<RM>(d, tile, reinterpret_cast<uint32_t *>(sp), x, v);
+            });
+        } else {
+            const Div by_unit(pos), by_row(d.G4);
+            const LoadBytes<RM> load = {st.spins + d.spin_base + (int64_t)tile.c0 * d.rep_bytes, d.rep_bytes,
+                                        d.G4, d.Mh, tile.P, by_unit, by_row};
+            Staged<RM ? 2 : 6, LoadBytes<RM>> s_sp(units * pos, load);
+            put_rest();
+            s_sp.put([&](int x, uint32_t v) {
+                const int q = by_unit(x);
+                reinterpret_cast<uint32_t *>(sp)[q * stride + x - q * pos] = v;
+            });
         }
-        move_bytes<true>(st, d, tile, sp);
     }
+    for (int k = tid; k < 2 * units * words_rpw(d); k += nt) red[k] = 0;
+    const uint64_t t0 = st.ctr[n].t;
     __syncthreads();
 
     const WordsLds t = {sp, ent, bias, csite, coff, tbl};
@@ -533,7 +627,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     a.tbl_words = d.tbl_words;
     // lanes run over (unit, group), groups fastest; each keeps its own and strides over the
     // sites of a class, threads past the last whole row of lanes stay idle
-    const int lanes = words_units(d, tile.P) * row;  // at most nt (the host's choice of P)
+    const int lanes = units * row;  // at most nt (the host's choice of P)
     Tid id;
     id.rows = nt / lanes;
     id.s = tid / lanes;
@@ -575,10 +669,14 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     case kWordsMiddle: run(IntC<kWordsMiddle>{}); break;
     default: run(IntC<kWordsWide>{}); break;
     }
-    if (packed)
-        move_bits<false>(st, d, tile, sp);
-    else
-        move_bytes<false>(st, d, tile, sp);
+    if (packed) {
+        Staged<4, LoadBits> s_sp(pos, load_bits);
+        s_sp.put([&](int x, const uint4 &v) {
+            store_bits<RM>(d, tile, reinterpret_cast<const uint32_t *>(sp), packed_dev, x, v);
+        });
+    } else {
+        store_bytes<RM>(st, d, tile, sp);
+    }
     __syncthreads();
     for (int q = tid; q < tile.P; q += nt) {
         const int64_t e = (int64_t)red[2 * q] / 2, cc = (int64_t)red[2 * q + 1];
