@@ -87,6 +87,9 @@ struct Plan {
     int64_t orec_words = 0;                    // words of each boundary-record region
     bool bp_generic = false;                   // some packed instance runs the per-class kernel
     bool words_alt = false;                    // every whole octet could run as word tiles
+    // byte encoding: every instance could run as octets (lists, tables and entries as for the
+    // packed one), which the tuner may choose instead of the byte tiles
+    bool oct_alt = false;
     int64_t halo_words = 0; // one buffer of slice-block boundary records, at most
     uint64_t flips_per_sweep = 0;
     // byte offsets in the workspace
@@ -200,8 +203,20 @@ bool rings_in_runs(const std::vector<std::pair<int, int>> &rings, int nb)
     return true;
 }
 
-int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t encoding, Plan &P)
+// Whether the launch shape is left to the tuner and no flag asks for a particular route.
+bool free_shape(const pt_options &opt)
 {
+    return opt.tile_replicas == 0 && opt.tile_bytes == 0 && opt.block_threads == 0 &&
+           !(opt.flags & (PT_FLAG_SLICE_BLOCKS | PT_FLAG_FOUR_SLICE_LANES | PT_FLAG_TWO_WORD_LANES |
+                          PT_FLAG_NO_LATENCY_PATH | PT_FLAG_BLOCK_LAUNCH_PER_SWEEP | PT_FLAG_DEVICE_SCOPE_RECORDS |
+                          PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT | PT_FLAG_TEST_XCD_MISMATCH |
+                          PT_FLAG_INJECT_LAUNCH_OOR_ONCE));
+}
+
+int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Plan &P)
+{
+    const uint32_t flags = opt.flags;
+    const int32_t encoding = opt.encoding;
     if (!inst || n_inst < 1) return fail(PT_EINVAL, "need at least one instance");
     if (encoding != PT_INT8 && encoding != PT_BITPACK32) return fail(PT_EINVAL, "unknown encoding");
     P = Plan();
@@ -209,7 +224,8 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
     const bool bp = encoding == PT_BITPACK32;
     // octets of the batch, whichever kernel runs them
     int64_t octets = 0;
-    for (int n = 0; bp && n < n_inst; ++n) octets += (inst[n].R + 7) / 8;
+    for (int n = 0; n < n_inst; ++n) octets += (inst[n].R + 7) / 8;
+    P.oct_alt = !bp && free_shape(opt);
     int64_t rep = 0, pair = 0, adjb = 0, offb = 0, siteb = 0, entb = 0, clsb = 0, tblb = 0,
             spinb = 0, wgb = 0;
     for (int n = 0; n < n_inst; ++n) {
@@ -280,7 +296,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and degrees
         // up to D <= 8 on the fast shapes (M a power-of-two multiple of 8).  Instances of
         // several degrees that do not fit them even as blocks of one group run elsewhere.
-        if (bp && d.fast && in.n_edges > 0 && in.N <= 32767) {
+        if ((bp || P.oct_alt) && d.fast && in.n_edges > 0 && in.N <= 32767) {
             bool ok = D <= 8, regular = true;
             for (int e = 0; ok && e < in.n_edges; ++e) ok = std::abs((int)in.edge_J[e]) == 1;
             for (int i = 0; ok && i < in.N; ++i) {
@@ -293,6 +309,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         // do not take (and, in batches with fewer octets than compute units, those they do:
         // the tuner decides), where padded neighbour rows and one replica fit a workgroup's
         // LDS (and, bit-packed, a row's lanes fit the smallest workgroup)
+        P.oct_alt = P.oct_alt && d.oct;
         if ((bp ? (!d.oct || octets < kMostCus) && d.G4 <= 64 : !d.fast) &&
             (int64_t)in.N * d.D * 4 <= kLdsPerWorkgroup) {
             d.words = words_mode(F);
@@ -353,7 +370,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         } else {
             for (int i = 0; i < in.N; ++i) P.bias.push_back(0);
         }
-        if (d.oct) {
+        if (bp ? d.oct : P.oct_alt) {
             // entries and field codes padded to 16 bytes per instance (the kernels copy them
             // in 16-byte pieces)
             d.oent_base = (int32_t)P.oent.size();
@@ -474,6 +491,18 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
             }
         }
         P.bp_n_eblk = (int32_t)(P.bp_eblk.size() / 4);
+        if (P.bp_sblk.size() / 2 > 0x7fffffff || P.bp_eblk.size() / 4 > 0x7fffffff)
+            return fail(PT_EINVAL, "batch too large");
+    }
+    // Byte batches that could run as octets may: a cycle of 192 (512) instances of the uneven
+    // batch takes 1182 (2998) us as byte tiles and 936 (2280) as octets.  Batches of fewer
+    // octets than half the compute units are not offered the choice (at 136 octets the byte
+    // tiles, several to an octet, fill the chip better: 210 us), and the tuner makes it.
+    bool any_block = false;
+    for (const auto &d : P.desc)
+        any_block = any_block || (d.oct && oct_lds_bytes(d, d.G4, kOctTile) > kLdsPerWorkgroup / 2);
+    P.oct_alt = P.oct_alt && (any_block || octets >= kMostCus / 2);
+    if (bp || P.oct_alt) {
         // octet work: whole octets where one takes at most half a compute unit's LDS
         // (largest first), else slice blocks of ng groups, ng about 512 colour-class items
         // per launch and class
@@ -491,11 +520,14 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
                 while (2 * ng < d.G4 && (int64_t)2 * ng * d.N <= 512 * (int64_t)d.n_colors &&
                        oct_lds_bytes(d, 2 * ng, kOctResident) <= kLdsPerWorkgroup / 2)
                     ng *= 2;
-                if (oct_lds_bytes(d, ng, kOctResident) > kLdsPerWorkgroup)
-                    return fail(PT_EINVAL, "instance " + std::to_string(n) +
-                                               ": an octet slice block does not fit in LDS");
+                if (oct_lds_bytes(d, ng, kOctResident) > kLdsPerWorkgroup) {
+                    if (bp)
+                        return fail(PT_EINVAL, "instance " + std::to_string(n) +
+                                                   ": an octet slice block does not fit in LDS");
+                    P.oct_alt = false;
+                }
             }
-            for (int w = 0; w < d.bp_W; ++w)
+            for (int w = 0; w < (d.R + 31) / 32; ++w)
                 for (int o = 0; o < 4 && 32 * w + 8 * o < d.R; ++o) {
                     if (whole) {
                         tiles.push_back({n, w, o, 0, d.G4, 0, 0, 0});
@@ -588,7 +620,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         for (const auto &t : blocks) P.otiles.insert(P.otiles.end(), t.begin(), t.end());
         P.n_otile = (int32_t)tiles.size();
         P.n_oblock = (int32_t)blocks.size();
-        P.words_alt = P.n_otile > 0 && P.n_oblock == 0 && !P.bp_generic && !(flags & PT_FLAG_WORK_QUEUE);
+        P.words_alt = bp && P.n_otile > 0 && P.n_oblock == 0 && !P.bp_generic && !(flags & PT_FLAG_WORK_QUEUE);
         for (const auto &d : P.desc) P.words_alt = P.words_alt && d.words;
         // slice blocks: one pass over a colour class of the largest block, with two lanes per
         // (site, group) when a class has at most 512 of them
@@ -601,9 +633,11 @@ int make_plan(const pt_instance *inst, int32_t n_inst, uint32_t flags, int32_t e
         if (P.oblock_split) most *= 2;
         P.oblock_threads = 64;
         while (P.oblock_threads < most && P.oblock_threads < 1024) P.oblock_threads *= 2;
-        if (P.bp_sblk.size() / 2 > 0x7fffffff || P.bp_eblk.size() / 4 > 0x7fffffff ||
-            P.orec_words > 0x3fffffff)
-            return fail(PT_EINVAL, "batch too large");
+        if (P.orec_words > 0x3fffffff) {
+            if (bp) return fail(PT_EINVAL, "batch too large");
+            P.oct_alt = false;
+        }
+        if (!bp && !P.oct_alt) P.n_otile = P.n_oblock = 0;
     }
     // layout
     size_t o = 0;
@@ -760,14 +794,17 @@ struct pt_ctx {
     bool oct_queue = false, oct_fuse = false;
     // whole octets run as word tiles instead (the tuner's choice, Plan::words_alt)
     bool oct_as_words = false;
+    // byte encoding: octets instead of the byte tiles (the tuner's choice, Plan::oct_alt)
+    bool byte_octets = false;
     int block_threads = 256;
     int tile_bytes = 0;        // target spin bytes per tile in use
     // self-tuning: candidate (tile bytes, threads) shapes timed on the first sweep launches
     bool tuning = false;
     std::vector<std::pair<int, int>> cand;
-    std::vector<char> cand_words;  // oct_as_words of each candidate
+    std::vector<char> cand_alt;    // oct_as_words or byte_octets of each candidate
+    std::vector<size_t> cand_order; // candidates still in the running, in the order they are tried
     std::vector<double> cand_ms;
-    size_t cand_next = 0;
+    size_t cand_next = 0, tune_round = 0;
     hipEvent_t tune_ev[2] = {nullptr, nullptr};
     int lds_fast = 0, lds_words = 0, lds_generic = 0;
     int max_P = 1;
@@ -989,8 +1026,10 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
                            hipMemcpyHostToDevice, c->stream));
     // tiles per instance: a PT cycle's exchange runs in the tile that completes the instance
     c->itiles.assign(P.desc.size(), 0);
-    for (const Tile &t : c->tiles) c->itiles[t.inst] += 1;
-    for (int32_t k = 0; k < P.n_otile && !c->oct_as_words; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
+    const bool octs = P.encoding == PT_BITPACK32 ? !c->oct_as_words : c->byte_octets;
+    if (!c->byte_octets)
+        for (const Tile &t : c->tiles) c->itiles[t.inst] += 1;
+    for (int32_t k = 0; k < P.n_otile && octs; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
     HIP_TRY(hipMemcpyAsync(c->ws + P.o_itiles, c->itiles.data(), c->itiles.size() * 4,
                            hipMemcpyHostToDevice, c->stream));
     HIP_TRY(sweep_kernels_set_lds(c->lds_fast, c->lds_generic, c->lds_block));
@@ -1217,7 +1256,7 @@ hipError_t energies_from_spins(pt_ctx *c, int rep_first, int n)
 // replica's ring.
 bool block_ring_xcd(const pt_ctx *c)
 {
-    return c->block_xcd && c->n_block_tiles > 0 && !c->resident_off &&
+    return c->block_xcd && c->n_block_tiles > 0 && !c->byte_octets && !c->resident_off &&
            !(c->opt.flags & (PT_FLAG_DEVICE_SCOPE_RECORDS | PT_FLAG_BLOCK_LAUNCH_PER_SWEEP));
 }
 
@@ -1349,7 +1388,7 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
 // launch of several PT cycles).
 bool whole_instance_tiles(const pt_ctx *c)
 {
-    if (c->n_words_tiles != 0 || c->n_generic_tiles != 0 || c->n_block_tiles != 0 || c->n_fast_tiles != n_inst_of(c))
+    if (c->byte_octets || c->n_words_tiles != 0 || c->n_generic_tiles != 0 || c->n_block_tiles != 0 || c->n_fast_tiles != n_inst_of(c))
         return false;
     for (int k = 0; k < c->n_fast_tiles; ++k) {
         const Tile &t = c->tiles[k];
@@ -1368,7 +1407,7 @@ bool whole_instance_tiles(const pt_ctx *c)
 // as usual.
 bool latency_path(const pt_ctx *c, int threads)
 {
-    if (!c->lat) return false;
+    if (!c->lat || c->byte_octets) return false;
     bool any = false;
     for (int k = 0; k < c->n_fast_tiles && !any; ++k) {
         const Tile &t = c->tiles[k];
@@ -1508,54 +1547,80 @@ int enqueue_sweep_once(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles =
     }
 }
 
+// Batches of at most this many tiles run a PT cycle as one set of launches, the exchange
+// step in the tile that completes each instance.  Each tile then ends with an agent-scope
+// release (its energies must reach the other XCDs' caches), which costs more than the
+// separate exchange launch it saves once a call has thousands of tiles; small batches are
+// launch-latency bound and gain (measured: 1 tile +22 %, 32 tiles +4 %, 256 tiles -4 %,
+// 7797 tiles -9 %).
+constexpr size_t kFuseMaxTiles = 64;
+
+// Whether a PT cycle's exchange step runs in the sweep launches of the route in use.
+bool can_fuse(const pt_ctx *c)
+{
+    if (c->plan.encoding == PT_BITPACK32 || c->byte_octets) return c->oct_fuse;
+    // word tiles count themselves without a release, whatever their number
+    return c->tiles.size() <= kFuseMaxTiles || c->n_words_tiles == (int)c->tiles.size();
+}
+
 // Self-tuning: while candidates remain, each sweep launch uses the next candidate shape
 // and is timed (synchronously) with its own events.  The candidates are run in
 // kTuneRounds rounds, each keeping its best per-sweep time (one timing of a short call
-// can be off by more than the gap between shapes), and the fastest shape is kept.
+// can be off by more than the gap between shapes), the slower half only in the first two,
+// and the fastest shape is kept.
 // Launch shape does not change the trajectory, so tuning costs only the slower
 // candidates' extra time.
 constexpr size_t kTuneRounds = 3;
-int enqueue_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
+// fused: ask for the exchange step too; set to whether the launches run it (the candidate's
+// route decides).
+int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr)
 {
     if (n_sweeps <= 0) return PT_OK;
     const bool bp = c->plan.encoding == PT_BITPACK32;
-    if (!c->tuning)
-        return bp ? enqueue_bp_sweep(c, n_sweeps, fuse_exchange)
-                  : enqueue_sweep_once(c, n_sweeps, fuse_exchange);
-    const size_t nc = c->cand.size();
-    const size_t k = c->cand_next % nc;
-    const auto shape = c->cand[k];
-    int rc = PT_OK;
-    c->block_threads = shape.second;
-    c->oct_as_words = c->cand_words[k] != 0;
-    if (!bp || c->n_words_tiles > 0 || c->plan.words_alt) {
-        rc = build_tiles(c, c->opt.tile_replicas, shape.first);
-        if (rc) return rc;
-    }
+    auto sweep = [&]() {
+        const bool fuse = fused && can_fuse(c);
+        if (fused) *fused = fuse;
+        return bp || c->byte_octets ? enqueue_bp_sweep(c, n_sweeps, fuse) : enqueue_sweep_once(c, n_sweeps, fuse);
+    };
+    if (!c->tuning) return sweep();
+    auto use = [&](size_t k) -> int {
+        c->block_threads = c->cand[k].second;
+        (bp ? c->oct_as_words : c->byte_octets) = c->cand_alt[k] != 0;
+        if (bp && c->n_words_tiles == 0 && !c->plan.words_alt) return PT_OK;
+        return build_tiles(c, c->opt.tile_replicas, c->cand[k].first);
+    };
+    const size_t k = c->cand_order[c->cand_next];
+    int rc = use(k);
+    if (rc) return rc;
     HIP_TRY(hipEventRecord(c->tune_ev[0], c->stream));
     const int fb = c->fallbacks;
-    rc = bp ? enqueue_bp_sweep(c, n_sweeps, fuse_exchange)
-            : enqueue_sweep_once(c, n_sweeps, fuse_exchange);
+    rc = sweep();
     if (rc) return rc;
     HIP_TRY(hipEventRecord(c->tune_ev[1], c->stream));
     HIP_TRY(hipEventSynchronize(c->tune_ev[1]));
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, c->tune_ev[0], c->tune_ev[1]));
     const double t = (c->fallbacks == fb) ? (double)ms / n_sweeps : 1e30;
-    c->cand_ms[k] = (c->cand_next < nc) ? t : std::min(c->cand_ms[k], t);
-    if (++c->cand_next == kTuneRounds * nc) {
-        size_t best = 0;
-        for (size_t j = 1; j < nc; ++j)
-            if (c->cand_ms[j] < c->cand_ms[best]) best = j;
-        c->tuning = false;
-        c->block_threads = c->cand[best].second;
-        c->oct_as_words = c->cand_words[best] != 0;
-        if (!bp || c->n_words_tiles > 0 || c->plan.words_alt) {
-            rc = build_tiles(c, c->opt.tile_replicas, c->cand[best].first);
-            if (rc) return rc;
-        }
+    c->cand_ms[k] = std::min(c->cand_ms[k], t);
+    if (++c->cand_next < c->cand_order.size()) return PT_OK;
+    c->cand_next = 0;
+    std::stable_sort(c->cand_order.begin(), c->cand_order.end(),
+                     [&](size_t x, size_t y) { return c->cand_ms[x] < c->cand_ms[y]; });
+    if (++c->tune_round < kTuneRounds) {
+        // (a process's first launch of a kernel loads its code, which spoils its first time)
+        if (c->tune_round == 2) c->cand_order.resize((c->cand.size() + 1) / 2);
+        return PT_OK;
     }
-    return PT_OK;
+    c->tuning = false;
+    rc = use(c->cand_order[0]);
+    if (rc == PT_OK && !bp && !c->byte_octets && c->plan.halo_words == 0 && c->shadow) {
+        // no octet blocks after all: nothing to recover from
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        HIP_TRY(hipFree(c->shadow));
+        c->shadow = nullptr;
+        c->journal.clear();
+    }
+    return rc;
 }
 
 int enqueue_exchange(pt_ctx *c, uint32_t t_add)
@@ -1577,14 +1642,6 @@ int enqueue_exchange(pt_ctx *c, uint32_t t_add)
     return PT_OK;
 }
 
-// Batches of at most this many tiles run a PT cycle as one set of launches, the exchange
-// step in the tile that completes each instance.  Each tile then ends with an agent-scope
-// release (its energies must reach the other XCDs' caches), which costs more than the
-// separate exchange launch it saves once a call has thousands of tiles; small batches are
-// launch-latency bound and gain (measured: 1 tile +22 %, 32 tiles +4 %, 256 tiles -4 %,
-// 7797 tiles -9 %).
-constexpr size_t kFuseMaxTiles = 64;
-
 static_assert(kTauLags == PT_TAU_LAGS, "device and ABI correlation lags differ");
 
 // With PT_FLAG_TAU_CORR: after an exchange step, the imaginary-time correlations of
@@ -1605,15 +1662,9 @@ int enqueue_tau_corr(pt_ctx *c)
 int enqueue_cycle(pt_ctx *c)
 {
     const int k = c->opt.sweeps_per_exchange;
-    int rc;
-    // word tiles count themselves without a release, whatever their number
-    const bool all_words = c->n_words_tiles == (int)c->tiles.size();
-    if ((c->plan.encoding == PT_INT8 && (c->tiles.size() <= kFuseMaxTiles || all_words)) || c->oct_fuse) {
-        rc = enqueue_sweep(c, k, true);
-    } else {
-        rc = enqueue_sweep(c, k, false);
-        if (rc == PT_OK) rc = enqueue_exchange(c, (uint32_t)k);
-    }
+    bool fused = false;
+    int rc = enqueue_sweep(c, k, &fused);
+    if (rc == PT_OK && !fused) rc = enqueue_exchange(c, (uint32_t)k);
     if (rc) return rc;
     return enqueue_tau_corr(c);
 }
@@ -1636,7 +1687,7 @@ int pt_workspace_bytes(const pt_instance *inst, int32_t n_inst, const pt_options
 {
     if (!bytes || !opt) return fail(PT_EINVAL, "null argument");
     Plan P;
-    int rc = make_plan(inst, n_inst, opt->flags, opt->encoding, P);
+    int rc = make_plan(inst, n_inst, *opt, P);
     if (rc) return rc;
     *bytes = P.total_bytes;
     return PT_OK;
@@ -1658,7 +1709,7 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
         return fail(PT_EINVAL, "tile_replicas and tile_bytes must be >= 0");
     pt_ctx *c = new (std::nothrow) pt_ctx();
     if (!c) return fail(PT_ENOMEM, "host allocation failed");
-    int rc = make_plan(inst, n_inst, opt->flags, opt->encoding, c->plan);
+    int rc = make_plan(inst, n_inst, *opt, c->plan);
     if (rc) {
         delete c;
         return rc;
@@ -1814,31 +1865,36 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     if (P.encoding == PT_INT8) {
         rc = build_tiles(c, opt->tile_replicas, opt->tile_bytes);
         if (rc) return cleanup(rc);
-    } else {
-        if (P.otile_lds > c->lds_limit || P.oblock_lds > c->lds_limit ||
-            P.oblock_res_lds > c->lds_limit)
+    }
+    bool oct_alt = P.oct_alt;
+    if (P.n_otile > 0 || P.n_oblock > 0) {
+        const bool fits = P.otile_lds <= c->lds_limit && P.oblock_lds <= c->lds_limit &&
+                          P.oblock_res_lds <= c->lds_limit;
+        if (!fits && P.encoding == PT_BITPACK32)
             return cleanup(fail(PT_EINVAL, "octet work needs more LDS than the device has"));
-        e = oct_kernels_set_lds(P.otile_lds, P.oblock_lds, P.oblock_res_lds);
+        oct_alt = oct_alt && fits;
+        e = fits ? oct_kernels_set_lds(P.otile_lds, P.oblock_lds, P.oblock_res_lds) : hipSuccess;
         if (e != hipSuccess) return cleanup(hip_fail(e, "octet kernel LDS attribute"));
-        // whole octets in list order (or from the device work queues), and the exchange step
-        // in the octet that completes an instance when every instance is in whole octets
-        c->oct_queue = P.n_otile > 0 && (opt->flags & PT_FLAG_WORK_QUEUE);
-        c->oct_fuse = P.n_oblock == 0 && !P.bp_generic;
-        c->block_threads = opt->block_threads > 0 ? opt->block_threads : 256;
-        rc = build_tiles(c, opt->tile_replicas, opt->tile_bytes);
-        if (rc) return cleanup(rc);
         // octet slice blocks run resident (one launch per call) when every block fits the
         // compute units at once: blocks wait for their neighbours, which must all have started
-        if (P.n_oblock > 0 && !(opt->flags & PT_FLAG_BLOCK_LAUNCH_PER_SWEEP)) {
+        if (fits && P.n_oblock > 0 && !(opt->flags & PT_FLAG_BLOCK_LAUNCH_PER_SWEEP)) {
             int32_t per_cu = 0;
             e = oct_resident_per_cu(P.oblock_threads, P.oblock_res_lds, &per_cu);
             if (e != hipSuccess) return cleanup(hip_fail(e, "octet occupancy query"));
             c->oct_resident = (int64_t)P.n_oblock <= (int64_t)per_cu * c->cus;
+            oct_alt = oct_alt && c->oct_resident;
         }
     }
     if (P.encoding == PT_BITPACK32) {
+        // whole octets in list order (or from the device work queues)
+        c->oct_queue = P.n_otile > 0 && (opt->flags & PT_FLAG_WORK_QUEUE);
         c->block_threads = opt->block_threads > 0 ? opt->block_threads : 256;
+        rc = build_tiles(c, opt->tile_replicas, opt->tile_bytes);
+        if (rc) return cleanup(rc);
     }
+    // the exchange step in the octet (or word tile) that completes an instance, when every
+    // instance is in those
+    c->oct_fuse = P.n_oblock == 0 && !P.bp_generic;
     int32_t most_R = 2;
     for (const auto &d : P.desc) most_R = std::max(most_R, d.R);
     e = hipHostMalloc((void **)&c->obs_pin, (size_t)ObsLayout(most_R).bytes, hipHostMallocDefault);
@@ -1858,7 +1914,13 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
         } else {
             for (int th : {256, 512, 1024}) c->cand.emplace_back(opt->tile_bytes, th);
         }
-        c->cand_words.assign(c->cand.size(), 0);
+        c->cand_alt.assign(c->cand.size(), 0);
+        if (tune_int8 && oct_alt)
+            for (int th : {512, 1024}) {
+                if (P.n_otile == 0 && th < 1024) continue;  // slice blocks have a size of their own
+                c->cand.emplace_back(0, th);
+                c->cand_alt.push_back(1);
+            }
         // Few octets leave most compute units idle, and a word tile can be as small as one
         // replica: try both.  40 octets of 336 x 64 spins take 255 us a cycle as octets and
         // 109 us as 320 word tiles; with an octet for every unit the octets' shared adder
@@ -1866,9 +1928,10 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
         if (tune_bp && P.words_alt)
             for (int th : {512, 1024}) {
                 c->cand.emplace_back(opt->tile_bytes, th);
-                c->cand_words.push_back(1);
+                c->cand_alt.push_back(1);
             }
-        c->cand_ms.assign(c->cand.size(), 0.0);
+        c->cand_ms.assign(c->cand.size(), 1e30);
+        for (size_t k = 0; k < c->cand.size(); ++k) c->cand_order.push_back(k);
         c->tuning = true;
         for (auto &ev : c->tune_ev) {
             e = hipEventCreate(&ev);
@@ -1897,7 +1960,7 @@ int pt_sweep(pt_ctx *c, int32_t n_sweeps)
     if (n_sweeps < 0) return fail(PT_EINVAL, "n_sweeps < 0");
     if (n_sweeps == 0) return PT_OK;
     journal_add(c, 0, n_sweeps);
-    int rc = enqueue_sweep(c, n_sweeps, false);
+    int rc = enqueue_sweep(c, n_sweeps);
     if (rc) return rc;
     hipError_t e = launch_advance(c->st, n_inst_of(c), (uint32_t)n_sweeps, c->stream);
     if (e != hipSuccess) return hip_fail(e, "advance launch");
@@ -2209,7 +2272,7 @@ int pt_checkpoint_validate(const pt_instance *inst, int32_t n_inst, const pt_opt
 {
     if (!opt) return fail(PT_EINVAL, "null options");
     Plan P;
-    int rc = make_plan(inst, n_inst, opt->flags, opt->encoding, P);
+    int rc = make_plan(inst, n_inst, *opt, P);
     if (rc) return rc;
     if (need) *need = sizeof(CkptHeader) + P.state_bytes;
     if (!buf) return PT_OK;
@@ -2237,16 +2300,17 @@ int pt_get_info(pt_ctx *c, pt_info *o)
     o->exchange_ms = c->exch_ms;
     o->exchange_launches = c->exch_n;
     o->sweep_groups = (int32_t)launch_groups(c).size();
-    o->block_tiles = c->n_block_tiles;
-    o->block_resident = c->block_persistent;
+    o->block_tiles = c->byte_octets ? 0 : c->n_block_tiles;
+    o->block_resident = c->byte_octets ? 0 : c->block_persistent;
     o->class_launches = 0;
-    o->oct_tiles = c->oct_as_words ? 0 : c->plan.n_otile;
-    o->oct_blocks = c->plan.n_oblock;
+    const bool octs = c->plan.encoding == PT_BITPACK32 ? !c->oct_as_words : c->byte_octets;
+    o->oct_tiles = octs ? c->plan.n_otile : 0;
+    o->oct_blocks = octs ? c->plan.n_oblock : 0;
     o->oct_tile_launches = o->oct_tiles > 0 ? 1 : 0;
-    o->oct_resident = c->oct_resident ? 1 : 0;
+    o->oct_resident = octs && c->oct_resident ? 1 : 0;
     o->oct_queue = c->oct_queue ? 1 : 0;
     o->oct_fused = c->oct_fuse && o->oct_tiles > 0 ? 1 : 0;
-    o->oct_ring_xcd = oct_ring_xcd(c) ? 1 : 0;
+    o->oct_ring_xcd = octs && oct_ring_xcd(c) ? 1 : 0;
     o->block_ring_xcd = block_ring_xcd(c) ? 1 : 0;
     o->recoveries = c->recoveries;
     o->last_device_error = c->last_device_error;

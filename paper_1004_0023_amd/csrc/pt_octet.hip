@@ -1,4 +1,5 @@
-// pt_octet.hip -- octet kernels of the bit-packed spin encoding (PT_BITPACK32).
+// pt_octet.hip -- octet kernels: eight replica slots to a word (both encodings; the packed one
+// first).
 //
 // In device memory a 32-bit word holds one spin of 32 replica slots (bit c mod 32 of word
 // group c / 32).  These kernels work on octets: byte o of every word of word group w, the
@@ -7,6 +8,9 @@
 // those bytes back, so the workgroups of the four octets of a word never write the same
 // byte.  The chain is the one every encoding runs: the same colour classes, Philox words
 // and thresholds.
+//
+// In the byte encoding an octet's slots are eight replicas of bytes; the LDS word gathers a
+// word of each with a shift, and the write-back spreads it again.
 //
 // The local field is bit-sliced.  For instances whose couplings are all +-1 and fields
 // in {-1, 0, 1}, with degrees up to D <= 8, a site's Metropolis move depends on
@@ -412,19 +416,52 @@ __device__ __forceinline__ uint32_t *oct_row(const DevState &st, const InstDesc 
            ((int64_t)(w * d.parities + p) * d.N + i) * d.bp_row;
 }
 
-// The octet's byte of the four words of group g in a row.
-__device__ __forceinline__ uint32_t oct_load(const uint32_t *row, int g, uint32_t sel)
-{
-    return octet_of(*reinterpret_cast<const uint4 *>(row + 4 * g), sel);
-}
-__device__ __forceinline__ void oct_store(uint32_t *row, int g, int o, uint32_t v)
-{
-    uint8_t *p = reinterpret_cast<uint8_t *>(row + 4 * g) + o;
-    p[0] = (uint8_t)v;
-    p[4] = (uint8_t)(v >> 8);
-    p[8] = (uint8_t)(v >> 16);
-    p[12] = (uint8_t)(v >> 24);
-}
+// The octet's spins of four-slice group g of (parity p, site i) in device memory.  Packed: one
+// byte of each of the four words of the group.  Byte encoding (no packed rows): one word of
+// each of the octet's replicas, whose rows are the octet's LDS rows with a replica per bit.
+struct OctSpins {
+    const DevState &st;
+    const InstDesc &d;
+    int w, oct, c0, nslots;
+    uint32_t sel;
+    __device__ __forceinline__ OctSpins(const DevState &st_, const InstDesc &d_, int w_, int oct_, int c0_, int nslots_)
+        : st(st_), d(d_), w(w_), oct(oct_), c0(c0_), nslots(nslots_),
+          sel(((uint32_t)(4 + oct_) << 8) | (uint32_t)oct_ | 0x0C0C0000u)
+    {
+    }
+    __device__ __forceinline__ uint32_t *replica(int r) const
+    {
+        return reinterpret_cast<uint32_t *>(st.spins + d.spin_base + (int64_t)(c0 + r) * d.rep_bytes);
+    }
+    __device__ __forceinline__ uint32_t load(int p, int i, int g) const
+    {
+        if (d.bp_row != 0)
+            return octet_of(*reinterpret_cast<const uint4 *>(oct_row(st, d, w, p, i) + 4 * g), sel);
+        const int k = (p * d.N + i) * d.G4 + g;
+        uint32_t v = 0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const uint32_t y = replica(min(r, nslots - 1))[k];
+            v |= (r < nslots ? y : 0u) << r;
+        }
+        return v;
+    }
+    __device__ __forceinline__ void store(int p, int i, int g, uint32_t v) const
+    {
+        if (d.bp_row != 0) {
+            uint8_t *b = reinterpret_cast<uint8_t *>(oct_row(st, d, w, p, i) + 4 * g) + oct;
+            b[0] = (uint8_t)v;
+            b[4] = (uint8_t)(v >> 8);
+            b[8] = (uint8_t)(v >> 16);
+            b[12] = (uint8_t)(v >> 24);
+            return;
+        }
+        const int k = (p * d.N + i) * d.G4 + g;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (r < nslots) replica(r)[k] = (v >> r) & 0x01010101u;
+    }
+};
 
 // The degree switch and the slots-per-lane choice around a work item's body.
 template <class Body>
@@ -612,14 +649,14 @@ __device__ __forceinline__ void oct_tile_item(const OctLaunch &L, char *lds, int
     const int N = d.N, G4 = d.G4, lgG4 = 31 - __clz(G4);
     const int c0 = 32 * w + 8 * oct;
     const int nslots = min(8, d.R - c0);
-    const uint32_t sel = ((uint32_t)(4 + oct) << 8) | (uint32_t)oct | 0x0C0C0000u;
+    const OctSpins sp(st, d, w, oct, c0, nslots);
     // the octet's bytes of both parities: LDS word [p][i][g]
     const int words = 2 * (N << lgG4);
     batched(words,
             [&](int k) {
                 const int g = k & (G4 - 1), pi = k >> lgG4;
                 const int p = pi >= N ? 1 : 0, i = pi - p * N;
-                return oct_load(oct_row(st, d, w, p, i), g, sel);
+                return sp.load(p, i, g);
             },
             [&](int k, uint32_t v) { st32(4u * (uint32_t)k, v); });
     oct_stage_common(st, d, lds, o, c0, nslots);
@@ -665,7 +702,7 @@ __device__ __forceinline__ void oct_tile_item(const OctLaunch &L, char *lds, int
     for (int k = tid; k < words; k += nt) {
         const int g = k & (G4 - 1), pi = k >> lgG4;
         const int p = pi >= N ? 1 : 0, i = pi - p * N;
-        oct_store(oct_row(st, d, w, p, i), g, oct, ld32(4u * (uint32_t)k));
+        sp.store(p, i, g, ld32(4u * (uint32_t)k));
     }
     if (!L.fuse) return;
     // every wave's E_cl, C stores complete before the count (a barrier does not wait for
@@ -858,14 +895,13 @@ __device__ __forceinline__ void oct_block_energy_out(const DevState &st, const I
 
 // ng1 consecutive groups of parity p from group gb on (cyclically) into LDS rows of ng1
 // words at base, x-major so that neighbouring threads read neighbouring rows.
-__device__ __forceinline__ void oct_stage_rows(const DevState &st, const InstDesc &d, int w, int p,
-                                               int gb, int ng1, uint32_t base, uint32_t sel)
+__device__ __forceinline__ void oct_stage_rows(const OctSpins &sp, int p, int gb, int ng1, uint32_t base)
 {
-    const int N = d.N, G4 = d.G4;
+    const int N = sp.d.N, G4 = sp.d.G4;
     batched(N * ng1,
             [&](int k) {
                 const int x = k / N, i = k - x * N;
-                return oct_load(oct_row(st, d, w, p, i), (gb + x + G4) & (G4 - 1), sel);
+                return sp.load(p, i, (gb + x + G4) & (G4 - 1));
             },
             [&](int k, uint32_t v) {
                 const int x = k / N, i = k - x * N;
@@ -889,16 +925,16 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     const int N = d.N, p = L.p, lgng = 31 - __clz(ng);
     const int c0 = 32 * w + 8 * oct;
     const int nslots = min(8, d.R - c0);
-    const uint32_t sel = ((uint32_t)(4 + oct) << 8) | (uint32_t)oct | 0x0C0C0000u;
+    const OctSpins sp(st, d, w, oct, c0, nslots);
     // own: parity p, groups g0 .. g0 + ng - 1; oth: parity 1 - p, ng + 1 groups from g0 - 1
     // (p = 0) or g0 (p = 1)
     batched(N << lgng,
             [&](int k) {
                 const int gl = k & (ng - 1), i = k >> lgng;
-                return oct_load(oct_row(st, d, w, p, i), g0 + gl, sel);
+                return sp.load(p, i, g0 + gl);
             },
             [&](int k, uint32_t v) { st32(o.sp + 4u * (uint32_t)k, v); });
-    oct_stage_rows(st, d, w, p ^ 1, p == 0 ? g0 - 1 : g0, ng + 1, o.oth, sel);
+    oct_stage_rows(sp, p ^ 1, p == 0 ? g0 - 1 : g0, ng + 1, o.oth);
     oct_stage_common(st, d, lds, o, c0, nslots);
     const uint32_t tt = (uint32_t)(st.ctr[n].t + (uint64_t)L.sweep_off);
     __syncthreads();
@@ -920,7 +956,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     if (energy) oct_block_energy_out(st, d, lds, o, c0, nslots);
     for (int k = tid; k < (N << lgng); k += nt) {
         const int gl = k & (ng - 1), i = k >> lgng;
-        oct_store(oct_row(st, d, w, p, i), g0 + gl, oct, ld32(o.sp + 4u * (uint32_t)k));
+        sp.store(p, i, g0 + gl, ld32(o.sp + 4u * (uint32_t)k));
     }
 }
 
@@ -1026,10 +1062,10 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
     const int N = d.N, lgng = 31 - __clz(ng);
     const int c0 = 32 * w + 8 * oct;
     const int nslots = min(8, d.R - c0);
-    const uint32_t sel = ((uint32_t)(4 + oct) << 8) | (uint32_t)oct | 0x0C0C0000u;
+    const OctSpins sp(st, d, w, oct, c0, nslots);
     const uint32_t RS = 4u * (uint32_t)(ng + 1), P0 = o.sp, P1 = o.oth;
-    oct_stage_rows(st, d, w, 0, g0, ng + 1, P0, sel);
-    oct_stage_rows(st, d, w, 1, g0 - 1, ng + 1, P1, sel);
+    oct_stage_rows(sp, 0, g0, ng + 1, P0);
+    oct_stage_rows(sp, 1, g0 - 1, ng + 1, P1);
     oct_stage_common(st, d, lds, o, c0, nslots);
     const uint64_t t0 = st.ctr[n].t;
     __syncthreads();
@@ -1079,8 +1115,8 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
     oct_block_energy_out(st, d, lds, o, c0, nslots);
     for (int k = tid; k < (N << lgng); k += nt) {
         const int x = k & (ng - 1), i = k >> lgng;
-        oct_store(oct_row(st, d, w, 0, i), g0 + x, oct, ld32(P0 + (uint32_t)i * RS + 4u * (uint32_t)x));
-        oct_store(oct_row(st, d, w, 1, i), g0 + x, oct, ld32(P1 + (uint32_t)i * RS + 4u * (uint32_t)(x + 1)));
+        sp.store(0, i, g0 + x, ld32(P0 + (uint32_t)i * RS + 4u * (uint32_t)x));
+        sp.store(1, i, g0 + x, ld32(P1 + (uint32_t)i * RS + 4u * (uint32_t)(x + 1)));
     }
     if (L.xcd_local) xcd_check(st, st.xseen, (int)blockIdx.x, kErrPlace, L.xcd_local == 2);
 }

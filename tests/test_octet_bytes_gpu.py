@@ -1,0 +1,72 @@
+"""Byte-encoded batches swept as octets (the tuner's alternative to the byte tiles) against the
+oracle: every degree, with and without fields, part octets, whole octets and slice blocks, with
+graph replays and eager calls, spins set and checkpointed between them."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from paper_1004_0023_amd import ptqmc
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("E_cl", "C", "rung_of", "replica_of", "acc", "att", "roundtrips", "label", "sumE", "sumC",
+        "sumE2", "sumC2", "nup", "ndown")
+
+
+def check(s, n, ref):
+    got, want = s.observables(n), ref.observables()
+    for key in KEYS:
+        assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), f"instance {n}: {key}"
+    assert np.array_equal(s.spins(n), ref.s), f"instance {n}: spins"
+
+
+def open_lattice(rng, lx, ly, lz, m, r):
+    at = lambda x, y, z: x + lx * (y + ly * z)
+    edges = np.array([(at(x, y, z), at(x + dx, y + dy, z + dz)) for z in range(lz) for y in range(ly)
+                      for x in range(lx) for dx, dy, dz in ((1, 0, 0), (0, 1, 0), (0, 0, 1))
+                      if x + dx < lx and y + dy < ly and z + dz < lz], np.int32)
+    n = lx * ly * lz
+    return W.make_instance(n, edges, rng.choice(np.array([-1, 1], np.int8), size=len(edges)),
+                           rng.integers(-1, 2, size=n).astype(np.int8), m,
+                           W.geometric_temperatures(0.3, 3.0, r), 1.0)
+
+
+def whole():
+    """More octets than half the compute units: many small ones, and a few of each degree."""
+    rng = np.random.default_rng([1004, 44])
+    mk = lambda *a, **k: W.random_small_instance(rng, *a, **k)
+    return ([mk(10, 8, 17, d=d) for d in range(1, 9)] + [mk(24, 16, 31, d=3) for _ in range(30)] +
+            [mk(16, 64, 9, d=4, hmax=0) for _ in range(8)] + [open_lattice(rng, 3, 4, 4, 32, 12)])
+
+
+def blocks():
+    """An octet too large for a workgroup's share of LDS, beside whole ones."""
+    rng = np.random.default_rng([1004, 45])
+    return [open_lattice(rng, 8, 8, 9, 256, 10), W.random_small_instance(rng, 20, 16, 5, d=3)]
+
+
+@pytest.mark.parametrize("batch,k,cycles", [(whole, 2, 60), (blocks, 1, 60)])
+def test_tuned_byte_batches(batch, k, cycles):
+    """Long enough that tuning ends (every candidate runs on the way) and graphs replay."""
+    print(f"case: byte octets, {batch.__name__}", flush=True)
+    insts = batch()
+    refs = [oracle.OracleChain(i, 12, index=n) for n, i in enumerate(insts)]
+    with ptqmc.Sampler(insts, 12, sweeps_per_exchange=k) as s:
+        for _ in range(2):
+            s.run(cycles)
+            s.sweep(1)
+            for n, ref in enumerate(refs):
+                ref.run(k, cycles)
+                ref.sweep(1)
+                if n < 8 or n == len(refs) - 1:
+                    check(s, n, ref)
+        assert s.info()["tuned"]
+        blob = s.save()
+        s.run(3)
+        s.load(blob)
+        s.run(17)
+        for n, ref in enumerate(refs):
+            ref.run(k, 17)
+            if n < 8 or n == len(refs) - 1:
+                check(s, n, ref)
