@@ -497,11 +497,13 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     // Byte batches that could run as octets may: a cycle of 192 (512) instances of the uneven
     // batch takes 1182 (2998) us as byte tiles and 936 (2280) as octets.  Batches of fewer
     // octets than half the compute units are not offered the choice (at 136 octets the byte
-    // tiles, several to an octet, fill the chip better: 210 us), and the tuner makes it.
+    // tiles, several to an octet, fill the chip better: 210 us), and the tuner makes it; nor
+    // are batches with byte slice blocks, which are as fast (one lattice of 1024 x 256 spins:
+    // 178 us and 181) or faster (two: 530 and 711).
     bool any_block = false;
     for (const auto &d : P.desc)
         any_block = any_block || (d.oct && oct_lds_bytes(d, d.G4, kOctTile) > kLdsPerWorkgroup / 2);
-    P.oct_alt = P.oct_alt && (any_block || octets >= kMostCus / 2);
+    P.oct_alt = P.oct_alt && P.halo_words == 0 && (any_block || octets >= kMostCus / 2);
     if (bp || P.oct_alt) {
         // octet work: whole octets where one takes at most half a compute unit's LDS
         // (largest first), else slice blocks of ng groups, ng about 512 colour-class items

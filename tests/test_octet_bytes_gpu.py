@@ -46,7 +46,13 @@ def blocks():
     return [open_lattice(rng, 8, 8, 9, 256, 10), W.random_small_instance(rng, 20, 16, 5, d=3)]
 
 
-@pytest.mark.parametrize("batch,k,cycles", [(whole, 2, 60), (blocks, 1, 60)])
+def blocks_of_tiles():
+    """As blocks, but a byte replica fits a workgroup's LDS."""
+    rng = np.random.default_rng([1004, 46])
+    return [open_lattice(rng, 8, 8, 6, 256, 10), W.random_small_instance(rng, 20, 16, 5, d=3)]
+
+
+@pytest.mark.parametrize("batch,k,cycles", [(whole, 2, 60), (blocks, 1, 60), (blocks_of_tiles, 1, 60)])
 def test_tuned_byte_batches(batch, k, cycles):
     """Long enough that tuning ends (every candidate runs on the way) and graphs replay."""
     print(f"case: byte octets, {batch.__name__}", flush=True)
