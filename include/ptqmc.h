@@ -46,12 +46,12 @@
  * thread-local message for the last failure on the calling thread.  A context is used
  * by one host thread at a time.  All calls that launch work are asynchronous on the
  * context's stream; pt_observables, pt_get_spins, pt_save and pt_sync synchronise it.
- * A slice-block launch with resident blocks bounds its waits for neighbouring blocks so
- * that every launch ends; if one gave up since the last of those four calls, the next of
+ * A launch whose workgroups wait for each other (resident slice blocks, several cycles of
+ * instances in several tiles) bounds its waits so that every launch ends; if one gave up since the last of those four calls, the next of
  * them restores the state of the last clean synchronisation (a device copy the context
- * keeps when resident launches are possible), replays the calls since with slice blocks
- * launched per sweep (or per parity), and then runs them that way for the rest of the
- * context (pt_info.recoveries counts this).  PT_ESTATE is returned only if that replay
+ * keeps when such launches are possible), replays the calls since with slice blocks
+ * launched per sweep (or per parity) and a launch per cycle, and then runs them that way for
+ * the rest of the context (pt_info.recoveries counts this).  PT_ESTATE is returned only if that replay
  * fails too.
  */
 #ifndef PTQMC_H
@@ -138,9 +138,9 @@ extern "C" {
                                           share an XCD report the launch's XCDs as
                                           mismatched, so the next synchronising call
                                           recovers (pt_info.recoveries)                */
-#define PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT 0x40u /* test hook: resident slice blocks wait for a
-                                          progress count that never comes, under a tiny
-                                          poll bound, so every wait gives up; the next
+#define PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT 0x40u /* test hook: resident slice blocks (and tiles
+                                          of several cycles a launch) wait for a count
+                                          that never comes, under a tiny poll bound, so every wait gives up; the next
                                           synchronising call recovers (pt_info.recoveries)
                                           */
 
@@ -217,7 +217,7 @@ typedef struct {
     int32_t class_launches;           /* PT_BITPACK32: sweep launches per sweep (one per
                                          colour class); 0 under PT_INT8                 */
     int64_t multi_launches;           /* pt_run launches that ran several PT cycles each
-                                         (batches whose instances each fit one tile)    */
+                                         (see pt_run)                                   */
     int64_t multi_cycles;             /* PT cycles those launches ran                  */
     double multi_ms;                  /* their summed event time under PT_FLAG_TIMING
                                          (not part of sweep_ms / exchange_ms)           */
@@ -251,7 +251,7 @@ typedef struct {
                                          launch's wait given up, restored the state of
                                          the last clean synchronisation and replayed
                                          the calls since with slice blocks launched per
-                                         sweep (resident launches stay off after one)   */
+                                         sweep and cycles one by one (resident launches stay off after one)   */
     int32_t lane_words;               /* PT_INT8 whole-replica tiles: four-slice words per
                                          lane (2, or 1 for batches too small to give
                                          every SIMD one wave per colour class; always 2
@@ -295,12 +295,14 @@ int pt_exchange(pt_ctx *ctx);
 
 /* n_cycles x (sweeps_per_exchange sweeps, then one exchange step), the same chain as
  * pt_sweep(k) + pt_exchange() per cycle (Figure 6's loop).  Cycles are replayed from a HIP
- * graph; for batches of at most 64 tiles each cycle is a single set of launches in which
- * the workgroup that finishes an instance's last tile runs that instance's exchange step
- * (per-instance completion counts), larger batches launch the exchange separately.  When
- * every instance fits one tile (and neither PT_FLAG_TAU_CORR nor PT_FLAG_NO_GRAPH is set)
- * up to 1024 cycles run in one launch instead, each workgroup doing its instance's exchange
- * steps itself; pt_info counts these launches (multi_launches, multi_cycles) and, with
+ * graph; for batches of at most 64 tiles (of word tiles, any number) each cycle is a single
+ * set of launches in which the workgroup that finishes an instance's last tile runs that
+ * instance's exchange step (per-instance completion counts), other batches launch the exchange
+ * separately.  When every instance fits one tile (and neither PT_FLAG_TAU_CORR nor
+ * PT_FLAG_NO_GRAPH is set) up to 1024 cycles run in one launch instead, each workgroup doing
+ * its instance's exchange steps itself.  So do batches whose tiles, all word tiles or byte
+ * tiles on the latency path, fit the device at once (without PT_FLAG_TIMING): an instance's
+ * tiles then wait for its exchange step between cycles.  pt_info counts these launches (multi_launches, multi_cycles) and, with
  * PT_FLAG_TIMING, times them apart from the sweep and exchange launches (multi_ms).  With
  * PT_FLAG_NO_GRAPH every cycle is launched eagerly.  The chain is the same in every case. */
 int pt_run(pt_ctx *ctx, int32_t n_cycles);

@@ -287,6 +287,8 @@ struct DevState {
     // per instance: tiles of one sweep call, and tiles that finished the current call
     const int32_t *itiles;
     uint32_t *icount;
+    // per instance: cycles whose exchange step is done in the current launch of several cycles
+    uint32_t *icycle;
     // resident slice blocks: sweeps each block has published in the current call (one per
     // block tile), and a sticky error word (nonzero: a wait gave up)
     int32_t *prog;

@@ -92,7 +92,8 @@ __device__ __forceinline__ void exchange_wave(const DevState &st, const InstDesc
     sC2 += Cc * Cc;
     if (in) {
         st.replica_of[base + t] = nrep;
-        st.rung_of[base + nrep] = t;
+        // read within a launch of several cycles by tiles on other XCDs
+        __hip_atomic_store(&st.rung_of[base + nrep], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         st.label[base + t] = nlab;
         if (trip) st.rt[base + t] += 1;
         st.nup[base + t] = nup;
@@ -156,8 +157,8 @@ __device__ __forceinline__ void exchange_instance(const DevState &st, int n, uin
         if (u <= thr) {
             st.replica_of[base + r] = y;
             st.replica_of[base + r + 1] = x;
-            st.rung_of[base + y] = r;
-            st.rung_of[base + x] = r + 1;
+            __hip_atomic_store(&st.rung_of[base + y], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st.rung_of[base + x], r + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             st.acc[pb + r] += 1;
         }
     }
@@ -192,6 +193,72 @@ __device__ __forceinline__ void exchange_instance(const DevState &st, int n, uin
         st.ctr[n].n_acc += 1;
         st.ctr[n].t += t_add;
     }
+}
+
+// ------------------------------------------------------------------ several cycles per launch
+//
+// When every tile of a launch is resident at once, the launch runs many PT cycles: the tiles
+// of an instance count themselves as their energies are stored, its first tile waits for the
+// count, runs the exchange step and publishes the cycle, and the others wait for that.  What
+// passes between tiles (E_cl, C, rungs, the counts) is stored and read coherently; the rest of
+// the exchange state is the first tile's own.  A cycle then costs these waits instead of a
+// launch with its staging, its write-back and its cold code (figures at the kernels).
+//
+// Waits are bounded, so that every wave exits: a tile that gives up sets the error word and
+// carries on, and once any has, the others stop waiting too (the host then restores the state
+// of the last clean synchronisation and replays the calls since with a launch per cycle).
+
+constexpr int kCoopPolls = 1 << 18;
+
+// Thread 0 polls *p until it reaches need while the workgroup waits at a barrier.
+__device__ __forceinline__ void coop_wait(const DevState &st, const uint32_t *p, uint32_t need, int max_polls,
+                                          uint32_t err)
+{
+    if (threadIdx.x == 0) {
+        int polls = 0;
+        while (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+            if (++polls > max_polls || __hip_atomic_load(st.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                atomicOr(st.err, err);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+    }
+    __syncthreads();
+}
+
+// The end of cycle cyc (of `cycles`) in a tile of instance n whose E_cl and C stores are under
+// way; `first`: the instance's first tile.  After it (but for the last cycle) the instance's
+// new rungs may be read with coherent_rung.  The counts are 0 again after the last cycle: by
+// then every tile has counted itself, so none waits any more.
+__device__ __forceinline__ void coop_cycle(const DevState &st, int n, bool first, int cyc, int cycles, uint32_t key0,
+                                           uint32_t key1, uint32_t t_add, int polls, uint32_t extra, uint32_t err)
+{
+    const bool last = cyc + 1 >= cycles;
+    if (polls <= 0) polls = kCoopPolls;
+    // every wave's stores complete (a barrier does not wait for them) before the tile counts
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vector-memory count 0, no other
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_fetch_add(&st.icount[n], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (first) {
+        coop_wait(st, &st.icount[n], (uint32_t)st.itiles[n] * (uint32_t)(cyc + 1) + extra, polls, err);
+        exchange_instance<true>(st, n, key0, key1, t_add);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (last) __hip_atomic_store(&st.icount[n], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st.icycle[n], last ? 0u : (uint32_t)(cyc + 1), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+    } else if (!last) {
+        coop_wait(st, &st.icycle[n], (uint32_t)(cyc + 1) + extra, polls, err);
+    }
+}
+
+__device__ __forceinline__ int coherent_rung(const DevState &st, int slot)
+{
+    return __hip_atomic_load(&st.rung_of[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace ptq

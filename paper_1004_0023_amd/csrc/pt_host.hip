@@ -94,7 +94,7 @@ struct Plan {
     uint64_t flips_per_sweep = 0;
     // byte offsets in the workspace
     size_t o_inst, o_adj, o_off, o_h, o_ent, o_bias, o_csite, o_cls, o_tbl, o_db, o_dK, o_tiles,
-        o_repinst, o_halo, o_itiles, o_icount, o_prog, o_err, o_bp_sblk, o_bp_eblk, o_bp_wg,
+        o_repinst, o_halo, o_itiles, o_icount, o_icycle, o_prog, o_err, o_bp_sblk, o_bp_eblk, o_bp_wg,
         o_bp_part, o_oent, o_ohinfo, o_otbl, o_otiles, o_orec, o_oprog, o_oqueue, o_oqitems,
         o_xseen;
     size_t o_state;  // start of the mutable region
@@ -664,6 +664,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     P.o_halo = take((size_t)P.halo_words * 2 * 4);
     P.o_itiles = take((size_t)n_inst * 4);
     P.o_icount = take((size_t)n_inst * 4);  // zero in the uploaded image
+    P.o_icycle = take((size_t)n_inst * 4);  // zero in the uploaded image
     P.o_prog = take((size_t)P.max_tiles * 4);
     P.o_err = take(4);                       // zero in the uploaded image
     P.o_bp_sblk = take(P.bp_sblk.size() * 4);
@@ -798,12 +799,18 @@ struct pt_ctx {
     bool oct_as_words = false;
     // byte encoding: octets instead of the byte tiles (the tuner's choice, Plan::oct_alt)
     bool byte_octets = false;
+    int coop_fits = -1;        // can_coop's answer for the tiles and block size in use (-1: not asked)
     int block_threads = 256;
     int tile_bytes = 0;        // target spin bytes per tile in use
     // self-tuning: candidate (tile bytes, threads) shapes timed on the first sweep launches
     bool tuning = false;
-    std::vector<std::pair<int, int>> cand;
-    std::vector<char> cand_alt;    // oct_as_words or byte_octets of each candidate
+    struct Shape {
+        int tile_bytes, threads;
+        bool alt;            // oct_as_words or byte_octets
+        int replicas;        // per tile; 0: from the tile bytes
+        uint64_t tiles = 0;  // hash of the tile list, once built
+    };
+    std::vector<Shape> cand;
     std::vector<size_t> cand_order; // candidates still in the running, in the order they are tried
     std::vector<double> cand_ms;
     size_t cand_next = 0, tune_round = 0;
@@ -852,6 +859,7 @@ int n_inst_of(const pt_ctx *c) { return (int)c->plan.desc.size(); }
 int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
 {
     const Plan &P = c->plan;
+    c->coop_fits = -1;
     // the tile list is uploaded from c->tiles: let any earlier upload finish first
     HIP_TRY(hipStreamSynchronize(c->stream));
     int64_t total_bytes = 0;
@@ -1538,6 +1546,7 @@ int enqueue_sweep_once(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles =
             if (rc) return rc;
         } else if (c->block_threads > 64) {
             c->block_threads /= 2;
+            c->coop_fits = -1;
             if (c->n_words_tiles > 0) {  // a word tile needs a thread per lane of a site
                 const int rc = build_tiles(c, 1, 0);
                 if (rc) return rc;
@@ -1565,17 +1574,108 @@ bool can_fuse(const pt_ctx *c)
     return c->tiles.size() <= kFuseMaxTiles || c->n_words_tiles == (int)c->tiles.size();
 }
 
+// Whether pt_run may run several cycles per launch of tiles that wait for each other between
+// cycles: every tile a word tile or, at most one per unit and on the latency path, a fast byte
+// tile; a launch per kind, each resident as a whole (hence no octets, no generic tiles).  Not
+// under PT_FLAG_TIMING, which times sweeps.
+bool can_coop(pt_ctx *c)
+{
+    if (!c->shadow || c->resident_off || c->byte_octets || c->inject_pending || c->tiles.empty() ||
+        (c->opt.flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)))
+        return false;
+    if (c->plan.encoding == PT_BITPACK32 && (!c->oct_fuse || (c->plan.n_otile > 0 && !c->oct_as_words)))
+        return false;
+    if ((int)c->tiles.size() != c->n_words_tiles + c->n_fast_tiles) return false;
+    if (c->coop_fits < 0) {
+        c->coop_fits = 1;
+        for (int kind : {kTileFast, kTileWords, kTileWordsR}) {
+            int64_t n = 0;
+            int lds = 0;
+            for (size_t k = 0; k < c->tiles.size(); ++k)
+                if (c->tiles[k].kind == kind) {
+                    ++n;
+                    lds = std::max(lds, c->tile_lds[k]);
+                }
+            if (n == 0) continue;
+            int32_t per_cu = 0;
+            const hipError_t e = kind == kTileFast
+                                     ? fast_resident_per_cu(c->block_threads, lds, &per_cu)
+                                     : words_resident_per_cu(kind == kTileWordsR, c->block_threads, lds, &per_cu);
+            if (e != hipSuccess) (void)hipGetLastError();
+            if (e != hipSuccess || n > (int64_t)per_cu * c->cus || (kind == kTileFast && !latency_path(c, c->block_threads)))
+                c->coop_fits = 0;
+        }
+    }
+    return c->coop_fits > 0;
+}
+
+// Whether launches of the shape in use may wait for other workgroups (and so may give up).
+bool waits(pt_ctx *c)
+{
+    return c->plan.halo_words > 0 ||
+           (c->plan.n_oblock > 0 && (c->plan.encoding == PT_BITPACK32 || c->byte_octets)) ||
+           (can_coop(c) && !whole_instance_tiles(c));
+}
+
+// `cycles` PT cycles in one launch per kind of tile (can_coop holds).
+int enqueue_coop(pt_ctx *c, int cycles)
+{
+    SweepLaunch L{};
+    L.st = c->st;
+    L.key0 = c->key_flip0;
+    L.key1 = c->key_flip1;
+    L.n_sweeps = c->opt.sweeps_per_exchange;
+    L.block_threads = c->block_threads;
+    L.lane_words = c->lane_words;
+    L.lat = 1;
+    L.fuse_exchange = 1;
+    L.swap_key0 = c->key_swap0;
+    L.swap_key1 = c->key_swap1;
+    L.t_add = (uint32_t)L.n_sweeps;
+    L.cycles = cycles;
+    L.coop = 1;
+    if (c->opt.flags & PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT) {
+        L.wait_polls = 16;
+        L.wait_extra = 1 << 30;
+    }
+    for (int at = 0; at < (int)c->tiles.size();) {
+        L.tile0 = at;
+        L.lds_bytes = 0;
+        const int kind = c->tiles[at].kind;
+        for (; at < (int)c->tiles.size() && c->tiles[at].kind == kind; ++at)
+            L.lds_bytes = std::max(L.lds_bytes, c->tile_lds[at]);
+        L.n_tiles = at - L.tile0;
+        const hipError_t e = launch_sweep(L, kind, c->stream);
+        if (e != hipSuccess) return hip_fail(e, "sweep launch of several cycles");
+    }
+    c->multi_launches += 1;
+    c->multi_cycles += cycles;
+    return PT_OK;
+}
+
 // Self-tuning: while candidates remain, each sweep launch uses the next candidate shape
 // and is timed (synchronously) with its own events.  The candidates are run in
 // kTuneRounds rounds, each keeping its best per-sweep time (one timing of a short call
-// can be off by more than the gap between shapes), the slower half only in the first two,
-// and the fastest shape is kept.
+// can be off by more than the gap between shapes), all but the fastest quarter only in the
+// first two, and the fastest shape is kept.  Shapes with the same tiles are one candidate, and
+// a shape that runs several cycles a launch is timed so from the second round on, over as many
+// cycles as keep the tuning under some 50 (320 replicas of 336 x
+// 64 spins take 87.9 us a cycle in resident tiles of 2 and 101.7 in tiles of 1; over two cycles
+// a launch the two timed alike).
 // Launch shape does not change the trajectory, so tuning costs only the slower
 // candidates' extra time.
 constexpr size_t kTuneRounds = 3;
+uint64_t tiles_hash(const pt_ctx *c)
+{
+    uint64_t h = 1469598103934665603ull;
+    for (const Tile &t : c->tiles)
+        for (const int32_t v : {t.inst, t.c0, t.P, t.kind, t.g0, t.ng}) h = (h ^ (uint32_t)v) * 1099511628211ull;
+    return h;
+}
 // fused: ask for the exchange step too; set to whether the launches run it (the candidate's
 // route decides).
-int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr)
+// cycles: how many PT cycles are asked for (with fused); set to those the call ran.
+int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = nullptr)
 {
     if (n_sweeps <= 0) return PT_OK;
     const bool bp = c->plan.encoding == PT_BITPACK32;
@@ -1584,25 +1684,54 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr)
         if (fused) *fused = fuse;
         return bp || c->byte_octets ? enqueue_bp_sweep(c, n_sweeps, fuse) : enqueue_sweep_once(c, n_sweeps, fuse);
     };
+    const int ask = cycles ? *cycles : 1;
+    if (cycles) *cycles = 1;
     if (!c->tuning) return sweep();
     auto use = [&](size_t k) -> int {
-        c->block_threads = c->cand[k].second;
-        (bp ? c->oct_as_words : c->byte_octets) = c->cand_alt[k] != 0;
+        const pt_ctx::Shape &s = c->cand[k];
+        c->block_threads = s.threads;
+        c->coop_fits = -1;
+        (bp ? c->oct_as_words : c->byte_octets) = s.alt;
         if (bp && c->n_words_tiles == 0 && !c->plan.words_alt) return PT_OK;
-        return build_tiles(c, c->opt.tile_replicas, c->cand[k].first);
+        return build_tiles(c, s.replicas > 0 ? s.replicas : c->opt.tile_replicas, s.tile_bytes);
     };
-    const size_t k = c->cand_order[c->cand_next];
-    int rc = use(k);
-    if (rc) return rc;
+    int rc = PT_OK;
+    size_t k = 0;
+    for (;;) {
+        k = c->cand_order[c->cand_next];
+        rc = use(k);
+        if (rc) return rc;
+        if (c->tune_round > 0) break;
+        c->cand[k].tiles = tiles_hash(c);
+        bool again = false;
+        for (size_t j = 0; j < c->cand_next; ++j) {
+            const pt_ctx::Shape &x = c->cand[c->cand_order[j]], &y = c->cand[k];
+            again = again || (x.tiles == y.tiles && x.threads == y.threads && x.alt == y.alt);
+        }
+        if (!again) break;
+        c->cand_order.erase(c->cand_order.begin() + (ptrdiff_t)c->cand_next);
+        if (c->cand_next == c->cand_order.size()) {  // the first candidate again, in its next round
+            c->cand_next = 0;
+            c->tune_round = 1;
+        }
+    }
     HIP_TRY(hipEventRecord(c->tune_ev[0], c->stream));
     const int fb = c->fallbacks;
-    rc = sweep();
+    const int most = std::min(8, std::max(2, 24 / (int)c->cand_order.size()));
+    const int n_cyc = fused && c->tune_round > 0 && can_coop(c) && !whole_instance_tiles(c) ? std::min(ask, most) : 1;
+    if (n_cyc > 1) {
+        *fused = true;
+        *cycles = n_cyc;
+        rc = enqueue_coop(c, n_cyc);
+    } else {
+        rc = sweep();
+    }
     if (rc) return rc;
     HIP_TRY(hipEventRecord(c->tune_ev[1], c->stream));
     HIP_TRY(hipEventSynchronize(c->tune_ev[1]));
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, c->tune_ev[0], c->tune_ev[1]));
-    const double t = (c->fallbacks == fb) ? (double)ms / n_sweeps : 1e30;
+    const double t = (c->fallbacks == fb) ? (double)ms / ((double)n_sweeps * n_cyc) : 1e30;
     c->cand_ms[k] = std::min(c->cand_ms[k], t);
     if (++c->cand_next < c->cand_order.size()) return PT_OK;
     c->cand_next = 0;
@@ -1610,13 +1739,14 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr)
                      [&](size_t x, size_t y) { return c->cand_ms[x] < c->cand_ms[y]; });
     if (++c->tune_round < kTuneRounds) {
         // (a process's first launch of a kernel loads its code, which spoils its first time)
-        if (c->tune_round == 2) c->cand_order.resize((c->cand.size() + 1) / 2);
+        if (c->tune_round == 2)
+            c->cand_order.resize(std::min(c->cand_order.size(), std::max<size_t>(2, (c->cand_order.size() + 3) / 4)));
         return PT_OK;
     }
     c->tuning = false;
     rc = use(c->cand_order[0]);
-    if (rc == PT_OK && !bp && !c->byte_octets && c->plan.halo_words == 0 && c->shadow) {
-        // no octet blocks after all: nothing to recover from
+    if (rc == PT_OK && c->shadow && !waits(c)) {
+        // no launch whose tiles wait for each other after all: nothing to recover from
         HIP_TRY(hipStreamSynchronize(c->stream));
         HIP_TRY(hipFree(c->shadow));
         c->shadow = nullptr;
@@ -1661,11 +1791,12 @@ int enqueue_tau_corr(pt_ctx *c)
     return PT_OK;
 }
 
-int enqueue_cycle(pt_ctx *c)
+// cycles: as for enqueue_sweep.
+int enqueue_cycle(pt_ctx *c, int *cycles = nullptr)
 {
     const int k = c->opt.sweeps_per_exchange;
     bool fused = false;
-    int rc = enqueue_sweep(c, k, &fused);
+    int rc = enqueue_sweep(c, k, &fused, cycles);
     if (rc == PT_OK && !fused) rc = enqueue_exchange(c, (uint32_t)k);
     if (rc) return rc;
     return enqueue_tau_corr(c);
@@ -1797,6 +1928,7 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     st.halo_words = P.halo_words;
     st.itiles = (const int32_t *)(w + P.o_itiles);
     st.icount = (uint32_t *)(w + P.o_icount);
+    st.icycle = (uint32_t *)(w + P.o_icycle);
     st.prog = (int32_t *)(w + P.o_prog);
     st.err = (uint32_t *)(w + P.o_err);
     st.bp_sblk = (const int32_t *)(w + P.o_bp_sblk);
@@ -1912,26 +2044,32 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     if (tune_int8 || tune_bp) {
         if (tune_int8) {
             for (int tb : {8 * 1024, 16 * 1024, 32 * 1024, 64 * 1024, 128 * 1024})
-                for (int th : {256, 512, 1024}) c->cand.emplace_back(tb, th);
+                for (int th : {256, 512, 1024}) c->cand.push_back({tb, th, false, 0});
         } else {
-            for (int th : {256, 512, 1024}) c->cand.emplace_back(opt->tile_bytes, th);
+            for (int th : {256, 512, 1024}) c->cand.push_back({opt->tile_bytes, th, false, 0});
         }
-        c->cand_alt.assign(c->cand.size(), 0);
         if (tune_int8 && oct_alt)
             for (int th : {512, 1024}) {
                 if (P.n_otile == 0 && th < 1024) continue;  // slice blocks have a size of their own
-                c->cand.emplace_back(0, th);
-                c->cand_alt.push_back(1);
+                c->cand.push_back({0, th, true, 0});
             }
         // Few octets leave most compute units idle, and a word tile can be as small as one
         // replica: try both.  40 octets of 336 x 64 spins take 255 us a cycle as octets and
         // 109 us as 320 word tiles; with an octet for every unit the octets' shared adder
         // tree wins (7.3e9 attempts/s a unit against about 3e9).
         if (tune_bp && P.words_alt)
-            for (int th : {512, 1024}) {
-                c->cand.emplace_back(opt->tile_bytes, th);
-                c->cand_alt.push_back(1);
-            }
+            for (int th : {512, 1024}) c->cand.push_back({opt->tile_bytes, th, true, 0});
+        // Packed word tiles that all fit the chip at once run many cycles a launch: about one
+        // large tile a unit, with a number of replicas that divides a word group (320 replicas
+        // of 336 x 64 spins: 87.9 us a cycle of 10 sweeps in 160 such tiles of 2 and 101.7 in
+        // 320 of 1, too many to be resident; 768 of 128 x 64: 81.8 in tiles of 4, 89.2 before).
+        if (tune_bp && opt->tile_replicas == 0 && opt->tile_bytes == 0) {
+            int64_t reps = 0;
+            for (const auto &d : P.desc) reps += d.words && (!d.oct || P.words_alt) ? d.R : 0;
+            int p = 1;
+            while (p < 32 && (int64_t)p * c->cus < reps) p *= 2;
+            if (p > 1 && p <= 8) c->cand.push_back({0, 1024, P.words_alt, p});
+        }
         c->cand_ms.assign(c->cand.size(), 1e30);
         for (size_t k = 0; k < c->cand.size(); ++k) c->cand_order.push_back(k);
         c->tuning = true;
@@ -1940,12 +2078,20 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
             if (e != hipSuccess) return cleanup(hip_fail(e, "hipEventCreate"));
         }
     }
-    // a resident slice-block launch may give up a wait: keep a copy of the state to restore
-    if (P.halo_words > 0 || P.n_oblock > 0) {
+    // A launch whose tiles wait for each other may give up a wait: keep a copy of the state to
+    // restore.  Tiles of several cycles a launch hold all spins in LDS, so no larger batch needs
+    // one for them, and without the memory for it they run a launch per cycle.
+    const bool blocks = P.halo_words > 0 || P.n_oblock > 0;
+    if (blocks || (!(opt->flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)) &&
+                   P.state_bytes <= (size_t)c->cus * (size_t)c->lds_limit)) {
         e = hipMalloc((void **)&c->shadow, std::max<size_t>(P.state_bytes, 1));
         if (e != hipSuccess) {
             c->shadow = nullptr;
-            return cleanup(hip_fail(e, "hipMalloc (state copy)"));
+            (void)hipGetLastError();
+            if (blocks) return cleanup(hip_fail(e, "hipMalloc (state copy)"));
+        } else if (!c->tuning && !waits(c)) {
+            (void)hipFree(c->shadow);
+            c->shadow = nullptr;
         }
         e = take_snapshot(c);
         if (e != hipSuccess) return cleanup(hip_fail(e, "state copy"));
@@ -1989,8 +2135,14 @@ int pt_run(pt_ctx *c, int32_t n_cycles)
     // exchange), while tuning, with a launch failure to inject, or under PT_FLAG_NO_GRAPH
     // (which asks for one set of launches per cycle).
     constexpr int kLaunchCycles = 1024;
+    while (n_cycles > 0 && c->tuning) {
+        int m = n_cycles;
+        const int rc = enqueue_cycle(c, &m);
+        if (rc) return rc;
+        n_cycles -= m;
+    }
     if (n_cycles > 1 && c->plan.encoding == PT_INT8 &&
-        !(c->opt.flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH)) && !c->tuning &&
+        !(c->opt.flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH)) &&
         !c->inject_pending && whole_instance_tiles(c)) {
         const int k = c->opt.sweeps_per_exchange;
         while (n_cycles > 0) {
@@ -2002,8 +2154,17 @@ int pt_run(pt_ctx *c, int32_t n_cycles)
         }
         if (n_cycles == 0) return PT_OK;
     }
+    // Batches of more tiles that are all resident do the same, the tiles waiting for each other
+    // between cycles.
+    if (n_cycles > 1 && can_coop(c)) {
+        for (; n_cycles > 0; n_cycles -= std::min(n_cycles, kLaunchCycles)) {
+            const int rc = enqueue_coop(c, std::min(n_cycles, kLaunchCycles));
+            if (rc) return rc;
+        }
+        return PT_OK;
+    }
     const bool eager = (c->opt.flags & (PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)) != 0 ||
-                       c->inject_pending || c->tuning;
+                       c->inject_pending;
     if (eager) {
         for (int i = 0; i < n_cycles; ++i) {
             int rc = enqueue_cycle(c);
@@ -2054,6 +2215,9 @@ int recover(pt_ctx *c)
 {
     HIP_TRY(hipMemcpyAsync(c->ws + c->plan.o_state, c->shadow, c->plan.state_bytes,
                            hipMemcpyDeviceToDevice, c->stream));
+    // a tile that gave up may have left its instance's counts behind
+    HIP_TRY(hipMemsetAsync(c->ws + c->plan.o_icount, 0, c->plan.desc.size() * 4, c->stream));
+    HIP_TRY(hipMemsetAsync(c->ws + c->plan.o_icycle, 0, c->plan.desc.size() * 4, c->stream));
     c->resident_off = true;
     c->oct_resident = false;
     drop_graph(c);

@@ -29,6 +29,10 @@ struct SweepLaunch {
     // fused whole-replica launches whose tiles each hold a whole instance: PT cycles run by
     // the launch (0 or 1: one)
     int32_t cycles;
+    // with cycles > 1: the instances may be in several tiles each, all of the launch resident
+    // at once, and wait for their instance's exchange step between cycles (wait_polls and
+    // wait_extra bound the waits as for slice blocks)
+    int32_t coop;
     // resident slice blocks: every replica's ring of blocks lies in one run of the
     // workgroup-to-tile map, so on one XCD, and records and counts pass through its L2 (2:
     // the same, and the launch reports its XCDs as mismatched; a test hook)
@@ -142,6 +146,10 @@ int words_mode(int32_t F);
 int32_t words_tile_lds_bytes(const InstDesc &d, int32_t P);
 int32_t words_lanes(const InstDesc &d, int32_t P);
 hipError_t words_kernels_set_lds(int32_t bytes);
+// Tiles of `threads` threads and `lds_bytes` of LDS that one compute unit holds at once in a
+// launch of several cycles.
+hipError_t words_resident_per_cu(bool replicas, int32_t threads, int32_t lds_bytes, int32_t *per_cu);
+hipError_t fast_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu);
 hipError_t launch_sweep_words(const SweepLaunch &L, bool replicas, hipStream_t s);
 
 // Byte offsets of one instance's observables in the buffer gather_obs writes: arrays of R

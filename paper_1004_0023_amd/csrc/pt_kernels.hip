@@ -246,7 +246,9 @@ __device__ __forceinline__ void copy_spins(uint32_t *lds_sp, uint32_t *dev, int 
 }
 
 // The threshold tables of the rungs that P consecutive replicas sit on, in one flat loop
-// so that the rung lookups of all replicas are in flight together.
+// so that the rung lookups of all replicas are in flight together.  RELOAD: the rungs were
+// written in this launch.
+template <bool RELOAD = false>
 __device__ __forceinline__ void stage_tables(const DevState &st, const InstDesc &d, int c0, int P,
                                              uint32_t *dst)
 {
@@ -254,7 +256,7 @@ __device__ __forceinline__ void stage_tables(const DevState &st, const InstDesc 
     const int qs = nt / tw, ks = nt - qs * tw;
     int q = threadIdx.x / tw, k = threadIdx.x - q * tw;
     for (; q < P;) {
-        const int rung = st.rung_of[d.rep_base + c0 + q];
+        const int rung = RELOAD ? coherent_rung(st, d.rep_base + c0 + q) : st.rung_of[d.rep_base + c0 + q];
         dst[q * tw + k] = st.tbl[d.tbl_base + (int64_t)rung * tw + k];
         q += qs;
         k += ks;
@@ -903,6 +905,9 @@ __device__ __forceinline__ void fast_energy(const DevState &st, const InstDesc &
 // waves per SIMD: the exchange step in the loop needs more registers than eight allow).
 // LAT: the latency path for tiles whose colour classes fit one pass of the workgroup (its
 // own instantiation at four waves per SIMD, for batches of at most one tile per unit).
+// Both: tiles on the latency path, all resident, that wait for each other between cycles
+// (coop_cycle): 32 replicas of 128 x 64 spins as 32 tiles took 46.4 us a cycle of 10 sweeps
+// with a launch per cycle and take 43.6.
 template <bool FUSE, bool MULTI = false, bool LAT = false>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MULTI || LAT ? 4 : 8))) sweep_fast_kernel(SweepLaunch L)
 {
@@ -916,15 +921,14 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MULTI
     uint64_t t0 = st.ctr[n].t;
     __syncthreads();
 
-    // With MULTI (fused launches whose tiles each hold a whole instance) the workgroup
-    // runs L.cycles PT cycles: after each but the last it does the instance's exchange
-    // step itself, with the replicas still in LDS, then stages the threshold tables of
-    // the replicas' new rungs and reads the advanced sweep counter.
+    // With MULTI the workgroup runs L.cycles PT cycles with the replicas in LDS, staging only
+    // the threshold tables of the replicas' new rungs between them.  A tile that holds a whole
+    // instance does the instance's exchange steps itself; others wait for their first tile.
     for (int cyc = 0;; ++cyc) {
         if (L.lane_words == 2 && d.G4 >= 2)
-            fast_dispatch<2, !MULTI, LAT>(L, d, tile, t, t0);
+            fast_dispatch<2, !MULTI || LAT, LAT>(L, d, tile, t, t0);
         else
-            fast_dispatch<1, !MULTI, LAT>(L, d, tile, t, t0);
+            fast_dispatch<1, !MULTI || LAT, LAT>(L, d, tile, t, t0);
 
         switch (d.D) {
         case 1: fast_energy<1>(st, d, tile, t); break;
@@ -937,19 +941,28 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MULTI
         case 8: fast_energy<8>(st, d, tile, t); break;
         default: fast_energy<0>(st, d, tile, t); break;
         }
-        if (!(FUSE && MULTI) || cyc + 1 >= L.cycles) break;
+        if constexpr (MULTI && LAT) {
+            coop_cycle(st, n, tile.c0 == 0, cyc, L.cycles, L.swap_key0, L.swap_key1, L.t_add, L.wait_polls,
+                       (uint32_t)L.wait_extra, kErrWait);
+            if (cyc + 1 >= L.cycles) break;
+            stage_tables<true>(st, d, tile.c0, tile.P, t.tbl);
+            t0 += (uint64_t)L.t_add;
+            __syncthreads();
+            continue;
+        }
+        if (!MULTI || cyc + 1 >= L.cycles) break;
         // only this workgroup reads what the exchange writes: its barriers order it; the
         // counters are re-read with vector loads (a scalar-cache copy would be stale)
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
         exchange_instance<true>(st, n, L.swap_key0, L.swap_key1, L.t_add);
         __syncthreads();
-        stage_tables(st, d, tile.c0, tile.P, t.tbl);
+        stage_tables<true>(st, d, tile.c0, tile.P, t.tbl);
         t0 = __hip_atomic_load(&st.ctr[n].t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
     }
     write_back(st, d, tile, t);
-    if constexpr (FUSE) finish_tile(L, st, n, t.red);
+    if constexpr (FUSE && !(MULTI && LAT)) finish_tile(L, st, n, t.red);
 }
 
 // ------------------------------------------------------------------ slice-block sweep
@@ -2008,6 +2021,7 @@ hipError_t sweep_kernels_set_lds(int32_t fast_bytes, int32_t generic_bytes, int3
         {reinterpret_cast<const void *>(&sweep_fast_kernel<false>), fast_bytes},
         {reinterpret_cast<const void *>(&sweep_fast_kernel<true>), fast_bytes},
         {reinterpret_cast<const void *>(&sweep_fast_kernel<true, true>), fast_bytes},
+        {reinterpret_cast<const void *>(&sweep_fast_kernel<true, true, true>), fast_bytes},
         {reinterpret_cast<const void *>(&sweep_fast_kernel<false, false, true>), fast_bytes},
         {reinterpret_cast<const void *>(&sweep_fast_kernel<true, false, true>), fast_bytes},
         {reinterpret_cast<const void *>(&sweep_generic_kernel<false>), generic_bytes},
@@ -2019,6 +2033,15 @@ hipError_t sweep_kernels_set_lds(int32_t fast_bytes, int32_t generic_bytes, int3
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t fast_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu)
+{
+    int v = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &v, reinterpret_cast<const void *>(&sweep_fast_kernel<true, true, true>), threads, lds_bytes);
+    *per_cu = v;
+    return e;
 }
 
 hipError_t block_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu)
@@ -2055,7 +2078,9 @@ hipError_t launch_sweep(const SweepLaunch &L, int kind, hipStream_t s)
     const dim3 grid(L.n_tiles), block(L.block_threads);
     const bool fuse = L.fuse_exchange != 0;
     if (kind == kTileFast) {
-        if (fuse && L.cycles > 1)
+        if (L.coop)
+            hipLaunchKernelGGL((sweep_fast_kernel<true, true, true>), grid, block, L.lds_bytes, s, L);
+        else if (fuse && L.cycles > 1)
             hipLaunchKernelGGL((sweep_fast_kernel<true, true>), grid, block, L.lds_bytes, s, L);
         else if (L.lat && fuse)
             hipLaunchKernelGGL((sweep_fast_kernel<true, false, true>), grid, block, L.lds_bytes, s, L);

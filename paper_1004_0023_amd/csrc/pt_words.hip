@@ -542,9 +542,13 @@ __device__ __forceinline__ void store_bits(const InstDesc &d, const Tile &tile, 
     }
 }
 
-// RM: replicas in a word (M <= 2).
-template <bool RM>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) sweep_words_kernel(SweepLaunch L)
+// RM: replicas in a word (M <= 2).  COOP: L.cycles PT cycles with every tile resident, the
+// arrays staged once and the exchange step in the launch (coop_cycle): 216 replicas of 201 x
+// 100 spins took 65.3 us a cycle of 10 sweeps with a launch per cycle and take 54.0, 512 of
+// 10^3 x 1 spins 32.1 and 26.6.  Its own instantiation, at four waves per SIMD: at eight the
+// loop with the exchange step in it spills (62.4 us and 31.3 with the same tiles).
+template <bool RM, bool COOP>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COOP ? 4 : 8))) sweep_words_kernel(SweepLaunch L)
 {
     extern __shared__ __align__(16) char lds[];
     const DevState &st = L.st;
@@ -608,7 +612,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         }
     }
     for (int k = tid; k < 2 * units * words_rpw(d); k += nt) red[k] = 0;
-    const uint64_t t0 = st.ctr[n].t;
+    uint64_t t0 = st.ctr[n].t;
     __syncthreads();
 
     const WordsLds t = {sp, ent, bias, csite, coff, tbl};
@@ -664,10 +668,31 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
         }
         energy<MODE, RM>(d, tile, t, a, red);
     };
-    switch (d.words) {
-    case kWordsNarrow: run(IntC<kWordsNarrow>{}); break;
-    case kWordsMiddle: run(IntC<kWordsMiddle>{}); break;
-    default: run(IntC<kWordsWide>{}); break;
+    for (int cyc = 0;; ++cyc) {
+        switch (d.words) {
+        case kWordsNarrow: run(IntC<kWordsNarrow>{}); break;
+        case kWordsMiddle: run(IntC<kWordsMiddle>{}); break;
+        default: run(IntC<kWordsWide>{}); break;
+        }
+        __syncthreads();
+        for (int q = tid; q < tile.P; q += nt) {
+            // coherently for the whole device: the exchange step of this launch may read them
+            __hip_atomic_store(&st.E[d.rep_base + tile.c0 + q], (int64_t)red[2 * q] / 2, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st.C[d.rep_base + tile.c0 + q], (int64_t)red[2 * q + 1], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if constexpr (!COOP) break;
+        coop_cycle(st, n, tile.c0 == 0, cyc, L.cycles, L.swap_key0, L.swap_key1, L.t_add, L.wait_polls,
+                   (uint32_t)L.wait_extra, kErrWait);
+        if (cyc + 1 >= L.cycles) break;
+        t0 += (uint64_t)L.t_add;
+        for (int k = tid; k < tile.P * d.tbl_words; k += nt) {
+            const int q = k / d.tbl_words, e = k - q * d.tbl_words;
+            tbl[k] = st.tbl[d.tbl_base + (int64_t)coherent_rung(st, d.rep_base + tile.c0 + q) * d.tbl_words + e];
+        }
+        for (int k = tid; k < 2 * units * words_rpw(d); k += nt) red[k] = 0;
+        __syncthreads();
     }
     if (packed) {
         Staged<4, LoadBits> s_sp(pos, load_bits);
@@ -677,25 +702,13 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     } else {
         store_bytes<RM>(st, d, tile, sp);
     }
-    __syncthreads();
-    for (int q = tid; q < tile.P; q += nt) {
-        const int64_t e = (int64_t)red[2 * q] / 2, cc = (int64_t)red[2 * q + 1];
-        int64_t *Eo = st.E + d.rep_base + tile.c0 + q, *Co = st.C + d.rep_base + tile.c0 + q;
-        if (L.fuse_exchange) {
-            __hip_atomic_store(Eo, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(Co, cc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            *Eo = e;
-            *Co = cc;
-        }
-    }
-    if (L.fuse_exchange) {
+    if (!COOP && L.fuse_exchange) {
         // The tile that completes its instance runs the exchange step.  The step reads no
         // other tile's stores but E_cl and C, which are written and read coherently, so a
         // tile waits for those and counts itself; nothing waits on another workgroup.
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
-        uint32_t *flag = reinterpret_cast<uint32_t *>(red + 2 * words_units(d, tile.P) * words_rpw(d));
+        uint32_t *flag = reinterpret_cast<uint32_t *>(red + 2 * units * words_rpw(d));
         if (tid == 0) {
             const uint32_t before = __hip_atomic_fetch_add(&st.icount[n], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t done = before + 1u == (uint32_t)st.itiles[n] ? 1u : 0u;
@@ -722,20 +735,38 @@ int32_t words_lanes(const InstDesc &d, int32_t P) { return words_units(d, P) * w
 hipError_t words_kernels_set_lds(int32_t bytes)
 {
     if (bytes <= 0) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_words_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_words_kernel<true>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    for (const void *fn : {reinterpret_cast<const void *>(&sweep_words_kernel<false, false>),
+                           reinterpret_cast<const void *>(&sweep_words_kernel<true, false>),
+                           reinterpret_cast<const void *>(&sweep_words_kernel<false, true>),
+                           reinterpret_cast<const void *>(&sweep_words_kernel<true, true>)}) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t words_resident_per_cu(bool replicas, int32_t threads, int32_t lds_bytes, int32_t *per_cu)
+{
+    int v = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &v, replicas ? reinterpret_cast<const void *>(&sweep_words_kernel<true, true>)
+                     : reinterpret_cast<const void *>(&sweep_words_kernel<false, true>), threads, lds_bytes);
+    *per_cu = v;
+    return e;
 }
 
 hipError_t launch_sweep_words(const SweepLaunch &L, bool replicas, hipStream_t s)
 {
     if (L.n_tiles <= 0) return hipSuccess;
-    if (replicas)
-        hipLaunchKernelGGL(sweep_words_kernel<true>, dim3(L.n_tiles), dim3(L.block_threads), L.lds_bytes, s, L);
+    const dim3 grid(L.n_tiles), block(L.block_threads);
+    if (L.coop && replicas)
+        hipLaunchKernelGGL((sweep_words_kernel<true, true>), grid, block, L.lds_bytes, s, L);
+    else if (L.coop)
+        hipLaunchKernelGGL((sweep_words_kernel<false, true>), grid, block, L.lds_bytes, s, L);
+    else if (replicas)
+        hipLaunchKernelGGL((sweep_words_kernel<true, false>), grid, block, L.lds_bytes, s, L);
     else
-        hipLaunchKernelGGL(sweep_words_kernel<false>, dim3(L.n_tiles), dim3(L.block_threads), L.lds_bytes, s, L);
+        hipLaunchKernelGGL((sweep_words_kernel<false, false>), grid, block, L.lds_bytes, s, L);
     return hipGetLastError();
 }
 

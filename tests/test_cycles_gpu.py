@@ -1,0 +1,98 @@
+"""Several cycles per launch with tiles that wait for each other (word tiles, and byte tiles on
+the latency path) against the oracle: one to many tiles an instance, both forms of the exchange
+step, calls of one cycle, of a few, and of more than a launch takes; and a wait that gives up."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from paper_1004_0023_amd import ptqmc
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("E_cl", "C", "rung_of", "replica_of", "acc", "att", "roundtrips", "label", "sumE", "sumC",
+        "sumE2", "sumC2", "nup", "ndown")
+
+
+def words():
+    rng = np.random.default_rng([1004, 51])
+    mk = lambda *a, **k: W.random_small_instance(rng, *a, **k)
+    return [mk(10, 1, 70, d=3, jmax=3), mk(12, 6, 9, d=3, jmax=8), mk(7, 2, 2, d=2), mk(9, 12, 67, d=4), mk(8, 14, 33, d=5)]
+
+
+def fast():
+    rng = np.random.default_rng([1004, 52])
+    return [W.random_small_instance(rng, 12, 64, 8), W.random_small_instance(rng, 8, 32, 66, d=4)]
+
+
+CASES = {
+    "words-bytes": (words, dict(encoding=ptqmc.PT_INT8)),
+    "words-packed": (words, dict(encoding=ptqmc.PT_BITPACK32)),
+    "words-one": (words, dict(encoding=ptqmc.PT_INT8, tile_replicas=1, block_threads=128)),
+    "words-packed-three": (words, dict(encoding=ptqmc.PT_BITPACK32, tile_replicas=3, block_threads=512)),
+    "fast-one": (fast, dict(encoding=ptqmc.PT_INT8, tile_replicas=1, block_threads=256)),
+    "fast-four": (fast, dict(encoding=ptqmc.PT_INT8, tile_replicas=4, block_threads=512)),
+    "both": (lambda: words() + fast(), dict(encoding=ptqmc.PT_INT8, tile_replicas=2, block_threads=1024)),
+}
+
+
+def check(s, refs, what):
+    for n, ref in enumerate(refs):
+        got, want = s.observables(n), ref.observables()
+        for key in KEYS:
+            assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), f"{what} instance {n}: {key}"
+        assert np.array_equal(s.spins(n), ref.s), f"{what} instance {n}: spins"
+
+
+def both(s, refs, k, cycles):
+    s.run(cycles)
+    for r in refs:
+        r.run(k, cycles)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_matches_oracle(case):
+    print(f"case: several cycles a launch, {case}", flush=True)
+    build, shape = CASES[case]
+    refs = [oracle.OracleChain(inst, 7, index=n) for n, inst in enumerate(build())]
+    with ptqmc.Sampler(build(), 7, sweeps_per_exchange=3, **shape) as s:
+        for cycles in (90, 2, 1, 37):  # the first call ends the tuning
+            both(s, refs, 3, cycles)
+            s.sweep(1)
+            for r in refs:
+                r.sweep(1)
+        check(s, refs, case)
+        before = s.info()
+        assert before["multi_launches"] >= 2
+        both(s, refs, 3, 1030)
+        check(s, refs, case)
+        after = s.info()
+        assert after["multi_cycles"] - before["multi_cycles"] == 1030
+        assert after["multi_launches"] - before["multi_launches"] == 2 and after["recoveries"] == 0
+
+
+@pytest.mark.parametrize("case", ["words-bytes", "words-packed-three", "fast-one"])
+def test_wait_timeout_recovers(case):
+    print(f"case: several cycles a launch, forced wait timeout, {case}", flush=True)
+    build, shape = CASES[case]
+    refs = [oracle.OracleChain(inst, 9, index=n) for n, inst in enumerate(build())]
+    with ptqmc.Sampler(build(), 9, sweeps_per_exchange=2, flags=ptqmc.PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT, **shape) as s:
+        for cycles in (90, 20):
+            both(s, refs, 2, cycles)
+            s.sync()
+        check(s, refs, "recovered")
+        info = s.info()
+        assert info["recoveries"] == 1
+        both(s, refs, 2, 20)
+        check(s, refs, "after recovery")
+        assert s.info()["recoveries"] == 1 and s.info()["multi_launches"] == info["multi_launches"]
+
+
+@pytest.mark.parametrize("flag", ["PT_FLAG_NO_GRAPH", "PT_FLAG_TAU_CORR"])
+def test_flags_that_ask_for_a_launch_per_cycle(flag):
+    print(f"case: several cycles a launch, {flag}", flush=True)
+    refs = [oracle.OracleChain(inst, 3, index=n) for n, inst in enumerate(words())]
+    with ptqmc.Sampler(words(), 3, sweeps_per_exchange=2, flags=getattr(ptqmc, flag), block_threads=256) as s:
+        both(s, refs, 2, 20)
+        check(s, refs, flag)
+        assert s.info()["multi_launches"] == 0
