@@ -300,9 +300,9 @@ int pt_exchange(pt_ctx *ctx);
  * instance's exchange step (per-instance completion counts), other batches launch the exchange
  * separately.  When every instance fits one tile (and neither PT_FLAG_TAU_CORR nor
  * PT_FLAG_NO_GRAPH is set) up to 1024 cycles run in one launch instead, each workgroup doing
- * its instance's exchange steps itself.  So do batches whose tiles, all word tiles or byte
- * tiles on the latency path, fit the device at once (without PT_FLAG_TIMING): an instance's
- * tiles then wait for its exchange step between cycles.  pt_info counts these launches (multi_launches, multi_cycles) and, with
+ * its instance's exchange steps itself.  So do batches whose tiles, all word tiles, byte
+ * tiles on the latency path or octet slice blocks, fit the device at once (without
+ * PT_FLAG_TIMING): an instance's tiles then wait for its exchange step between cycles.  pt_info counts these launches (multi_launches, multi_cycles) and, with
  * PT_FLAG_TIMING, times them apart from the sweep and exchange launches (multi_ms).  With
  * PT_FLAG_NO_GRAPH every cycle is launched eagerly.  The chain is the same in every case. */
 int pt_run(pt_ctx *ctx, int32_t n_cycles);

@@ -230,7 +230,9 @@ __device__ __forceinline__ void coop_wait(const DevState &st, const uint32_t *p,
 // The end of cycle cyc (of `cycles`) in a tile of instance n whose E_cl and C stores are under
 // way; `first`: the instance's first tile.  After it (but for the last cycle) the instance's
 // new rungs may be read with coherent_rung.  The counts are 0 again after the last cycle: by
-// then every tile has counted itself, so none waits any more.
+// then every tile has counted itself, so none waits any more.  CLEAR: the tiles add to E_cl and
+// C, which are 0 again before the next cycle.
+template <bool CLEAR = false>
 __device__ __forceinline__ void coop_cycle(const DevState &st, int n, bool first, int cyc, int cycles, uint32_t key0,
                                            uint32_t key1, uint32_t t_add, int polls, uint32_t extra, uint32_t err)
 {
@@ -244,6 +246,14 @@ __device__ __forceinline__ void coop_cycle(const DevState &st, int n, bool first
     if (first) {
         coop_wait(st, &st.icount[n], (uint32_t)st.itiles[n] * (uint32_t)(cyc + 1) + extra, polls, err);
         exchange_instance<true>(st, n, key0, key1, t_add);
+        if constexpr (CLEAR) {
+            __syncthreads();  // every wave has read them
+            const InstDesc d = st.inst[n];
+            for (int r = (int)threadIdx.x; r < d.R && !last; r += (int)blockDim.x) {
+                __hip_atomic_store(&st.E[d.rep_base + r], (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&st.C[d.rep_base + r], (int64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -94,7 +94,7 @@ struct Plan {
     uint64_t flips_per_sweep = 0;
     // byte offsets in the workspace
     size_t o_inst, o_adj, o_off, o_h, o_ent, o_bias, o_csite, o_cls, o_tbl, o_db, o_dK, o_tiles,
-        o_repinst, o_halo, o_itiles, o_icount, o_icycle, o_prog, o_err, o_bp_sblk, o_bp_eblk, o_bp_wg,
+        o_repinst, o_halo, o_itiles, o_icount, o_icycle, o_dev, o_prog, o_err, o_bp_sblk, o_bp_eblk, o_bp_wg,
         o_bp_part, o_oent, o_ohinfo, o_otbl, o_otiles, o_orec, o_oprog, o_oqueue, o_oqitems,
         o_xseen;
     size_t o_state;  // start of the mutable region
@@ -665,6 +665,7 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     P.o_itiles = take((size_t)n_inst * 4);
     P.o_icount = take((size_t)n_inst * 4);  // zero in the uploaded image
     P.o_icycle = take((size_t)n_inst * 4);  // zero in the uploaded image
+    P.o_dev = take(sizeof(DevState));
     P.o_prog = take((size_t)P.max_tiles * 4);
     P.o_err = take(4);                       // zero in the uploaded image
     P.o_bp_sblk = take(P.bp_sblk.size() * 4);
@@ -1039,7 +1040,7 @@ int build_tiles(pt_ctx *c, int force_P, int tile_bytes)
     const bool octs = P.encoding == PT_BITPACK32 ? !c->oct_as_words : c->byte_octets;
     if (!c->byte_octets)
         for (const Tile &t : c->tiles) c->itiles[t.inst] += 1;
-    for (int32_t k = 0; k < P.n_otile && octs; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
+    for (int32_t k = 0; k < P.n_otile + P.n_oblock && octs; ++k) c->itiles[P.otiles[(size_t)k * kOctRec]] += 1;
     HIP_TRY(hipMemcpyAsync(c->ws + P.o_itiles, c->itiles.data(), c->itiles.size() * 4,
                            hipMemcpyHostToDevice, c->stream));
     HIP_TRY(sweep_kernels_set_lds(c->lds_fast, c->lds_generic, c->lds_block));
@@ -1280,7 +1281,8 @@ bool oct_ring_xcd(const pt_ctx *c)
 
 // Bit-packed encoding: n_sweeps sweeps as one launch per colour class (parity, colour) of
 // every instance, then E_cl and C of every replica.
-int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
+// cycles: PT cycles of a batch of resident octet blocks (can_coop), their exchange steps too.
+int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles = 0)
 {
     const Plan &P = c->plan;
     const bool timing = (c->opt.flags & PT_FLAG_TIMING) != 0;
@@ -1349,6 +1351,11 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange)
                 O.wait_polls = 16;
                 O.wait_extra = 1 << 30;
             }
+            O.cycles = cycles;
+            O.dev = reinterpret_cast<const DevState *>(c->ws + P.o_dev);
+            O.swap_key0 = c->key_swap0;
+            O.swap_key1 = c->key_swap1;
+            O.t_add = (uint32_t)n_sweeps;
             e = launch_oct_resident(O, c->stream);
             if (e != hipSuccess) return hip_fail(e, "octet resident launch");
         }
@@ -1559,33 +1566,43 @@ int enqueue_sweep_once(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles =
 }
 
 // Batches of at most this many tiles run a PT cycle as one set of launches, the exchange
-// step in the tile that completes each instance.  Each tile then ends with an agent-scope
-// release (its energies must reach the other XCDs' caches), which costs more than the
-// separate exchange launch it saves once a call has thousands of tiles; small batches are
-// launch-latency bound and gain (measured: 1 tile +22 %, 32 tiles +4 %, 256 tiles -4 %,
-// 7797 tiles -9 %).
+// step in the tile that completes each instance.  Every tile then waits for its stores and
+// counts itself, which costs more than the separate exchange launch it saves once a call has
+// hundreds of tiles; small batches are launch-latency bound and gain (measured a cycle, separate
+// and fused: 1 tile +22 %, 32 tiles +4 %, 510 tiles 209.7 us and 217.3, 1155 tiles 454 and 475,
+// 2303 tiles 782 and 826).
 constexpr size_t kFuseMaxTiles = 64;
 
 // Whether a PT cycle's exchange step runs in the sweep launches of the route in use.
 bool can_fuse(const pt_ctx *c)
 {
     if (c->plan.encoding == PT_BITPACK32 || c->byte_octets) return c->oct_fuse;
-    // word tiles count themselves without a release, whatever their number
+    // word tiles: whatever their number
     return c->tiles.size() <= kFuseMaxTiles || c->n_words_tiles == (int)c->tiles.size();
+}
+
+// Whether octet slice blocks are the whole batch on the route in use.
+bool octet_blocks(const pt_ctx *c)
+{
+    const Plan &P = c->plan;
+    return P.n_oblock > 0 && P.n_otile == 0 && !P.bp_generic &&
+           (P.encoding == PT_BITPACK32 ? c->n_words_tiles == 0 : c->byte_octets);
 }
 
 // Whether pt_run may run several cycles per launch of tiles that wait for each other between
 // cycles: every tile a word tile or, at most one per unit and on the latency path, a fast byte
-// tile; a launch per kind, each resident as a whole (hence no octets, no generic tiles).  Not
+// tile; a launch per kind, each resident as a whole.  Or every octet in resident slice blocks.  Not
 // under PT_FLAG_TIMING, which times sweeps.
 bool can_coop(pt_ctx *c)
 {
-    if (!c->shadow || c->resident_off || c->byte_octets || c->inject_pending || c->tiles.empty() ||
+    if (!c->shadow || c->resident_off || c->inject_pending ||
         (c->opt.flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)))
         return false;
+    if (octet_blocks(c)) return c->oct_resident;
+    if (c->byte_octets) return false;
     if (c->plan.encoding == PT_BITPACK32 && (!c->oct_fuse || (c->plan.n_otile > 0 && !c->oct_as_words)))
         return false;
-    if ((int)c->tiles.size() != c->n_words_tiles + c->n_fast_tiles) return false;
+    if (c->tiles.empty() || (int)c->tiles.size() != c->n_words_tiles + c->n_fast_tiles) return false;
     if (c->coop_fits < 0) {
         c->coop_fits = 1;
         for (int kind : {kTileFast, kTileWords, kTileWordsR}) {
@@ -1620,6 +1637,13 @@ bool waits(pt_ctx *c)
 // `cycles` PT cycles in one launch per kind of tile (can_coop holds).
 int enqueue_coop(pt_ctx *c, int cycles)
 {
+    if (octet_blocks(c)) {
+        const int rc = enqueue_bp_sweep(c, c->opt.sweeps_per_exchange, false, cycles);
+        if (rc) return rc;
+        c->multi_launches += 1;
+        c->multi_cycles += cycles;
+        return PT_OK;
+    }
     SweepLaunch L{};
     L.st = c->st;
     L.key0 = c->key_flip0;
@@ -1983,6 +2007,7 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
             ((int32_t *)(img.data() + P.o_label))[d.rep_base + r] = (r == 0) ? PT_LABEL_UP : PT_LABEL_NONE;
         }
     }
+    std::memcpy(img.data() + P.o_dev, &st, sizeof st);
     e = hipMemcpyAsync(c->ws, img.data(), P.total_bytes, hipMemcpyHostToDevice, c->stream);
     if (e != hipSuccess) return cleanup(hip_fail(e, "upload"));
     if (P.encoding == PT_BITPACK32) {
@@ -2157,8 +2182,10 @@ int pt_run(pt_ctx *c, int32_t n_cycles)
     // Batches of more tiles that are all resident do the same, the tiles waiting for each other
     // between cycles.
     if (n_cycles > 1 && can_coop(c)) {
-        for (; n_cycles > 0; n_cycles -= std::min(n_cycles, kLaunchCycles)) {
-            const int rc = enqueue_coop(c, std::min(n_cycles, kLaunchCycles));
+        // (slice blocks count the sweeps of a launch in 32 bits)
+        const int most = std::min(kLaunchCycles, std::max(1, (1 << 29) / c->opt.sweeps_per_exchange));
+        for (; n_cycles > 0; n_cycles -= std::min(n_cycles, most)) {
+            const int rc = enqueue_coop(c, std::min(n_cycles, most));
             if (rc) return rc;
         }
         return PT_OK;

@@ -85,6 +85,9 @@ struct OctLaunch {
     // one XCD, and records and progress counts pass through its L2 (2: the same, and the
     // launch reports its XCDs as mismatched; a test hook)
     int32_t xcd_local;
+    // resident: PT cycles run by the launch, the exchange steps in it (0: sweeps only)
+    int32_t cycles;
+    const DevState *dev;  // with cycles: st in device memory
 };
 constexpr int kOctRec = 8;  // ints per octet work item
 enum OctMode { kOctTile = 0, kOctPhase = 1, kOctResident = 2 };

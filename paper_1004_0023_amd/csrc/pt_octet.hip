@@ -304,19 +304,28 @@ __host__ __device__ __forceinline__ OctLds oct_layout(const InstDesc &d, int ng,
 // Stage the tables of the eight slots (by their current rungs), the neighbour entries,
 // field codes and colour lists.  Entries and field codes are padded to 16 bytes per
 // instance in device memory, so they move as 16-byte pieces.
-__device__ __forceinline__ void oct_stage_common(const DevState &st, const InstDesc &d, char *lds,
-                                                 const OctLds &o, int c0, int nslots)
+// The threshold tables of an octet's replicas.  RELOAD: their rungs were written in this launch.
+template <bool RELOAD = false>
+__device__ __forceinline__ void oct_stage_tables(const DevState &st, const InstDesc &d, char *lds, const OctLds &o,
+                                                 int c0, int nslots)
 {
-    const int tid = threadIdx.x;
     uint4 *tb = reinterpret_cast<uint4 *>(lds + o.tbl);
     constexpr int kQ = kOctTableWords / 4;  // 16-byte pieces per table
     batched<2>(nslots * kQ,
             [&](int k) {
                 const int r = k / kQ, e = k - r * kQ;
-                const int rg = st.rung_of[d.rep_base + c0 + r];
+                const int at = d.rep_base + c0 + r;
+                const int rg = RELOAD ? coherent_rung(st, at) : st.rung_of[at];
                 return reinterpret_cast<const uint4 *>(st.otbl + d.otbl_base + (int64_t)rg * kOctTableWords)[e];
             },
             [&](int k, uint4 v) { tb[k] = v; });
+}
+
+__device__ __forceinline__ void oct_stage_common(const DevState &st, const InstDesc &d, char *lds,
+                                                 const OctLds &o, int c0, int nslots)
+{
+    const int tid = threadIdx.x;
+    oct_stage_tables(st, d, lds, o, c0, nslots);
     const uint4 *es = reinterpret_cast<const uint4 *>(st.oent + d.oent_base);
     uint4 *ed = reinterpret_cast<uint4 *>(lds + o.ent);
     batched<2>((d.N * d.D + 7) / 8, [&](int k) { return es[k]; }, [&](int k, uint4 v) { ed[k] = v; });
@@ -1019,6 +1028,15 @@ __device__ __forceinline__ void oct_publish(int32_t *flag, int v, bool local)
     if (threadIdx.x == 0) rec_st(reinterpret_cast<uint32_t *>(flag), (uint32_t)v, local);
 }
 
+// The end of a cycle out of line: in the kernel its registers come out of the sweeps' (64
+// cycles of 64 replicas of 1024 x 256 spins, with read-back: 11.4 ms so, 9.7 out of line).
+__device__ __attribute__((noinline)) void oct_cycle(const DevState *dev, int n, bool first, int cyc, int cycles,
+                                                    uint32_t key0, uint32_t key1, uint32_t t_add, int polls,
+                                                    uint32_t extra)
+{
+    coop_cycle<true>(*dev, n, first, cyc, cycles, key0, key1, t_add, polls, extra, kErrWait);
+}
+
 // All sweeps of a call over one octet slice block, with every block of the launch resident.
 // LDS keeps P0 = parity 0 of groups g0 .. g0 + ng and P1 = parity 1 of groups g0 - 1 ..
 // g0 + ng - 1 (rows of ng + 1 words); the first group of P0 and of P1 are halos owned by
@@ -1038,6 +1056,10 @@ __device__ __forceinline__ void oct_publish(int32_t *flag, int v, bool local)
 // sweep s + 1 only after step 4 has seen next reach step 3 of sweep s + 1 (after its step 1
 // read R1).  Progress counts are per call (zeroed by oct_clear).  After the last sweep the
 // block adds its part of E_cl and C and writes its own groups back.
+// COOP: L.cycles PT cycles with the exchange steps in the launch (coop_cycle), the rows staged
+// once; the blocks' progress counts and records run on from cycle to cycle.  The same 64 cycles
+// took 10.3 ms with a launch to clear E_cl and C, one to sweep and one to exchange a cycle.
+template <bool COOP>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) oct_resident_kernel(OctLaunch L)
 {
     extern __shared__ __align__(16) char lds[];
@@ -1067,7 +1089,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
     oct_stage_rows(sp, 0, g0, ng + 1, P0);
     oct_stage_rows(sp, 1, g0 - 1, ng + 1, P1);
     oct_stage_common(st, d, lds, o, c0, nslots);
-    const uint64_t t0 = st.ctr[n].t;
+    uint64_t t0 = st.ctr[n].t;
     __syncthreads();
     uint32_t *R0 = st.orec + roff;                   // records: R0 region, then R1 region
     uint32_t *R1 = st.orec + L.rec_words + roff;
@@ -1078,41 +1100,56 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
     const OctPlanes pl0 = {P0, RS, P1, RS}, pl1 = {P1 + 4u, RS, P0, RS};
     const uint32_t halo1 = P1, halo0 = P0 + 4u * (uint32_t)ng;  // x = 0 of P1, x = ng of P0
     const bool local = L.xcd_local != 0;
+    const int cycles = COOP ? L.cycles : 1;
     oct_dispatch(d.D, L.split != 0, [&](auto dt, auto spl) __attribute__((always_inline)) {
         constexpr int DT = decltype(dt)::value, SPL = decltype(spl)::value;
         const OctBlock<DT, SPL> blk(L, d, o, n, c0, nslots, g0, ng);
-        oct_put_draws(o.red, 0, (uint32_t)t0, (uint32_t)c0, L.key0, L.key1);
-        __syncthreads();
-        for (int ph = 0; ph < 2 * L.n_sweeps; ++ph) {
-            const int p = ph & 1, sw = ph >> 1;
-            if (p == 0)
-                oct_put_draws(o.red, sw + 1, (uint32_t)(t0 + (uint64_t)(sw + 1)), (uint32_t)c0, L.key0, L.key1);
-            const int32_t *flag = p == 0 ? prog + 2 * prev + 1 : prog + 2 * next;
-            const uint32_t *rin = p == 0 ? R1prev : R0next;
-            const uint32_t hin = p == 0 ? halo1 : halo0;
-            blk.sweep(p == 0 ? pl0 : pl1, p, sw, [&](int g) {
-                if (g > 0) {
-                    __syncthreads();
-                } else if (ph > 0) {
-                    // the neighbour's record, on its way while this block drew
-                    oct_wait(st, flag, sw + p + L.wait_extra, polls);
-                    for (int i = tid; i < N; i += nt) st32(hin + (uint32_t)i * RS, rec_ld(rin + i));
-                    __syncthreads();
+        for (int cyc = 0;; ++cyc) {
+            const int done = cyc * L.n_sweeps;  // sweeps of this launch before the cycle
+            oct_put_draws(o.red, 0, (uint32_t)t0, (uint32_t)c0, L.key0, L.key1);
+            __syncthreads();
+            for (int ph = 0; ph < 2 * L.n_sweeps; ++ph) {
+                const int p = ph & 1, sw = ph >> 1;
+                if (p == 0)
+                    oct_put_draws(o.red, sw + 1, (uint32_t)(t0 + (uint64_t)(sw + 1)), (uint32_t)c0, L.key0, L.key1);
+                const int32_t *flag = p == 0 ? prog + 2 * prev + 1 : prog + 2 * next;
+                const uint32_t *rin = p == 0 ? R1prev : R0next;
+                const uint32_t hin = p == 0 ? halo1 : halo0;
+                blk.sweep(p == 0 ? pl0 : pl1, p, sw, [&](int g) {
+                    if (g > 0) {
+                        __syncthreads();
+                    } else if (ph > 0 || done > 0) {
+                        // the neighbour's record, on its way while this block drew
+                        oct_wait(st, flag, done + sw + p + L.wait_extra, polls);
+                        for (int i = tid; i < N; i += nt) st32(hin + (uint32_t)i * RS, rec_ld(rin + i));
+                        __syncthreads();
+                    }
+                });
+                if (ph + 1 < 2 * L.n_sweeps || cyc + 1 < cycles) {
+                    uint32_t *rout = p == 0 ? R0 : R1;
+                    const uint32_t from = p == 0 ? P0 : P1 + 4u * (uint32_t)ng;
+                    for (int i = tid; i < N; i += nt) rec_st(rout + i, ld32(from + (uint32_t)i * RS), local);
+                    oct_publish(prog + 2 * b + p, done + sw + 1, local);
                 }
-            });
-            if (ph + 1 < 2 * L.n_sweeps) {
-                uint32_t *rout = p == 0 ? R0 : R1;
-                const uint32_t from = p == 0 ? P0 : P1 + 4u * (uint32_t)ng;
-                for (int i = tid; i < N; i += nt) rec_st(rout + i, ld32(from + (uint32_t)i * RS), local);
-                oct_publish(prog + 2 * b + p, sw + 1, local);
             }
+            if (tid < 32) st32(o.red + 4u * (uint32_t)tid, 0u);  // held draws until here
+            __syncthreads();
+            oct_block_energy<DT>(L, d, lds, o, pl1, ng);
+            if (!COOP) break;
+            __syncthreads();
+            oct_block_energy_out(st, d, lds, o, c0, nslots);
+            oct_cycle(L.dev, n, c0 == 0 && g0 == 0, cyc, cycles, L.swap_key0, L.swap_key1, L.t_add, L.wait_polls,
+                      (uint32_t)L.wait_extra);
+            if (cyc + 1 >= cycles) break;
+            oct_stage_tables<true>(st, d, lds, o, c0, nslots);
+            t0 += (uint64_t)L.t_add;
+            __syncthreads();
         }
-        if (tid < 32) st32(o.red + 4u * (uint32_t)tid, 0u);  // held draws until here
-        __syncthreads();
-        oct_block_energy<DT>(L, d, lds, o, pl1, ng);
     });
-    __syncthreads();
-    oct_block_energy_out(st, d, lds, o, c0, nslots);
+    if constexpr (!COOP) {
+        __syncthreads();
+        oct_block_energy_out(st, d, lds, o, c0, nslots);
+    }
     for (int k = tid; k < (N << lgng); k += nt) {
         const int x = k & (ng - 1), i = k >> lgng;
         sp.store(0, i, g0 + x, ld32(P0 + (uint32_t)i * RS + 4u * (uint32_t)x));
@@ -1156,24 +1193,33 @@ hipError_t oct_kernels_set_lds(int32_t tile_bytes, int32_t phase_bytes, int32_t 
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(&oct_phase_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, phase_bytes);
     if (e == hipSuccess && resident_bytes > 0)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&oct_resident_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, resident_bytes);
+        for (const void *fn : {reinterpret_cast<const void *>(&oct_resident_kernel<false>),
+                               reinterpret_cast<const void *>(&oct_resident_kernel<true>)}) {
+            e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, resident_bytes);
+            if (e != hipSuccess) break;
+        }
     return e;
 }
 
 hipError_t oct_resident_per_cu(int32_t threads, int32_t lds_bytes, int32_t *per_cu)
 {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &n, reinterpret_cast<const void *>(&oct_resident_kernel), threads, (size_t)lds_bytes);
-    *per_cu = n;
+    int a = 0, b = 0;
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &a, reinterpret_cast<const void *>(&oct_resident_kernel<false>), threads, (size_t)lds_bytes);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &b, reinterpret_cast<const void *>(&oct_resident_kernel<true>), threads, (size_t)lds_bytes);
+    *per_cu = a < b ? a : b;
     return e;
 }
 
 hipError_t launch_oct_resident(const OctLaunch &L, hipStream_t s)
 {
     if (L.n_tiles <= 0 || L.n_sweeps <= 0) return hipSuccess;
-    hipLaunchKernelGGL(oct_resident_kernel, dim3(L.n_tiles), dim3(L.threads), L.lds_bytes, s, L);
+    if (L.cycles > 0)
+        hipLaunchKernelGGL(oct_resident_kernel<true>, dim3(L.n_tiles), dim3(L.threads), L.lds_bytes, s, L);
+    else
+        hipLaunchKernelGGL(oct_resident_kernel<false>, dim3(L.n_tiles), dim3(L.threads), L.lds_bytes, s, L);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""Several cycles per launch with tiles that wait for each other (word tiles, and byte tiles on
-the latency path) against the oracle: one to many tiles an instance, both forms of the exchange
+"""Several cycles per launch with tiles that wait for each other (word tiles, byte tiles on the
+latency path, octet slice blocks) against the oracle: one to many tiles an instance, both forms of the exchange
 step, calls of one cycle, of a few, and of more than a launch takes; and a wait that gives up."""
 import numpy as np
 import pytest
@@ -86,6 +86,37 @@ def test_wait_timeout_recovers(case):
         both(s, refs, 2, 20)
         check(s, refs, "after recovery")
         assert s.info()["recoveries"] == 1 and s.info()["multi_launches"] == info["multi_launches"]
+
+
+def blocks():
+    """Two lattices too large for whole octets: a part octet, and two with a part one."""
+    rng = np.random.default_rng([1004, 53])
+    at = lambda x, y, z: (x % 6) + 6 * ((y % 6) + 6 * (z % 6))
+    edges = np.array([(at(x, y, z), at(x + dx, y + dy, z + dz)) for z in range(6) for y in range(6) for x in range(6)
+                      for dx, dy, dz in ((1, 0, 0), (0, 1, 0), (0, 0, 1))], np.int32)
+    lattice = lambda R: W.make_instance(216, edges, rng.choice(np.array([-1, 1], np.int8), size=len(edges)),
+                                        rng.integers(-1, 2, size=216).astype(np.int8), 512,
+                                        W.geometric_temperatures(0.3, 3.0, R), 1.0)
+    return [lattice(3), lattice(13)]
+
+
+@pytest.mark.parametrize("flags", [0, ptqmc.PT_FLAG_DEVICE_SCOPE_RECORDS, ptqmc.PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT],
+                         ids=["xcd", "device", "timeout"])
+def test_octet_blocks(flags):
+    print(f"case: several cycles a launch, octet slice blocks, flags {flags:#x}", flush=True)
+    refs = [oracle.OracleChain(inst, 11, index=n) for n, inst in enumerate(blocks())]
+    with ptqmc.Sampler(blocks(), 11, sweeps_per_exchange=2, encoding=ptqmc.PT_BITPACK32, flags=flags) as s:
+        assert s.info()["oct_blocks"] > 0 and s.info()["oct_tiles"] == 0
+        for cycles in (9, 1, 20):
+            both(s, refs, 2, cycles)
+            s.sweep(1)
+            for r in refs:
+                r.sweep(1)
+            check(s, refs, f"after {cycles}")
+        timeout = flags == ptqmc.PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT
+        info = s.info()
+        assert info["recoveries"] == (1 if timeout else 0)
+        assert info["multi_cycles"] == (9 if timeout else 29)
 
 
 @pytest.mark.parametrize("flag", ["PT_FLAG_NO_GRAPH", "PT_FLAG_TAU_CORR"])
