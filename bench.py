@@ -223,19 +223,21 @@ def main():
                       tile_bytes=args.tile_bytes, block_threads=args.block_threads,
                       encoding=encoding)
     # Untimed set-up: without a launch shape given, the first sweep calls time the candidate
-    # shapes (three rounds of 15); run cycles until that is done, whatever W is, so that
-    # neither the warm-up nor the timed steps include tuning.  Then the W warm-up cycles.
-    for _ in range(64):
+    # shapes (up to three rounds of 17); run cycles until that is done, whatever W is, so that
+    # neither the warm-up nor the timed steps include tuning.  Several cycles a call, as a
+    # program runs them: shapes that run many cycles a launch are timed so.  Then the W
+    # warm-up cycles.
+    for _ in range(16):
         if s.info()["tuned"]:
             break
-        s.run(1)
+        s.run(8)
     if not s.info()["tuned"]:
-        raise RuntimeError("launch-shape tuning did not finish in 64 cycles")
+        raise RuntimeError("launch-shape tuning did not finish in 128 cycles")
     s.run(args.warmup)
     s.sync()
     torch.cuda.synchronize()
     # The timed region is pt_run's own route (graph replays, or multi-cycle launches when
-    # every instance fits one tile), with no events inside it.  The K steps run as five
+    # every instance fits one tile or all tiles are resident), with no events inside it.  The K steps run as five
     # equal segments, each closed by a synchronisation, so the spread of the rate is
     # visible; the reported value is all K steps over the whole time.
     n_seg = 5 if steps >= 5 else 1
@@ -259,12 +261,12 @@ def main():
     # on, pt_run launches cycle by cycle with HIP events on the library's stream around
     # every sweep call (one launch per occupancy class of whole-replica tiles; slice
     # blocks: one resident launch per call, or one per sweep; packed: one per colour
-    # class) and every exchange launch; multi-cycle launches are timed whole.  The
+    # class) and every exchange launch; multi-cycle launches of whole instances are timed
+    # whole, and resident tiles run their one-cycle launches here.  The
     # roofline is quoted per launch of the dominant kernel: the call's algorithmic work
     # and event time divided by its launch count, so the mean launch duration is the one
     # a kernel trace of the timed route reports.
-    multi = info["multi_launches"] > 0
-    cal_cycles = 4096 if multi else max(1, min(steps, 100))
+    cal_cycles = 4096 if info["multi_launches"] > 0 and info["n_tiles"] == len(insts) else max(1, min(steps, 100))
     s.timing_reset()
     pre = s.info()
     s.timing_enable(True)
@@ -275,6 +277,7 @@ def main():
     # the launch counts of multi-cycle launches run on; keep this pass's
     cal["multi_launches"] -= pre["multi_launches"]
     cal["multi_cycles"] -= pre["multi_cycles"]
+    multi = cal["multi_launches"] > 0
     blocked = cal["block_tiles"] > 0
     packed = encoding == ptqmc.PT_BITPACK32
     if multi:
@@ -286,19 +289,22 @@ def main():
         avg_sweep_s = launch_s / cycles_per_launch  # one cycle, its exchange included
     else:
         avg_sweep_s = cal["sweep_ms"] / max(1, cal["sweep_launches"]) / 1e3
-        if (packed and cal["oct_blocks"] > 0 and cal["oct_tiles"] == 0 and
-                cal["class_launches"] == 0 and cal["oct_resident"]):
+        if cal["oct_blocks"] > 0 and cal["oct_tiles"] == 0 and cal["class_launches"] == 0 and cal["oct_resident"]:
             # octet slice blocks, all resident: one launch per call
             kernel = "oct_resident_kernel"
             launches_per_call = 1
-        elif packed and cal["oct_blocks"] > 0 and cal["oct_tiles"] == 0 and cal["class_launches"] == 0:
+        elif cal["oct_blocks"] > 0 and cal["oct_tiles"] == 0 and cal["class_launches"] == 0:
             # octet slice blocks: one launch per parity of every sweep
             kernel = "oct_phase_kernel"
             launches_per_call = 2 * k
-        elif packed and cal["oct_tiles"] > 0 and cal["oct_blocks"] == 0 and cal["class_launches"] == 0:
+        elif cal["oct_tiles"] > 0 and cal["oct_blocks"] == 0 and cal["class_launches"] == 0:
             # whole octets: one launch per call and workgroup size
             kernel = "oct_tile_kernel"
             launches_per_call = max(1, cal["oct_tile_launches"])
+        elif packed and cal["n_tiles"] > 0 and cal["class_launches"] == 0:
+            # word tiles: one launch per kind and call
+            kernel = "sweep_words_kernel"
+            launches_per_call = max(1, cal["sweep_groups"])
         elif packed:
             # one launch per colour class and sweep, plus the two energy launches of the call
             kernel = "bp_sweep_kernel"
