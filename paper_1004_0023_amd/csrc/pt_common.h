@@ -256,6 +256,10 @@ struct Tile {
     int32_t next;  //   same replica (cyclically; itself when one block covers the replica)
 };
 
+// Polls of a tile that waits between the cycles of a launch (coop_cycle): some 0.1 s; the host
+// adds to it for calls of many sweeps.
+constexpr int kCoopPolls = 1 << 16;
+
 struct Counters {
     uint64_t t;      // sweeps done
     uint64_t e;      // exchange steps done

@@ -208,8 +208,6 @@ __device__ __forceinline__ void exchange_instance(const DevState &st, int n, uin
 // carries on, and once any has, the others stop waiting too (the host then restores the state
 // of the last clean synchronisation and replays the calls since with a launch per cycle).
 
-constexpr int kCoopPolls = 1 << 18;
-
 // Thread 0 polls *p until it reaches need while the workgroup waits at a barrier.
 __device__ __forceinline__ void coop_wait(const DevState &st, const uint32_t *p, uint32_t need, int max_polls,
                                           uint32_t err)

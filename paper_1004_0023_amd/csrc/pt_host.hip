@@ -790,7 +790,7 @@ struct pt_ctx {
     // 1 pt_exchange, 2 pt_run), and whether resident launches are off since a recovery.
     char *shadow = nullptr;
     std::vector<std::pair<int, int>> journal;
-    bool replaying = false, resident_off = false;
+    bool replaying = false, resident_off = false, captured = false;
     int64_t recoveries = 0;
     uint32_t last_device_error = 0;  // the device error word of the last failed synchronisation
     // whole octets from the device work queue; the exchange fused into the octet that
@@ -1204,9 +1204,24 @@ hipError_t take_snapshot(pt_ctx *c)
                           hipMemcpyDeviceToDevice, c->stream);
 }
 
+// Whether the caller is capturing the context's stream.
+bool capturing(const pt_ctx *c)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
+}
+
+// A call captured into a caller's graph does not run now, and its replays are not seen here: it
+// is not noted, and no several cycles a launch (can_coop) from then on, which a recovery would
+// have to replay in order with them.
 void journal_add(pt_ctx *c, int kind, int n)
 {
-    if (c->shadow && !c->replaying) c->journal.emplace_back(kind, n);
+    if (!c->shadow || c->replaying) return;
+    if (capturing(c))
+        c->captured = true;
+    else
+        c->journal.emplace_back(kind, n);
 }
 
 int check_err(pt_ctx *c, uint32_t err);
@@ -1595,7 +1610,7 @@ bool octet_blocks(const pt_ctx *c)
 // under PT_FLAG_TIMING, which times sweeps.
 bool can_coop(pt_ctx *c)
 {
-    if (!c->shadow || c->resident_off || c->inject_pending ||
+    if (!c->shadow || c->resident_off || c->captured || c->inject_pending ||
         (c->opt.flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)))
         return false;
     if (octet_blocks(c)) return c->oct_resident;
@@ -1658,6 +1673,10 @@ int enqueue_coop(pt_ctx *c, int cycles)
     L.t_add = (uint32_t)L.n_sweeps;
     L.cycles = cycles;
     L.coop = 1;
+    // an instance's tiles may be shared out unevenly: allow some 0.1 ms of difference a sweep.
+    // (Two contexts that each hold part of the chip wait for each other: the sooner they give
+    // up, the less that costs.)
+    L.wait_polls = kCoopPolls + 64 * std::min(L.n_sweeps, 1 << 23);
     if (c->opt.flags & PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT) {
         L.wait_polls = 16;
         L.wait_extra = 1 << 30;

@@ -127,3 +127,27 @@ def test_flags_that_ask_for_a_launch_per_cycle(flag):
         both(s, refs, 2, 20)
         check(s, refs, flag)
         assert s.info()["multi_launches"] == 0
+
+
+def test_a_callers_capture_records_a_launch_per_cycle():
+    """Into a caller's graph go launches that wait for nothing; every replay is four cycles."""
+    import torch
+    print("case: several cycles a launch, a caller's capture", flush=True)
+    refs = [oracle.OracleChain(inst, 4, index=n) for n, inst in enumerate(words())]
+    stream = torch.cuda.Stream()
+    with ptqmc.Sampler(words(), 4, sweeps_per_exchange=2, block_threads=256, stream=stream) as s:
+        both(s, refs, 2, 20)
+        s.sync()
+        before = s.info()["multi_launches"]
+        assert before > 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            s.run(4)
+        assert s.info()["multi_launches"] == before
+        for replay in range(3):
+            with torch.cuda.stream(stream):
+                graph.replay()
+            for r in refs:
+                r.run(2, 4)
+            both(s, refs, 2, 3)
+            check(s, refs, f"replay {replay}")
