@@ -13,9 +13,10 @@
 // is written back, so the sweep itself is the same for both.
 //
 // Measured on MI355X, us per cycle of 10 sweeps and an exchange, the one-byte-at-a-time kernel
-// or a launch per colour class -> word tiles: 16 lattices of 10^3 spins at M = 1, 32 replicas,
-// 149 -> 33; 8 instances of 201 spins at M = 100, 27 replicas, 262 -> 70; 16 packed instances
-// of 128 spins at M = 64 with couplings up to 3, 48 replicas, 760 -> 95.
+// or a launch per colour class -> word tiles, a launch per cycle -> many cycles a launch: 16
+// lattices of 10^3 spins at M = 1, 32 replicas, 149 -> 32 -> 27; 8 instances of 201 spins at
+// M = 100, 27 replicas, 262 -> 65 -> 54; 16 packed instances of 128 spins at M = 64 with
+// couplings up to 3, 48 replicas, 760 -> 89 -> 82.
 //
 // What bounds it is VALU issue: per word about 37 operations of Philox, 2 to 3 per neighbour,
 // 5 for the table index and 4.5 per attempt for lookup, compare and merge.  The time
