@@ -1195,7 +1195,8 @@ hipError_t blocks_resident(pt_ctx *c, bool &resident)
 int recover(pt_ctx *c);
 
 // The state region copied to the shadow copy, the journal cleared (stream-ordered: the
-// copy reads the state as the calls queued so far leave it).
+// copy reads the state as the calls queued so far leave it).  Only where the device error word
+// is known to be 0 or the whole state was just written.
 hipError_t take_snapshot(pt_ctx *c)
 {
     c->journal.clear();
@@ -2419,6 +2420,9 @@ int pt_set_spins(pt_ctx *c, int32_t inst, const int8_t *in)
     const InstDesc &d = c->plan.desc[inst];
     for (size_t x = 0; x < (size_t)d.R * d.M * d.N; ++x)
         if (in[x] != 1 && in[x] != -1) return fail(PT_EINVAL, "spins must be +1 or -1");
+    // the other instances' state must be the chain's before it becomes the copy a recovery
+    // restores: a launch that gave up a wait is recovered from first
+    if ((rc = sync_and_check(c))) return rc;
     if (c->plan.encoding == PT_BITPACK32) {
         std::vector<uint32_t> wb((size_t)bp_words(d), 0u);
         for (int r = 0; r < d.R; ++r)

@@ -1,0 +1,83 @@
+"""Calls that meet a launch that gave up a wait, before any synchronisation has seen it: the
+state they leave, write out or return is the chain's, or the call says that it is not."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from paper_1004_0023_amd import ptqmc
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("E_cl", "C", "rung_of", "replica_of", "acc", "att", "roundtrips", "label", "sumE", "sumC",
+        "sumE2", "sumC2", "nup", "ndown")
+SEED, K = 21, 2
+
+
+def words(rng):
+    mk = lambda *a, **k: W.random_small_instance(rng, *a, **k)
+    return [mk(12, 6, 9, d=3, jmax=8), mk(10, 1, 70, d=3, jmax=3), mk(9, 12, 67, d=4)]
+
+
+def fast(rng):
+    return [W.random_small_instance(rng, 12, 64, 8), W.random_small_instance(rng, 8, 32, 66, d=4)]
+
+
+def blocks(rng):
+    edges = W.cubic_lattice(6, 6, 6)
+    return [W.make_instance(216, edges, rng.choice(np.array([-1, 1], np.int8), size=len(edges)),
+                            np.zeros(216, np.int8), 512, W.geometric_temperatures(0.3, 3.0, R), 1.0) for R in (3, 13)]
+
+
+# routes whose tiles wait for each other, with fixed shapes: the first run gives up its waits
+ROUTES = {
+    "words-bytes": (words, dict(block_threads=256)),
+    "words-packed": (words, dict(block_threads=256, encoding=ptqmc.PT_BITPACK32)),
+    "fast": (fast, dict(tile_replicas=4, block_threads=512)),
+    "octet-blocks": (blocks, dict(encoding=ptqmc.PT_BITPACK32)),
+}
+
+
+def build(route):
+    make, shape = ROUTES[route]
+    return make(np.random.default_rng([1004, 61])), shape
+
+
+def chains(insts, cycles):
+    refs = [oracle.OracleChain(inst, SEED, index=n) for n, inst in enumerate(insts)]
+    for r in refs:
+        r.run(K, cycles)
+    return refs
+
+
+def gives_up(insts, shape, **more):
+    return ptqmc.Sampler(insts, SEED, sweeps_per_exchange=K, flags=ptqmc.PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT, **shape,
+                         **more)
+
+
+def check(s, refs, what):
+    for n, ref in enumerate(refs):
+        got, want = s.observables(n), ref.observables()
+        for key in KEYS:
+            assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), f"{what} instance {n}: {key}"
+        assert np.array_equal(s.spins(n), ref.s), f"{what} instance {n}: spins"
+
+
+@pytest.mark.parametrize("route", ROUTES)
+def test_set_spins(route):
+    """Spins set in one instance: the others are the chain's, and so is what follows."""
+    print(f"case: spins set after a wait that gave up, {route}", flush=True)
+    insts, shape = build(route)
+    refs = chains(insts, 6)
+    x = np.random.default_rng(5).choice(np.array([-1, 1], np.int8), size=refs[1].s.shape)
+    refs[1].s[...] = x
+    refs[1].E[...], refs[1].C[...] = refs[1].energies()
+    with gives_up(insts, shape) as s:
+        s.run(6)
+        s.set_spins(1, x)
+        check(s, refs, "set")
+        assert s.info()["recoveries"] == 1
+        s.run(3)
+        for r in refs:
+            r.run(K, 3)
+        check(s, refs, "after")
