@@ -2462,11 +2462,13 @@ int pt_save(pt_ctx *c, void *buf, size_t *len)
     if (*len < need) return fail(PT_EINVAL, "checkpoint buffer too small");
     CkptHeader h{kMagic, kVersion, c->plan.state_bytes, c->opt.seed, n_inst_of(c),
                  c->opt.encoding, c->plan.flips_per_sweep};
+    // checked (and recovered) before the copy: what is written is the chain's state
+    const int rc = sync_and_check(c);
+    if (rc) return rc;
     std::memcpy(buf, &h, sizeof h);
     HIP_TRY(hipMemcpyAsync((char *)buf + sizeof h, c->ws + c->plan.o_state, c->plan.state_bytes,
                            hipMemcpyDeviceToHost, c->stream));
-    const int rc = sync_and_check(c);
-    if (rc) return rc;
+    HIP_TRY(hipStreamSynchronize(c->stream));
     *len = need;
     return PT_OK;
 }

@@ -81,3 +81,18 @@ def test_set_spins(route):
         for r in refs:
             r.run(K, 3)
         check(s, refs, "after")
+
+
+@pytest.mark.parametrize("route", ROUTES)
+def test_save(route):
+    """The checkpoint that the failed launch's recovery precedes holds the chain's state."""
+    print(f"case: checkpoint after a wait that gave up, {route}", flush=True)
+    insts, shape = build(route)
+    refs = chains(insts, 6)
+    with gives_up(insts, shape) as s:
+        s.run(6)
+        blob = s.save()
+        assert s.info()["recoveries"] == 1
+    with ptqmc.Sampler(insts, SEED, sweeps_per_exchange=K, **shape) as s:
+        s.load(blob)
+        check(s, refs, "loaded")
