@@ -51,8 +51,11 @@
  * them restores the state of the last clean synchronisation (a device copy the context
  * keeps when such launches are possible), replays the calls since with slice blocks
  * launched per sweep (or per parity) and a launch per cycle, and then runs them that way for
- * the rest of the context (pt_info.recoveries counts this).  PT_ESTATE is returned only if that replay
- * fails too.
+ * the rest of the context (pt_info.recoveries counts this).  PT_ESTATE is returned if that replay
+ * fails too, and if a call on the context was captured into a caller's graph before: the library
+ * does not see the graph's replays, so it cannot tell which calls to replay.  (A context that a
+ * caller has captured runs no several cycles per launch any more, so only resident slice blocks
+ * and calls made before the capture can come to that; synchronise before capturing.)
  */
 #ifndef PTQMC_H
 #define PTQMC_H

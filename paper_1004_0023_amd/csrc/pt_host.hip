@@ -787,7 +787,8 @@ struct pt_ctx {
     bool oct_resident = false;  // octet slice blocks: one resident launch per call
     // Recovery when a resident launch's wait gave up: a device copy of the state region at
     // the last clean synchronisation, the calls queued since (kind, count: 0 pt_sweep,
-    // 1 pt_exchange, 2 pt_run), and whether resident launches are off since a recovery.
+    // 1 pt_exchange, 2 pt_run), whether resident launches are off since a recovery, and whether
+    // a caller has captured a call.
     char *shadow = nullptr;
     std::vector<std::pair<int, int>> journal;
     bool replaying = false, resident_off = false, captured = false;
@@ -1213,12 +1214,12 @@ bool capturing(const pt_ctx *c)
     return status != hipStreamCaptureStatusNone;
 }
 
-// A call captured into a caller's graph does not run now, and its replays are not seen here: it
-// is not noted, and no several cycles a launch (can_coop) from then on, which a recovery would
-// have to replay in order with them.
+// A call captured into a caller's graph does not run now, and its replays are not seen here: from
+// then on the calls that ran since a synchronisation are not known, so none is noted, nothing is
+// recovered (check_err), and there are no several cycles a launch (can_coop).
 void journal_add(pt_ctx *c, int kind, int n)
 {
-    if (!c->shadow || c->replaying) return;
+    if (!c->shadow || c->replaying || c->captured) return;
     if (capturing(c))
         c->captured = true;
     else
@@ -1231,9 +1232,9 @@ int check_err(pt_ctx *c, uint32_t err);
 // that gave up a wait, an octet kernel that refused to run).  After a wait that gave up,
 // the state is restored from the copy of the last clean synchronisation and the calls
 // queued since are replayed with every slice block launched per sweep (or per parity),
-// which gives the chain's state again; otherwise the call fails with PT_ESTATE (the word
-// is cleared, and the chain state after such a launch is not the sampler's).  A clean
-// synchronisation after new calls takes a new copy.
+// which gives the chain's state again; otherwise, and once a caller has captured a call, the
+// call fails with PT_ESTATE (the word is cleared, and the chain state after such a launch is
+// not the sampler's).  A clean synchronisation after new calls takes a new copy.
 int sync_and_check(pt_ctx *c)
 {
     uint32_t *err = reinterpret_cast<uint32_t *>(c->obs_pin);
@@ -1253,14 +1254,18 @@ int check_err(pt_ctx *c, uint32_t err)
         if (err & kErrLdsBase)
             return fail(PT_ESTATE, "an octet kernel found its dynamic LDS away from address 0 "
                                    "and did not run; the state is inconsistent");
-        if ((err & kErrPlace) && c->shadow && !c->replaying) return recover(c);
+        const bool known = c->shadow && !c->replaying;  // the state to restore
+        if (known && c->captured && (err & (kErrWait | kErrPlace)))
+            return fail(PT_ESTATE, "a resident launch gave up a wait, and replays of a caller's graph "
+                                   "may have run since the last synchronisation; the state is inconsistent");
+        if ((err & kErrPlace) && known) return recover(c);
         if (err & kErrPlace)
             return fail(PT_ESTATE, "the workgroups of a resident slice-block launch did not keep "
                                    "to round-robin XCDs; the state is inconsistent");
         if (err & kErrQueue)
             return fail(PT_ESTATE, "a whole-octet workgroup found every work queue empty; the "
                                    "state is inconsistent");
-        if (c->shadow && !c->replaying) return recover(c);
+        if (known) return recover(c);
         return fail(PT_ESTATE, "a resident slice-block launch waited too long for its "
                                "neighbouring blocks; the state is inconsistent");
     }

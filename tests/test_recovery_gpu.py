@@ -96,3 +96,25 @@ def test_save(route):
     with ptqmc.Sampler(insts, SEED, sweeps_per_exchange=K, **shape) as s:
         s.load(blob)
         check(s, refs, "loaded")
+
+
+@pytest.mark.parametrize("route", ROUTES)
+def test_replays_of_a_callers_graph_are_not_dropped(route):
+    """A recovery cannot know of replays: a wait that gave up before the capture (or, of resident
+    slice blocks, in a replay) is an error then, never a state without them."""
+    import torch
+    print(f"case: a caller's graph after a wait that gave up, {route}", flush=True)
+    insts, shape = build(route)
+    stream = torch.cuda.Stream()
+    with gives_up(insts, shape, stream=stream) as s:
+        if route != "octet-blocks":
+            s.run(20)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            s.run(4)
+        for _ in range(3):
+            with torch.cuda.stream(stream):
+                graph.replay()
+        with pytest.raises(ptqmc.PTError) as e:
+            s.observables(0)
+        assert e.value.code == ptqmc.PT_ESTATE and s.info()["recoveries"] == 0
