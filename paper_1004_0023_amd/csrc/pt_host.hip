@@ -1228,6 +1228,18 @@ void journal_add(pt_ctx *c, int kind, int n)
 
 int check_err(pt_ctx *c, uint32_t err);
 
+// The error word cleared, and the counts of tiles and cycles that a tile which gave up a wait
+// may have left behind.
+hipError_t clear_err(pt_ctx *c)
+{
+    const Plan &P = c->plan;
+    const size_t n = P.desc.size() * 4;
+    hipError_t e = hipMemsetAsync(c->ws + P.o_err, 0, 4, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws + P.o_icount, 0, n, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->ws + P.o_icycle, 0, n, c->stream);
+    return e;
+}
+
 // Wait for the stream, then check the device error word (a resident slice-block launch
 // that gave up a wait, an octet kernel that refused to run).  After a wait that gave up,
 // the state is restored from the copy of the last clean synchronisation and the calls
@@ -1249,8 +1261,7 @@ int check_err(pt_ctx *c, uint32_t err)
 {
     if (err != 0) {
         c->last_device_error = err;
-        const uint32_t zero = 0;
-        HIP_TRY(hipMemcpy(c->ws + c->plan.o_err, &zero, 4, hipMemcpyHostToDevice));
+        HIP_TRY(clear_err(c));
         if (err & kErrLdsBase)
             return fail(PT_ESTATE, "an octet kernel found its dynamic LDS away from address 0 "
                                    "and did not run; the state is inconsistent");
@@ -2267,9 +2278,6 @@ int recover(pt_ctx *c)
 {
     HIP_TRY(hipMemcpyAsync(c->ws + c->plan.o_state, c->shadow, c->plan.state_bytes,
                            hipMemcpyDeviceToDevice, c->stream));
-    // a tile that gave up may have left its instance's counts behind
-    HIP_TRY(hipMemsetAsync(c->ws + c->plan.o_icount, 0, c->plan.desc.size() * 4, c->stream));
-    HIP_TRY(hipMemsetAsync(c->ws + c->plan.o_icycle, 0, c->plan.desc.size() * 4, c->stream));
     c->resident_off = true;
     c->oct_resident = false;
     drop_graph(c);
@@ -2485,6 +2493,8 @@ int pt_load(pt_ctx *c, const void *buf, size_t len)
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(c->ws + c->plan.o_state, (const char *)buf + sizeof(CkptHeader),
                            c->plan.state_bytes, hipMemcpyHostToDevice, c->stream));
+    // the whole state is replaced: a wait that gave up before is of no account any more
+    HIP_TRY(clear_err(c));
     HIP_TRY(take_snapshot(c));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return PT_OK;

@@ -118,3 +118,32 @@ def test_replays_of_a_callers_graph_are_not_dropped(route):
         with pytest.raises(ptqmc.PTError) as e:
             s.observables(0)
         assert e.value.code == ptqmc.PT_ESTATE and s.info()["recoveries"] == 0
+
+
+@pytest.mark.parametrize("seen", [False, True], ids=["pending", "failed"])
+@pytest.mark.parametrize("route", ["words-bytes", "words-packed", "fast"])
+def test_load(route, seen):
+    """A checkpoint loaded over such a launch's state, whether or not its failure was reported
+    first, is the state the next cycles start from."""
+    import torch
+    print(f"case: checkpoint loaded after a wait that gave up, {route}, seen {seen}", flush=True)
+    insts, shape = build(route)
+    refs = chains(insts, 4)
+    with ptqmc.Sampler(insts, SEED, sweeps_per_exchange=K, **shape) as s:
+        s.run(4)
+        blob = s.save()
+    stream = torch.cuda.Stream()
+    with gives_up(insts, shape, stream=stream) as s:
+        s.run(300)
+        if seen:
+            with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=stream):
+                s.run(1)
+            with pytest.raises(ptqmc.PTError):
+                s.sync()
+        s.load(blob)
+        for _ in range(3):
+            s.run(1)  # the exchange step in the launch, by the tiles' counts
+        for r in refs:
+            r.run(K, 3)
+        check(s, refs, "continued")
+        assert s.info()["recoveries"] == 0
