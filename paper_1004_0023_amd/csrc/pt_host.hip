@@ -789,7 +789,8 @@ struct pt_ctx {
     // the last clean synchronisation, the calls queued since (kind, count: 0 pt_sweep,
     // 1 pt_exchange, 2 pt_run), whether resident launches are off since a recovery, and whether
     // a caller has captured a call.
-    char *shadow = nullptr;
+    // (shadow is null where nothing can give up; shadow_mem is what was allocated for it.)
+    char *shadow = nullptr, *shadow_mem = nullptr;
     std::vector<std::pair<int, int>> journal;
     bool replaying = false, resident_off = false, captured = false;
     int64_t recoveries = 0;
@@ -1193,6 +1194,7 @@ hipError_t blocks_resident(pt_ctx *c, bool &resident)
     return hipSuccess;
 }
 
+int restore(pt_ctx *c);
 int recover(pt_ctx *c);
 
 // The state region copied to the shadow copy, the journal cleared (stream-ordered: the
@@ -1724,6 +1726,12 @@ int enqueue_coop(pt_ctx *c, int cycles)
 // a launch the two timed alike).
 // Launch shape does not change the trajectory, so tuning costs only the slower
 // candidates' extra time.
+//
+// A timed launch whose tiles wait for each other is checked before the next: the shape that
+// wins may be one that never waits and keeps no copy to restore, and once a wait has been given
+// up no tile waits, so such shapes would time too fast.  The copy is taken anew before the
+// launch, so that only its own cycles are run again after it, and the round starts over with
+// resident launches off.
 constexpr size_t kTuneRounds = 3;
 uint64_t tiles_hash(const pt_ctx *c)
 {
@@ -1775,10 +1783,16 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
             c->tune_round = 1;
         }
     }
-    HIP_TRY(hipEventRecord(c->tune_ev[0], c->stream));
     const int fb = c->fallbacks;
     const int most = std::min(8, std::max(2, 24 / (int)c->cand_order.size()));
     const int n_cyc = fused && c->tune_round > 0 && can_coop(c) && !whole_instance_tiles(c) ? std::min(ask, most) : 1;
+    const bool waiting = c->shadow && !c->replaying &&
+                         (n_cyc > 1 || (c->byte_octets && c->plan.n_oblock > 0 && c->oct_resident));
+    if (waiting) {
+        HIP_TRY(take_snapshot(c));
+        c->journal.emplace_back(fused ? 2 : 0, fused ? ask : n_sweeps);  // the rest of this call
+    }
+    HIP_TRY(hipEventRecord(c->tune_ev[0], c->stream));
     if (n_cyc > 1) {
         *fused = true;
         *cycles = n_cyc;
@@ -1789,6 +1803,21 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
     if (rc) return rc;
     HIP_TRY(hipEventRecord(c->tune_ev[1], c->stream));
     HIP_TRY(hipEventSynchronize(c->tune_ev[1]));
+    if (waiting) {
+        uint32_t *err = reinterpret_cast<uint32_t *>(c->obs_pin);
+        HIP_TRY(launch_gather_err(c->st, err, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        if (*err & ~(kErrWait | kErrPlace)) return check_err(c, *err);
+        if (*err != 0) {
+            c->last_device_error = *err;
+            if ((rc = restore(c))) return rc;
+            c->recoveries += 1;
+            c->cand_ms.assign(c->cand.size(), 1e30);
+            c->cand_next = 0;
+            if (cycles) *cycles = ask;
+            return enqueue_sweep(c, n_sweeps, fused, cycles);
+        }
+    }
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, c->tune_ev[0], c->tune_ev[1]));
     const double t = (c->fallbacks == fb) ? (double)ms / ((double)n_sweeps * n_cyc) : 1e30;
@@ -1806,9 +1835,9 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
     c->tuning = false;
     rc = use(c->cand_order[0]);
     if (rc == PT_OK && c->shadow && !waits(c)) {
-        // no launch whose tiles wait for each other after all: nothing to recover from
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        HIP_TRY(hipFree(c->shadow));
+        // no launch whose tiles wait for each other after all, and those timed were checked:
+        // nothing to recover from.  (The memory stays until pt_free: freeing it here would
+        // wait for every stream of the device.)
         c->shadow = nullptr;
         c->journal.clear();
     }
@@ -2145,14 +2174,16 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     const bool blocks = P.halo_words > 0 || P.n_oblock > 0;
     if (blocks || (!(opt->flags & (PT_FLAG_TAU_CORR | PT_FLAG_NO_GRAPH | PT_FLAG_TIMING)) &&
                    P.state_bytes <= (size_t)c->cus * (size_t)c->lds_limit)) {
-        e = hipMalloc((void **)&c->shadow, std::max<size_t>(P.state_bytes, 1));
+        e = hipMalloc((void **)&c->shadow_mem, std::max<size_t>(P.state_bytes, 1));
         if (e != hipSuccess) {
-            c->shadow = nullptr;
+            c->shadow_mem = nullptr;
             (void)hipGetLastError();
             if (blocks) return cleanup(hip_fail(e, "hipMalloc (state copy)"));
-        } else if (!c->tuning && !waits(c)) {
-            (void)hipFree(c->shadow);
-            c->shadow = nullptr;
+        }
+        c->shadow = c->shadow_mem;
+        if (c->shadow && !c->tuning && !waits(c)) {
+            (void)hipFree(c->shadow_mem);
+            c->shadow = c->shadow_mem = nullptr;
         }
         e = take_snapshot(c);
         if (e != hipSuccess) return cleanup(hip_fail(e, "state copy"));
@@ -2271,16 +2302,24 @@ int pt_run(pt_ctx *c, int32_t n_cycles)
 
 namespace {
 
-// After a resident launch gave up a wait: restore the state of the last clean
-// synchronisation, turn resident launches off (and drop the captured graph, which holds
-// them), and replay the calls queued since; the result is the chain's state.
-int recover(pt_ctx *c)
+// After a resident launch gave up a wait: the state of the last copy again, with resident
+// launches off from here on (and the captured graph, which holds them, dropped).
+int restore(pt_ctx *c)
 {
+    HIP_TRY(clear_err(c));
     HIP_TRY(hipMemcpyAsync(c->ws + c->plan.o_state, c->shadow, c->plan.state_bytes,
                            hipMemcpyDeviceToDevice, c->stream));
     c->resident_off = true;
     c->oct_resident = false;
     drop_graph(c);
+    return PT_OK;
+}
+
+// restore, then the calls queued since the copy was taken; the result is the chain's state.
+int recover(pt_ctx *c)
+{
+    const int restored = restore(c);
+    if (restored) return restored;
     const auto calls = c->journal;
     c->replaying = true;
     int rc = PT_OK;
@@ -2589,7 +2628,7 @@ void pt_free(pt_ctx *c)
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     drop_graph(c);
-    if (c->shadow) (void)hipFree(c->shadow);
+    if (c->shadow_mem) (void)hipFree(c->shadow_mem);
     if (c->obs_pin) (void)hipHostFree(c->obs_pin);
     if (c->spin_pin) (void)hipHostFree(c->spin_pin);
     for (auto e : c->spin_ev)

@@ -147,3 +147,71 @@ def test_load(route, seen):
             r.run(K, 3)
         check(s, refs, "continued")
         assert s.info()["recoveries"] == 0
+
+
+def test_tuning_onto_a_shape_that_waits_for_nothing():
+    """200 whole octets, where the tuner also times 50 resident word tiles: a wait that one of them
+    gives up is recovered from there and then, although octets win and nothing can later."""
+    print("case: a timed shape gave up a wait, another one won", flush=True)
+    rng = np.random.default_rng([1004, 62])
+    edges = W.random_regular_graph(64, 6, rng)
+    insts = [W.make_instance(64, edges, rng.choice(np.array([-1, 1], np.int8), size=len(edges)),
+                             np.zeros(64, np.int8), 64, W.geometric_temperatures(0.2, 3.0, 64), 1.0)
+             for _ in range(25)]
+    packed = dict(sweeps_per_exchange=10, encoding=ptqmc.PT_BITPACK32, tile_replicas=32)
+    with ptqmc.Sampler(insts, SEED, block_threads=512, **packed) as a, \
+            ptqmc.Sampler(insts, SEED, flags=ptqmc.PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT, **packed) as s:
+        a.run(100)
+        a.sweep(3)
+        s.run(70)
+        s.run(30)
+        s.sweep(3)
+        s.sync()
+        info = s.info()
+        assert info["tuned"] == 1 and info["oct_tiles"] == 200 and info["recoveries"] == 1, info
+        assert a.info()["multi_launches"] == 0
+        for n in range(len(insts)):
+            got, want = s.observables(n), a.observables(n)
+            for key in KEYS:
+                assert np.array_equal(got[key], want[key]), f"instance {n}: {key}"
+            assert np.array_equal(s.spins(n), a.spins(n)), f"instance {n}: spins"
+
+
+@pytest.mark.parametrize("k,calls,shape", [(2, (30, 50, 300, 100), {}),
+                                           (200, (40, 1000, 1000), dict(tile_replicas=1, block_threads=1024))],
+                         ids=["tuned", "full"])
+def test_two_contexts_at_work(k, calls, shape):
+    """Two contexts, a thread each; in the second case 210 resident tiles each, one of which
+    fills a compute unit, for longer than a wait lasts: whichever gives up a wait, both chains
+    are those of contexts alone."""
+    import threading
+    print(f"case: two contexts at work at the same time, {shape}", flush=True)
+    rng = np.random.default_rng([1004, 63])
+    batches = [[W.random_small_instance(rng, 65, 20, 70, d=4, jmax=3) for _ in range(3)] for _ in range(2)]
+    alone = []
+    for insts in batches:
+        with ptqmc.Sampler(insts, SEED, sweeps_per_exchange=k, block_threads=256, flags=ptqmc.PT_FLAG_NO_GRAPH) as a:
+            a.run(sum(calls))
+            alone.append([(a.observables(n), a.spins(n)) for n in range(3)])
+    failed = []
+
+    def work(b):
+        try:
+            with ptqmc.Sampler(batches[b], SEED, sweeps_per_exchange=k, **shape) as s:
+                for cycles in calls:
+                    s.run(cycles)
+                for n, (want, spins) in enumerate(alone[b]):
+                    got = s.observables(n)
+                    for key in KEYS:
+                        assert np.array_equal(got[key], want[key]), f"context {b} instance {n}: {key}"
+                    assert np.array_equal(s.spins(n), spins), f"context {b} instance {n}: spins"
+                print(f"context {b}: recoveries {s.info()['recoveries']}", flush=True)
+        except Exception as e:
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(b,)) for b in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
