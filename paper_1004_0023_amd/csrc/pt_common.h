@@ -256,8 +256,8 @@ struct Tile {
     int32_t next;  //   same replica (cyclically; itself when one block covers the replica)
 };
 
-// Polls of a tile that waits between the cycles of a launch (coop_cycle): some 0.1 s; the host
-// adds to it for calls of many sweeps.
+// Polls of a tile that waits between the cycles of a launch (some 40 ms of them), before what
+// the host adds for the sweeps of a cycle (coop_polls).
 constexpr int kCoopPolls = 1 << 16;
 
 struct Counters {

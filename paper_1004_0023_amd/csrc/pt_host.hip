@@ -1313,6 +1313,19 @@ bool oct_ring_xcd(const pt_ctx *c)
            !(c->opt.flags & PT_FLAG_DEVICE_SCOPE_RECORDS);
 }
 
+// Poll bound of the waits between the cycles of a launch.  An instance's tiles run unevenly
+// where some share a unit and others do not, and they meet once a cycle: 66 octets of 2600 sites
+// and 32 slices, 264 blocks on 256 units, take 65 us a sweep and 64 of them, a block a unit, 43;
+// with 2000 sweeps a cycle the 66 gave up a bound of kCoopPolls alone (a poll takes some 0.6 us).
+// A sweep's part grows with the classes, each a step of its own.  (Two contexts that each hold
+// part of the chip wait for each other: the sooner they give up, the less that costs.)
+int coop_polls(const pt_ctx *c)
+{
+    int64_t colors = 1;
+    for (const auto &d : c->plan.desc) colors = std::max<int64_t>(colors, d.n_colors);
+    return kCoopPolls + (int)std::min<int64_t>(c->opt.sweeps_per_exchange * (64 + 4 * colors), 1 << 30);
+}
+
 // Bit-packed encoding: n_sweeps sweeps as one launch per colour class (parity, colour) of
 // every instance, then E_cl and C of every replica.
 // cycles: PT cycles of a batch of resident octet blocks (can_coop), their exchange steps too.
@@ -1381,11 +1394,12 @@ int enqueue_bp_sweep(pt_ctx *c, int n_sweeps, bool fuse_exchange, int cycles = 0
             O.lds_bytes = P.oblock_res_lds;
             O.rec_words = (int32_t)P.orec_words;
             O.xcd_local = !oct_ring_xcd(c) ? 0 : (c->opt.flags & PT_FLAG_TEST_XCD_MISMATCH) ? 2 : 1;
+            O.cycles = cycles;
+            O.cycle_polls = coop_polls(c);
             if (c->opt.flags & PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT) {
-                O.wait_polls = 16;
+                O.wait_polls = O.cycle_polls = 16;
                 O.wait_extra = 1 << 30;
             }
-            O.cycles = cycles;
             O.dev = reinterpret_cast<const DevState *>(c->ws + P.o_dev);
             O.swap_key0 = c->key_swap0;
             O.swap_key1 = c->key_swap1;
@@ -1692,10 +1706,7 @@ int enqueue_coop(pt_ctx *c, int cycles)
     L.t_add = (uint32_t)L.n_sweeps;
     L.cycles = cycles;
     L.coop = 1;
-    // an instance's tiles may be shared out unevenly: allow some 0.1 ms of difference a sweep.
-    // (Two contexts that each hold part of the chip wait for each other: the sooner they give
-    // up, the less that costs.)
-    L.wait_polls = kCoopPolls + 64 * std::min(L.n_sweeps, 1 << 23);
+    L.wait_polls = coop_polls(c);
     if (c->opt.flags & PT_FLAG_TEST_BLOCK_WAIT_TIMEOUT) {
         L.wait_polls = 16;
         L.wait_extra = 1 << 30;

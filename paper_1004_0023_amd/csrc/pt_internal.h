@@ -30,8 +30,8 @@ struct SweepLaunch {
     // the launch (0 or 1: one)
     int32_t cycles;
     // with cycles > 1: the instances may be in several tiles each, all of the launch resident
-    // at once, and wait for their instance's exchange step between cycles (wait_polls and
-    // wait_extra bound the waits as for slice blocks)
+    // at once, and wait for their instance's exchange step between cycles (wait_polls, always
+    // given, and wait_extra bound the waits)
     int32_t coop;
     // resident slice blocks: every replica's ring of blocks lies in one run of the
     // workgroup-to-tile map, so on one XCD, and records and counts pass through its L2 (2:
@@ -87,6 +87,7 @@ struct OctLaunch {
     int32_t xcd_local;
     // resident: PT cycles run by the launch, the exchange steps in it (0: sweeps only)
     int32_t cycles;
+    int32_t cycle_polls;  // with cycles: poll bound of the waits between them
     const DevState *dev;  // with cycles: st in device memory
 };
 constexpr int kOctRec = 8;  // ints per octet work item

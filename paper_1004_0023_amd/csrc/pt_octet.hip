@@ -1138,7 +1138,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
             if (!COOP) break;
             __syncthreads();
             oct_block_energy_out(st, d, lds, o, c0, nslots);
-            oct_cycle(L.dev, n, c0 == 0 && g0 == 0, cyc, cycles, L.swap_key0, L.swap_key1, L.t_add, L.wait_polls,
+            oct_cycle(L.dev, n, c0 == 0 && g0 == 0, cyc, cycles, L.swap_key0, L.swap_key1, L.t_add, L.cycle_polls,
                       (uint32_t)L.wait_extra);
             if (cyc + 1 >= cycles) break;
             oct_stage_tables<true>(st, d, lds, o, c0, nslots);

@@ -215,3 +215,28 @@ def test_two_contexts_at_work(k, calls, shape):
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+def test_uneven_rings_of_a_long_cycle():
+    """66 octets as rings of 4 blocks, some of which share units: their instance's exchange step
+    waits for the slowest ring's 2000 sweeps without giving up."""
+    print("case: octet slice blocks, uneven rings, 2000 sweeps a cycle", flush=True)
+    rng = np.random.default_rng([1004, 64])
+    N, M, R = 2600, 32, 528
+    edges = np.array(sorted({tuple(sorted((i, (i + d) % N))) for i in range(N) for d in (1, 5)}), np.int32)
+    T = W.geometric_temperatures(0.3, 3.0, R)
+    b, Kr = W.st_rungs(T, 1.0, M)
+    inst = W.Instance(N=N, M=M, R=R, edges=edges, J=rng.choice(np.array([-1, 1], np.int8), size=len(edges)),
+                      h=np.zeros(N, np.int8), color=(np.arange(N) % 13).astype(np.uint8), n_colors=13, b=b, K=Kr,
+                      T=T, Gamma=1.0)
+    packed = dict(sweeps_per_exchange=2000, encoding=ptqmc.PT_BITPACK32)
+    with ptqmc.Sampler([inst], SEED, **packed) as s, \
+            ptqmc.Sampler([inst], SEED, flags=ptqmc.PT_FLAG_BLOCK_LAUNCH_PER_SWEEP, **packed) as a:
+        assert s.info()["oct_blocks"] == 264 and s.info()["oct_resident"] == 1
+        s.run(2)
+        got = s.observables(0)
+        assert s.info()["multi_cycles"] == 2 and s.info()["recoveries"] == 0
+        a.run(2)
+        want = a.observables(0)
+        for key in KEYS:
+            assert np.array_equal(got[key], want[key]), key
