@@ -223,9 +223,14 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     P.encoding = encoding;
     const bool bp = encoding == PT_BITPACK32;
     // octets of the batch, whichever kernel runs them
-    int64_t octets = 0;
-    for (int n = 0; n < n_inst; ++n) octets += (inst[n].R + 7) / 8;
-    P.oct_alt = !bp && free_shape(opt);
+    int64_t octets = 0, replicas = 0;
+    for (int n = 0; n < n_inst; ++n) {
+        octets += (inst[n].R + 7) / 8;
+        replicas += inst[n].R;
+    }
+    // A byte batch that might run as octets carries their tables (512 bytes a replica) beside its
+    // own: up to 1 GiB of them, so that no batch outgrows the device for a route it need not take.
+    P.oct_alt = !bp && free_shape(opt) && replicas * kOctTableWords * 4 <= (1ll << 30);
     int64_t rep = 0, pair = 0, adjb = 0, offb = 0, siteb = 0, entb = 0, clsb = 0, tblb = 0,
             spinb = 0, wgb = 0;
     for (int n = 0; n < n_inst; ++n) {
@@ -369,6 +374,12 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
             }
         } else {
             for (int i = 0; i < in.N; ++i) P.bias.push_back(0);
+        }
+        if (bp ? d.oct : P.oct_alt) {
+            if (P.oent.size() > 0x7fffffff || P.otbl.size() > 0x7fffffff) {  // 32-bit bases
+                if (bp) return fail(PT_EINVAL, "batch too large");
+                P.oct_alt = false;
+            }
         }
         if (bp ? d.oct : P.oct_alt) {
             // entries and field codes padded to 16 bytes per instance (the kernels copy them
@@ -640,6 +651,13 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
             P.oct_alt = false;
         }
         if (!bp && !P.oct_alt) P.n_otile = P.n_oblock = 0;
+    }
+    if (!bp && !P.oct_alt) {
+        P.oent.clear();
+        P.ohinfo.clear();
+        P.otbl.clear();
+        P.otiles.clear();
+        P.orec_words = 0;
     }
     // layout
     size_t o = 0;
