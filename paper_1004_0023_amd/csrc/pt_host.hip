@@ -1920,6 +1920,50 @@ int enqueue_cycle(pt_ctx *c, int *cycles = nullptr)
     return enqueue_tau_corr(c);
 }
 
+// Instances of at most this many replicas are read back through the pinned buffer (164 bytes a
+// replica, kept with the context, its offsets 32 bits), larger ones by a copy per array.  With the
+// binding's Python 208 us by the buffer and 345 by copies at 16385 replicas, 906 and 797 at 65536.
+constexpr int32_t kObsReplicas = 1 << 15;
+
+// pt_observables by a copy per array.
+int copy_observables(pt_ctx *c, int32_t inst, pt_obs *o)
+{
+    const Plan &P = c->plan;
+    const InstDesc &d = P.desc[inst];
+    const size_t R = (size_t)d.R, b = (size_t)d.rep_base, pb = (size_t)d.pair_base;
+    const int rc = sync_and_check(c);
+    if (rc) return rc;
+    std::vector<int32_t> label;
+    try {
+        if (o->label) label.resize(R);
+    } catch (...) {
+        return fail(PT_ENOMEM, "host staging allocation failed");
+    }
+    Counters ctr{};
+    const struct {
+        void *dst;
+        size_t off, bytes;
+    } arrays[] = {
+        {o->E_cl, P.o_E + 8 * b, 8 * R}, {o->C, P.o_C + 8 * b, 8 * R},
+        {o->rung_of, P.o_rung + 4 * b, 4 * R}, {o->replica_of, P.o_repof + 4 * b, 4 * R},
+        {o->acc, P.o_acc + 8 * pb, 8 * (R - 1)}, {o->att, P.o_att + 8 * pb, 8 * (R - 1)},
+        {o->roundtrips, P.o_rt + 8 * b, 8 * R}, {label.data(), P.o_label + 4 * b, 4 * label.size()},
+        {o->sumE, P.o_sumE + 8 * b, 8 * R}, {o->sumC, P.o_sumC + 8 * b, 8 * R},
+        {o->sumE2, P.o_sumE2 + 8 * b, 8 * R}, {o->sumC2, P.o_sumC2 + 8 * b, 8 * R},
+        {o->nup, P.o_nup + 8 * b, 8 * R}, {o->ndown, P.o_ndown + 8 * b, 8 * R},
+        {o->sumCt, P.o_sumCt + 8 * PT_TAU_LAGS * b, 8 * PT_TAU_LAGS * R},
+        {&ctr, P.o_ctr + sizeof(Counters) * (size_t)inst, sizeof(Counters)}};
+    for (const auto &a : arrays)
+        if (a.dst && a.bytes)
+            HIP_TRY(hipMemcpyAsync(a.dst, c->ws + a.off, a.bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    for (size_t r = 0; r < label.size(); ++r) o->label[r] = (int8_t)label[r];
+    o->t = ctr.t;
+    o->e = ctr.e;
+    o->n_acc = ctr.n_acc;
+    return PT_OK;
+}
+
 int check_inst(pt_ctx *c, int32_t inst)
 {
     if (!c) return fail(PT_EINVAL, "null context");
@@ -2149,7 +2193,7 @@ int pt_init(pt_ctx **out, const pt_instance *inst, int32_t n_inst, const pt_opti
     // instance is in those
     c->oct_fuse = P.n_oblock == 0 && !P.bp_generic;
     int32_t most_R = 2;
-    for (const auto &d : P.desc) most_R = std::max(most_R, d.R);
+    for (const auto &d : P.desc) most_R = std::max(most_R, std::min(d.R, kObsReplicas));
     e = hipHostMalloc((void **)&c->obs_pin, (size_t)ObsLayout(most_R).bytes, hipHostMallocDefault);
     if (e != hipSuccess) {
         c->obs_pin = nullptr;
@@ -2380,6 +2424,7 @@ int pt_observables(pt_ctx *c, int32_t inst, pt_obs *o)
     if (rc) return rc;
     if (!o) return fail(PT_EINVAL, "null output");
     const InstDesc &d = c->plan.desc[inst];
+    if (d.R > kObsReplicas) return copy_observables(c, inst, o);
     const ObsLayout L(d.R);
     const char *pin = c->obs_pin;
     uint32_t err = 0;
