@@ -1236,14 +1236,18 @@ bool capturing(const pt_ctx *c)
 
 // A call captured into a caller's graph does not run now, and its replays are not seen here: from
 // then on the calls that ran since a synchronisation are not known, so none is noted, nothing is
-// recovered (check_err), and there are no several cycles a launch (can_coop).
+// recovered (check_err), and there are no several cycles a launch (can_coop).  The graph holds
+// the shape in use, whose tile list must stay as it is: tuning, which waits for the stream and
+// so cannot be captured, ends there.
 void journal_add(pt_ctx *c, int kind, int n)
 {
-    if (!c->shadow || c->replaying || c->captured) return;
-    if (capturing(c))
+    if (c->replaying || c->captured || !(c->shadow || c->tuning)) return;
+    if (capturing(c)) {
         c->captured = true;
-    else
+        c->tuning = false;
+    } else if (c->shadow) {
         c->journal.emplace_back(kind, n);
+    }
 }
 
 int check_err(pt_ctx *c, uint32_t err);

@@ -240,3 +240,30 @@ def test_uneven_rings_of_a_long_cycle():
         want = a.observables(0)
         for key in KEYS:
             assert np.array_equal(got[key], want[key]), key
+
+
+@pytest.mark.parametrize("first", [0, 5])
+@pytest.mark.parametrize("route", ["words-packed", "words-bytes", "fast"])
+def test_a_capture_before_tuning_has_ended(route, first):
+    """A call captured as the first one, or while shapes are still timed: every replay is its
+    cycles, and so are the calls between."""
+    import torch
+    print(f"case: a caller's capture while shapes are timed, {route} after {first}", flush=True)
+    insts, shape = build(route)
+    refs = chains(insts, first)
+    stream = torch.cuda.Stream()
+    with ptqmc.Sampler(insts, SEED, sweeps_per_exchange=K, encoding=shape.get("encoding", ptqmc.PT_INT8),
+                       stream=stream) as s:
+        s.run(first)
+        s.sync()
+        assert s.info()["tuned"] == 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            s.run(4)
+        for replay in range(3):
+            with torch.cuda.stream(stream):
+                graph.replay()
+            s.run(21)
+            for r in refs:
+                r.run(K, 25)
+            check(s, refs, f"replay {replay}")
