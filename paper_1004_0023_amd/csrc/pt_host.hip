@@ -835,6 +835,7 @@ struct pt_ctx {
     std::vector<size_t> cand_order; // candidates still in the running, in the order they are tried
     std::vector<double> cand_ms;
     size_t cand_next = 0, tune_round = 0;
+    int tune_done = 0, tune_most = 1;  // cycles timed so far; a launch's in the round under way
     hipEvent_t tune_ev[2] = {nullptr, nullptr};
     int lds_fast = 0, lds_words = 0, lds_generic = 0;
     int max_P = 1;
@@ -1754,9 +1755,9 @@ int enqueue_coop(pt_ctx *c, int cycles)
 // can be off by more than the gap between shapes), all but the fastest quarter only in the
 // first two, and the fastest shape is kept.  Shapes with the same tiles are one candidate, and
 // a shape that runs several cycles a launch is timed so from the second round on, over as many
-// cycles as keep the tuning under some 50 (320 replicas of 336 x
-// 64 spins take 87.9 us a cycle in resident tiles of 2 and 101.7 in tiles of 1; over two cycles
-// a launch the two timed alike).
+// cycles as keep the whole tuning within kTuneCycles (320 replicas of 336 x 64 spins take 87.9 us
+// a cycle in resident tiles of 2 and 101.7 in tiles of 1; over two cycles a launch the two timed
+// alike).  With 13 shapes or more that is the third round only.
 // Launch shape does not change the trajectory, so tuning costs only the slower
 // candidates' extra time.
 //
@@ -1766,6 +1767,20 @@ int enqueue_coop(pt_ctx *c, int cycles)
 // launch, so that only its own cycles are run again after it, and the round starts over with
 // resident launches off.
 constexpr size_t kTuneRounds = 3;
+// Cycles that tuning takes at most when no wait is given up: three of each of the fifteen shapes
+// of a byte batch, what it took before shapes ran several cycles a launch, so that a warm-up that
+// was long enough is so still.
+constexpr int kTuneCycles = 45;
+// Candidates of the third round, of n in the second.
+size_t tune_finalists(size_t n) { return std::min(n, std::max<size_t>(2, (n + 3) / 4)); }
+// Cycles a launch of a candidate that runs several is timed over, with `left` of kTuneCycles for
+// the rest of the tuning as the round begins.
+int tune_cycles(const pt_ctx *c, int left)
+{
+    const int n = (int)c->cand_order.size();
+    if (c->tune_round + 1 < kTuneRounds) left -= 2 * (int)tune_finalists(c->cand_order.size());
+    return std::max(1, std::min({8, std::max(2, 24 / n), left / n}));
+}
 uint64_t tiles_hash(const pt_ctx *c)
 {
     uint64_t h = 1469598103934665603ull;
@@ -1817,7 +1832,8 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
         }
     }
     const int fb = c->fallbacks;
-    const int most = std::min(8, std::max(2, 24 / (int)c->cand_order.size()));
+    if (c->cand_next == 0) c->tune_most = tune_cycles(c, kTuneCycles - c->tune_done);
+    const int most = c->tune_most;
     const int n_cyc = fused && c->tune_round > 0 && can_coop(c) && !whole_instance_tiles(c) ? std::min(ask, most) : 1;
     const bool waiting = c->shadow && !c->replaying &&
                          (n_cyc > 1 || (c->byte_octets && c->plan.n_oblock > 0 && c->oct_resident));
@@ -1847,6 +1863,7 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
             c->recoveries += 1;
             c->cand_ms.assign(c->cand.size(), 1e30);
             c->cand_next = 0;
+            c->tune_done = (int)c->tune_round * (int)c->cand_order.size();
             if (cycles) *cycles = ask;
             return enqueue_sweep(c, n_sweeps, fused, cycles);
         }
@@ -1855,6 +1872,7 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
     HIP_TRY(hipEventElapsedTime(&ms, c->tune_ev[0], c->tune_ev[1]));
     const double t = (c->fallbacks == fb) ? (double)ms / ((double)n_sweeps * n_cyc) : 1e30;
     c->cand_ms[k] = std::min(c->cand_ms[k], t);
+    c->tune_done += n_cyc;
     if (++c->cand_next < c->cand_order.size()) return PT_OK;
     c->cand_next = 0;
     std::stable_sort(c->cand_order.begin(), c->cand_order.end(),
@@ -1862,7 +1880,7 @@ int enqueue_sweep(pt_ctx *c, int n_sweeps, bool *fused = nullptr, int *cycles = 
     if (++c->tune_round < kTuneRounds) {
         // (a process's first launch of a kernel loads its code, which spoils its first time)
         if (c->tune_round == 2)
-            c->cand_order.resize(std::min(c->cand_order.size(), std::max<size_t>(2, (c->cand_order.size() + 3) / 4)));
+            c->cand_order.resize(tune_finalists(c->cand_order.size()));
         return PT_OK;
     }
     c->tuning = false;
