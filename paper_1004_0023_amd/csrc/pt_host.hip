@@ -2653,9 +2653,11 @@ int pt_get_info(pt_ctx *c, pt_info *o)
     int rc = harvest_events(c);
     if (rc) return rc;
     o->n_instances = n_inst_of(c);
-    o->n_tiles = (int)c->tiles.size();
+    o->n_tiles = c->byte_octets ? 0 : (int)c->tiles.size();
     o->block_threads = c->block_threads;
-    o->lds_bytes = std::max(c->lds_fast, std::max(c->lds_generic, c->lds_block));
+    o->lds_bytes = c->byte_octets
+                       ? std::max(c->plan.otile_lds, c->oct_resident ? c->plan.oblock_res_lds : c->plan.oblock_lds)
+                       : std::max({c->lds_fast, c->lds_words, c->lds_generic, c->lds_block});
     o->max_tile_replicas = c->max_P;
     o->fallbacks = c->fallbacks;
     o->encoding = c->opt.encoding;
@@ -2667,7 +2669,7 @@ int pt_get_info(pt_ctx *c, pt_info *o)
     o->sweep_launches = c->sweep_n;
     o->exchange_ms = c->exch_ms;
     o->exchange_launches = c->exch_n;
-    o->sweep_groups = (int32_t)launch_groups(c).size();
+    o->sweep_groups = c->byte_octets ? 0 : (int32_t)launch_groups(c).size();
     o->block_tiles = c->byte_octets ? 0 : c->n_block_tiles;
     o->block_resident = c->byte_octets ? 0 : c->block_persistent;
     o->class_launches = 0;
