@@ -377,14 +377,16 @@ int pt_threshold_device(const double *dS, uint32_t *out, int32_t n, void *stream
 int32_t pt_mlp_param_count(void);
 size_t pt_mlp_workspace_bytes(int32_t batch);
 
-/* logits[batch][64] for features x[batch][32] (the workspace is not used, but checked). */
+/* logits[batch][64] for features x[batch][32].  The workspace is used only where logits
+ * overlaps x or params. */
 int pt_mlp_forward(const float *params, const float *x, float *logits, int32_t batch,
                    void *workspace, void *stream);
 
 /* pt_mlp_forward without a workspace, for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * the same kernel, whose hidden activations stay on chip.  Nothing is allocated or freed by
- * the call.  batch must be in [1, PT_MLP_STATIC_MAX_BATCH], else PT_EINVAL. */
+ * the call.  batch must be in [1, PT_MLP_STATIC_MAX_BATCH], else PT_EINVAL.  (Logits that overlap
+ * x or params pass through one array of the library, which calls on different streams share.) */
 #define PT_MLP_STATIC_MAX_BATCH 4096
 int pt_mlp_forward_static(const float *params, const float *x, float *logits, int32_t batch,
                           void *stream);

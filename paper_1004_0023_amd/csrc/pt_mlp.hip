@@ -113,6 +113,16 @@ __device__ __forceinline__ void row_loss(int kind, float v, float tq, float &d, 
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
 }
 
+// Logits of a call without a workspace whose logits overlap its inputs (forward).
+__device__ float aside[(size_t)PT_MLP_STATIC_MAX_BATCH * kOut];
+
+__global__ void copy_aside_kernel(float *logits, int n)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) logits[i] = aside[i];
+}
+
+// logits: null for `aside`.
 template <bool GRAD>
 __global__ void __launch_bounds__(kRowThreads) mlp_rows_kernel(const float *P, const float *x, const float *q,
                                                                float *logits, Acts g, int B, int kind)
@@ -161,7 +171,7 @@ __global__ void __launch_bounds__(kRowThreads) mlp_rows_kernel(const float *P, c
             if constexpr (GRAD) {
                 zs[row * kOutL + col] = v;
             } else {
-                if (m0 + row < B) logits[(int64_t)(m0 + row) * kOut + col] = v;
+                if (m0 + row < B) (logits ? logits : aside)[(int64_t)(m0 + row) * kOut + col] = v;
             }
         }
     }
@@ -296,10 +306,24 @@ Acts carve(void *ws, int B)
     return a;
 }
 
-hipError_t forward(hipStream_t s, const float *P, const float *x, float *out, int B)
+bool overlap(const float *a, size_t na, const float *b, size_t nb)
 {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + 4 * nb && y < x + 4 * na;
+}
+
+// A workgroup writes its logits while others may still read x and the parameters.  Where the
+// logits overlap those they go to the workspace (or, without one, `aside`) first.
+hipError_t forward(hipStream_t s, const float *P, const float *x, float *out, int B, float *ws)
+{
+    const size_t n = (size_t)B * kOut;
+    const bool over = overlap(out, n, x, (size_t)B * kIn) || overlap(out, n, P, kParams);
     hipLaunchKernelGGL(mlp_rows_kernel<false>, dim3((B + kRows - 1) / kRows), dim3(kRowThreads), 0, s, P, x,
-                       (const float *)nullptr, out, Acts{}, B, 0);
+                       (const float *)nullptr, over ? ws : out, Acts{}, B, 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !over) return e;
+    if (ws) return hipMemcpyAsync(out, ws, n * sizeof(float), hipMemcpyDeviceToDevice, s);
+    hipLaunchKernelGGL(copy_aside_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, (int)n);
     return hipGetLastError();
 }
 
@@ -321,7 +345,7 @@ int pt_mlp_forward(const float *params, const float *x, float *logits, int32_t b
     if (!params || !x || !logits || !workspace)
         return ptq::report_error(PT_EINVAL, "pt_mlp_forward: null pointer");
     if (batch < 1) return ptq::report_error(PT_EINVAL, "pt_mlp_forward: batch < 1");
-    return launched(forward((hipStream_t)stream, params, x, logits, batch), "pt_mlp_forward");
+    return launched(forward((hipStream_t)stream, params, x, logits, batch, (float *)workspace), "pt_mlp_forward");
 }
 
 int pt_mlp_forward_static(const float *params, const float *x, float *logits, int32_t batch,
@@ -334,7 +358,7 @@ int pt_mlp_forward_static(const float *params, const float *x, float *logits, in
         return ptq::report_error(PT_EINVAL, ("pt_mlp_forward_static: batch " + std::to_string(batch) +
                                              " exceeds PT_MLP_STATIC_MAX_BATCH (" +
                                              std::to_string(PT_MLP_STATIC_MAX_BATCH) + ")").c_str());
-    return launched(forward((hipStream_t)stream, params, x, logits, batch), "pt_mlp_forward_static");
+    return launched(forward((hipStream_t)stream, params, x, logits, batch, nullptr), "pt_mlp_forward_static");
 }
 
 int pt_mlp_loss_grad(const float *params, const float *x, const float *target, int32_t batch,
