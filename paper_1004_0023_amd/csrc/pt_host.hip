@@ -509,8 +509,10 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     // batch takes 1182 (2998) us as byte tiles and 936 (2280) as octets.  Batches of fewer
     // octets than half the compute units are not offered the choice (at 136 octets the byte
     // tiles, several to an octet, fill the chip better: 210 us), and the tuner makes it; nor
-    // are batches with byte slice blocks, which are as fast (one lattice of 1024 x 256 spins:
-    // 178 us and 181) or faster (two: 530 and 711).
+    // are batches with byte slice blocks: with a launch per cycle those are as fast (one lattice
+    // of 1024 x 256 spins: 178 us and 181, with correlations 194 and 199) or faster (two: 530 and
+    // 711).  In launches of 64 cycles octet blocks take 138 us for the one lattice, which the few
+    // cycles a shape is timed over do not show.
     bool any_block = false;
     for (const auto &d : P.desc)
         any_block = any_block || (d.oct && oct_lds_bytes(d, d.G4, kOctTile) > kLdsPerWorkgroup / 2);
@@ -1302,8 +1304,8 @@ int check_err(pt_ctx *c, uint32_t err)
             return fail(PT_ESTATE, "a whole-octet workgroup found every work queue empty; the "
                                    "state is inconsistent");
         if (known) return recover(c);
-        return fail(PT_ESTATE, "a resident slice-block launch waited too long for its "
-                               "neighbouring blocks; the state is inconsistent");
+        return fail(PT_ESTATE, "a launch whose workgroups wait for each other gave up a wait; the "
+                               "state is inconsistent");
     }
     if (!c->journal.empty() && !c->replaying) HIP_TRY(take_snapshot(c));
     return PT_OK;

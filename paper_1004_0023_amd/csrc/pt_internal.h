@@ -95,7 +95,7 @@ enum OctMode { kOctTile = 0, kOctPhase = 1, kOctResident = 2 };
 
 
 // Bits of the device error word (DevState::err), read and cleared by the host after a call.
-constexpr uint32_t kErrWait = 1u;     // a resident slice block gave up waiting for a neighbour
+constexpr uint32_t kErrWait = 1u;     // a wait for another workgroup was given up
 constexpr uint32_t kErrLdsBase = 2u;  // an octet kernel found its dynamic LDS away from address 0
 constexpr uint32_t kErrQueue = 4u;    // a whole-octet workgroup found every work queue empty
 constexpr uint32_t kErrPlace = 8u;    // a resident launch's workgroups left round-robin XCDs

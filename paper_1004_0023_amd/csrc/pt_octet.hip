@@ -30,6 +30,9 @@
 //   oct_phase  octet slice blocks: one launch per parity of every sweep, staging ng
 //              four-slice groups of the parity swept and ng + 1 of the other; the last
 //              launch of a call adds each block's part of E_cl and C
+//   oct_resident  octet slice blocks, all resident at once: one launch for all sweeps of a
+//              call, neighbouring blocks passing boundary groups in device memory, or for many
+//              PT cycles with their exchange steps
 //   oct_clear  E_cl and C of the slice-block octets set to zero before a call
 #include "pt_exchange.h"
 #include "pt_xcd.h"

@@ -18,8 +18,12 @@
 // M = 100, 27 replicas, 262 -> 65 -> 54; 16 packed instances of 128 spins at M = 64 with
 // couplings up to 3, 48 replicas, 760 -> 89 -> 82.
 //
-// What bounds it is VALU issue: per word about 37 operations of Philox, 2 to 3 per neighbour,
-// 5 for the table index and 4.5 per attempt for lookup, compare and merge.  The time
+// Its operations are, per word, about 37 of Philox, 2 to 3 per neighbour, 5 for the table index
+// and 4.5 per attempt for lookup, compare and merge (28 lane-operations an attempt in the packed
+// batch above, 78 at M = 1).  What bounds it is not their number alone: the units that hold tiles
+// issue VALU on 59 to 69 % of the slots in the packed batch and on 39 % at M = 1, and the waves
+// wait the rest, since a class step is one pass of the workgroup and so a barrier, a chain of LDS
+// trips and ten Philox rounds in series.  The time
 // neighbours of every word come from one v_perm whose selector, fixed per thread, also does
 // the wrap at the ends of a row, so slice counts that are not a multiple of eight cost
 // nothing more.
@@ -547,7 +551,8 @@ __device__ __forceinline__ void store_bits(const InstDesc &d, const Tile &tile, 
 // arrays staged once and the exchange step in the launch (coop_cycle): 216 replicas of 201 x
 // 100 spins took 65.3 us a cycle of 10 sweeps with a launch per cycle and take 54.0, 512 of
 // 10^3 x 1 spins 32.1 and 26.6.  Its own instantiation, at four waves per SIMD: at eight the
-// loop with the exchange step in it spills (62.4 us and 31.3 with the same tiles).
+// loop with the exchange step in it spills (62.4 us and 31.3 with the same tiles); the form for
+// M <= 2 spills at four as well (148 registers).
 template <bool RM, bool COOP>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COOP ? 4 : 8))) sweep_words_kernel(SweepLaunch L)
 {
