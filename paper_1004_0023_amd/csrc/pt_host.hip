@@ -86,6 +86,10 @@ struct Plan {
     int32_t oblock_res_lds = 0;                // slice blocks, resident layout
     int64_t orec_words = 0;                    // words of each boundary-record region
     bool bp_generic = false;                   // some packed instance runs the per-class kernel
+    // per instance: octets of several degrees; whether any such slice block has a long sweep, or
+    // is slower than the per-class kernel when launched per parity (make_plan)
+    std::vector<char> irregular;
+    bool long_blocks = false, slow_phases = false;
     bool words_alt = false;                    // every whole octet could run as word tiles
     // byte encoding: every instance could run as octets (lists, tables and entries as for the
     // packed one), which the tuner may choose instead of the byte tiles
@@ -213,7 +217,14 @@ bool free_shape(const pt_options &opt)
                           PT_FLAG_INJECT_LAUNCH_OOR_ONCE));
 }
 
-int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Plan &P)
+// What a packed batch leaves to the launches per colour class although octets or word tiles
+// could take it (make_plan).
+struct PackedRoutes {
+    bool irregular = true;                       // octets of several degrees run as octets
+    int32_t merge_colors = 0, merge_parities = 0; // word tiles of at most so many classes do not
+};
+
+int lay_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, const PackedRoutes &routes, Plan &P)
 {
     const uint32_t flags = opt.flags;
     const int32_t encoding = opt.encoding;
@@ -301,15 +312,17 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
         // bit-packed encoding: the octet kernels take +-1 couplings, |h| <= 1 and degrees
         // up to D <= 8 on the fast shapes (M a power-of-two multiple of 8).  Instances of
         // several degrees that do not fit them even as blocks of one group run elsewhere.
+        bool regular = true;
         if ((bp || P.oct_alt) && d.fast && in.n_edges > 0 && in.N <= 32767) {
-            bool ok = D <= 8, regular = true;
+            bool ok = D <= 8;
             for (int e = 0; ok && e < in.n_edges; ++e) ok = std::abs((int)in.edge_J[e]) == 1;
             for (int i = 0; ok && i < in.N; ++i) {
                 ok = std::abs((int)in.h[i]) <= 1;
                 regular = regular && deg[i + 1] - deg[i] == D;
             }
-            d.oct = ok && (regular || oct_lds_bytes(d, 1, kOctResident) <= kLdsPerWorkgroup) ? 1 : 0;
+            d.oct = ok && (regular || (routes.irregular && oct_lds_bytes(d, 1, kOctResident) <= kLdsPerWorkgroup)) ? 1 : 0;
         }
+        P.irregular.push_back(d.oct && !regular);
         // word tiles: byte instances off the fast shapes and bit-packed ones the octet kernels
         // do not take (and, in batches with fewer octets than compute units, those they do:
         // the tuner decides), where padded neighbour rows and one replica fit a workgroup's
@@ -319,6 +332,13 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
             (int64_t)in.N * d.D * 4 <= kLdsPerWorkgroup) {
             d.words = words_mode(F);
             if (words_tile_lds_bytes(d, 1) > kLdsPerWorkgroup) d.words = 0;
+            // In a lone packed instance a tile's sweep is the whole time, and two launches a class
+            // and sweep take less for the largest replicas of few classes: 512 sites, 256 slices
+            // and two classes take 250 us a cycle as word tiles and 238 (2 replicas) or 275 (8 to
+            // 32) per class; 300 sites without couplings and 400 slices 213 and 158 (8).
+            const int few = d.n_colors == 1 ? 32 : d.n_colors == 2 ? 4 : 0;
+            if (bp && n_inst == 1 && in.R <= few && (int64_t)in.N * in.M > 40000 * (d.n_colors + 1)) d.words = 0;
+            if (bp && !d.oct && d.n_colors <= routes.merge_colors && d.parities <= routes.merge_parities) d.words = 0;
         }
         // fast-path rows: D entries per site, (j << ent_sh) << 16 | w1 << 8 | w0 with w0 / w1 the
         // contribution |J| [J < 0] / |J| [J > 0] of a neighbour whose spin byte is 0 / 1;
@@ -541,6 +561,9 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
                                                    ": an octet slice block does not fit in LDS");
                     P.oct_alt = false;
                 }
+                P.long_blocks = P.long_blocks || (P.irregular[n] && (int64_t)ng * d.N > 1400 * d.n_colors);
+                P.slow_phases = P.slow_phases ||
+                                (P.irregular[n] && (d.n_colors < 4 || (int64_t)ng * d.N > 500 * d.n_colors));
             }
             for (int w = 0; w < (d.R + 31) / 32; ++w)
                 for (int o = 0; o < 4 && 32 * w + 8 * o < d.R; ++o) {
@@ -723,6 +746,46 @@ int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Pl
     P.total_bytes = o;
     return PT_OK;
 }
+
+// The plan of a batch.  Packed instances that octets (of several degrees) or word tiles could take
+// stay with the launches per colour class where those are faster, us a cycle of 10 sweeps:
+//   - in a batch that needs those launches for another instance, whose launches the further items
+//     share: beside 8000 sites (8 slices, couplings up to 3, 32 replicas: 278 alone) an open lattice
+//     of 336 sites, 64 slices and 8 replicas takes 284 so and 514 as an octet of its own, 64 sites
+//     with couplings up to 3 284 and 310 as word tiles.  Word tiles only while they are few spins
+//     in all and bring no more classes (48 replicas of 128 x 64 spins in five classes: 660 and 342);
+//   - octet slice blocks of several degrees with a long sweep and not enough of them: 16^3 sites
+//     take 380 whatever the number of blocks, and per class 278 (4 blocks), 316 (32), 411 (64);
+//     14^3 sites 275 and 280 to 361;
+//   - those that are too many to be resident: 512 blocks of 9^3 to 16^3 sites take 611 to 2340
+//     against 519 to 2106, but 1013 against 1392 for 1000 sites in four classes.
+int make_plan(const pt_instance *inst, int32_t n_inst, const pt_options &opt, Plan &P)
+{
+    constexpr int kEnoughBlocks = 64;
+    constexpr int64_t kMergeSpins = 4 << 20;  // some 40 us a cycle in launches that run anyway
+    PackedRoutes routes;
+    int rc = lay_plan(inst, n_inst, opt, routes, P);
+    if (opt.encoding != PT_BITPACK32) return rc;
+    auto per_class = [](const InstDesc &d) { return !d.oct && !d.words; };
+    const bool any = std::find(P.irregular.begin(), P.irregular.end(), 1) != P.irregular.end();
+    if (any && (rc || std::any_of(P.desc.begin(), P.desc.end(), per_class) ||
+                (P.n_oblock > kMostCus ? P.slow_phases : P.long_blocks && P.n_oblock < kEnoughBlocks))) {
+        routes.irregular = false;
+        rc = lay_plan(inst, n_inst, opt, routes, P);
+    }
+    if (rc) return rc;
+    for (const auto &d : P.desc)
+        if (per_class(d)) {
+            routes.merge_colors = std::max(routes.merge_colors, d.n_colors);
+            routes.merge_parities = std::max(routes.merge_parities, d.parities);
+        }
+    int64_t spins = 0;
+    for (const auto &d : P.desc)
+        if (!d.oct && d.words && d.n_colors <= routes.merge_colors && d.parities <= routes.merge_parities)
+            spins += (int64_t)d.bp_W * 32 * d.N * d.M;
+    return spins > 0 && spins <= kMergeSpins ? lay_plan(inst, n_inst, opt, routes, P) : PT_OK;
+}
+
 
 struct CkptHeader {
     uint32_t magic, version;
