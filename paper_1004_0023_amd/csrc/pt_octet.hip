@@ -34,6 +34,8 @@
 //              call, neighbouring blocks passing boundary groups in device memory, or for many
 //              PT cycles with their exchange steps
 //   oct_clear  E_cl and C of the slice-block octets set to zero before a call
+#include <type_traits>
+
 #include "pt_exchange.h"
 #include "pt_xcd.h"
 #include "pt_internal.h"
@@ -219,12 +221,14 @@ __device__ __forceinline__ uint32_t oct_update(uint32_t X, uint32_t Tlo,
 // halves of Draws (a replica's part of a Philox call).  A lane reads a slot's pair where it
 // would otherwise form two products and two xors per call: whole octets are bound by VALU
 // issue, and this takes the 512-instance batch from 2.32 to 2.18 ms a cycle (1.87e12 to
-// 1.99e12 attempts/s).
+// 1.99e12 attempts/s).  The last wave forms them: in steps of few items it has none of its own
+// (1000 instances of 16 sites, 16 slices and 8 replicas take 62.6 us a cycle where the first wave
+// does it and 60.7 so).
 __device__ __forceinline__ void oct_put_draws(uint32_t at, int sw, uint32_t tt, uint32_t c0, uint32_t key0,
                                               uint32_t key1)
 {
-    const uint32_t r = threadIdx.x;
-    if (r < 8) {
+    const int r = (int)threadIdx.x - ((int)blockDim.x - kWave);
+    if (r >= 0 && r < 8) {
         const Draws d = draws_of(tt, c0 + r, key0, key1);
         st64(at + 64u * (uint32_t)(sw & 1) + 8u * r, ((uint64_t)d.l2 << 32) | d.h2);
     }
@@ -239,6 +243,28 @@ struct OctDraws {
     {
         const uint64_t v = ld64(at + 8u * (uint32_t)r);
         const Draws d = {c1 + kPhiloxM1 * (uint32_t)r, (uint32_t)v, (uint32_t)(v >> 32)};
+        return philox_draw<true>(d, s, L.key0, L.key1);
+    }
+};
+
+// The same for one item of SPL slots taken in order, each slot's pair read while the slot before it
+// draws: the slots are under branches of their own, which keep the compiler from reading ahead.  For
+// lanes of four slots, which are those of steps of few items, where a pair's way from LDS is not
+// hidden: the 1000 instances took 67.4 us a cycle without it, 64.2 with draws formed in registers.
+// With eight slots the two registers it holds cost more than the wait.
+template <int SPL>
+struct OctDrawsAhead {
+    const OctLaunch &L;
+    uint32_t at, c1;
+    uint64_t next;
+    __device__ __forceinline__ OctDrawsAhead(const OctLaunch &L_, uint32_t at_, uint32_t c1_)
+        : L(L_), at(at_), c1(c1_), next(ld64(at_))
+    {
+    }
+    __device__ __forceinline__ Words4 get(const SiteDraws &s, int r)
+    {
+        const Draws d = {c1 + kPhiloxM1 * (uint32_t)r, (uint32_t)next, (uint32_t)(next >> 32)};
+        if (r + 1 < SPL) next = ld64(at + 8u * (uint32_t)(r + 1));
         return philox_draw<true>(d, s, L.key0, L.key1);
     }
 };
@@ -556,7 +582,8 @@ __device__ __forceinline__ void oct_tile_sweeps(const OctLaunch &L, const InstDe
                 const OctSite site = oct_site(o, i);
                 const SiteDraws sd = site_draws((uint32_t)(2 * i + p) * (uint32_t)G4 + (uint32_t)gg,
                                                 (uint32_t)n, L.key0, L.key1);
-                const OctDraws dr = {L, dat + 64u * (uint32_t)((inA ? sw : swB) & 1), c1};
+                using Source = std::conditional_t<SPL == 4, OctDrawsAhead<SPL>, OctDraws>;
+                Source dr{L, dat + 64u * (uint32_t)((inA ? sw : swB) & 1), c1};
                 const uint32_t nx = oct_update<DT, SPL, false>(X, Tlo, Thi, Y, nm, site,
                                                                [&](int r) { return dr.get(sd, r); }, nv, half);
                 if (half == 0) st32(pb + rowi + 4u * (uint32_t)gg, nx);
