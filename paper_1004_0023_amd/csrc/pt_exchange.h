@@ -235,6 +235,7 @@ __device__ __forceinline__ void coop_cycle(const DevState &st, int n, bool first
                                            uint32_t key1, uint32_t t_add, int polls, uint32_t extra, uint32_t err)
 {
     const bool last = cyc + 1 >= cycles;
+    if (polls <= 0) polls = kCoopPolls;
     // every wave's stores complete (a barrier does not wait for them) before the tile counts
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vector-memory count 0, no other
     __syncthreads();
