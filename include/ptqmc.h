@@ -84,8 +84,9 @@ extern "C" {
                            byte of each word) staged in LDS with bit-sliced local fields;
                            others, and batches of fewer octets than compute units where the
                            tuner finds it faster, replica by replica with their spins spread
-                           to bytes in LDS; what fits neither one colour class per launch in
-                           device memory.  The chain is the same as under PT_INT8        */
+                           to bytes in LDS; what fits neither, or runs faster so, one colour
+                           class per launch in device memory.  The chain is the same as
+                           under PT_INT8                                                  */
 
 /* Imaginary-time correlation lags: with PT_FLAG_TAU_CORR every exchange step adds, for
  * each rung r and l < PT_TAU_LAGS, Ct_l = sum_k sum_i s_i^k s_i^{(k + lag_l) mod M} of
